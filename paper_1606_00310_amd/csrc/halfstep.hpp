@@ -73,7 +73,7 @@ __device__ __forceinline__ void mask_words(const SweepArgs& a, uint32_t g, bool 
         if (a.parity == 1) {
             r = *tail;
         } else {
-            const u32x4 o = philox4x32_10(g, a.t, 2u * (uint32_t)j, 0u, a.k0, a.k1);
+            const u32x4 o = philox_word(g, a.t, 2u * (uint32_t)j, a.k0, a.k1);
             r = (uint64_t)o.v0 | ((uint64_t)o.v1 << 32);
             *tail = (uint64_t)o.v2 | ((uint64_t)o.v3 << 32);
         }
@@ -83,7 +83,7 @@ __device__ __forceinline__ void mask_words(const SweepArgs& a, uint32_t g, bool 
     const bool odd = D == Draws::Any && (a.ndraw & 1) != 0;
     for (; j >= 0; --j) {
         const bool shared = odd && 2 * j + 1 == a.ndraw;  // the odd last draw: counter n-1 in both half-steps
-        const u32x4 o = philox4x32_10(g, a.t, 2u * (uint32_t)j + (shared ? 0u : (uint32_t)a.parity), 0u, a.k0, a.k1);
+        const u32x4 o = philox_word(g, a.t, 2u * (uint32_t)j + (shared ? 0u : (uint32_t)a.parity), a.k0, a.k1);
         const uint64_t lo = (uint64_t)o.v0 | ((uint64_t)o.v1 << 32);
         const uint64_t hi = (uint64_t)o.v2 | ((uint64_t)o.v3 << 32);
         // apart from the shared draw every call gives two
@@ -94,25 +94,46 @@ __device__ __forceinline__ void mask_words(const SweepArgs& a, uint32_t g, bool 
     xq = has_q ? (aq | a.all_q) : 0;
 }
 
+// acc <- (acc << 4) | the four bits lane i of o < thr, bit i: each comparison
+// leaves its result as a carry and enters acc as the carry of acc + acc, two
+// instructions per site.  (From C++ the compiler makes a select, a shift and
+// an or of it: three.)  Four compares lie before the first add, so that every
+// add reads its carry three instructions after it was written.
+__device__ __forceinline__ uint32_t shift_in_compares(uint32_t acc, const u32x4& o, uint32_t thr)
+{
+    uint64_t s0, s1, s2, s3;
+    asm("v_cmp_gt_u32_e64 %[s3], %[thr], %[v3]\n\t"
+        "v_cmp_gt_u32_e64 %[s2], %[thr], %[v2]\n\t"
+        "v_cmp_gt_u32_e64 %[s1], %[thr], %[v1]\n\t"
+        "v_cmp_gt_u32_e64 %[s0], %[thr], %[v0]\n\t"
+        "v_addc_co_u32_e64 %[acc], %[s3], %[acc], %[acc], %[s3]\n\t"
+        "v_addc_co_u32_e64 %[acc], %[s2], %[acc], %[acc], %[s2]\n\t"
+        "v_addc_co_u32_e64 %[acc], %[s1], %[acc], %[acc], %[s1]\n\t"
+        "v_addc_co_u32_e64 %[acc], %[s0], %[acc], %[acc], %[s0]"
+        : [acc] "+v"(acc), [s0] "=&s"(s0), [s1] "=&s"(s1), [s2] "=&s"(s2), [s3] "=&s"(s3)
+        : [thr] "s"(thr), [v0] "v"(o.v0), [v1] "v"(o.v1), [v2] "v"(o.v2), [v3] "v"(o.v3));
+    return acc;
+}
+
 // Acceptance words, per-site mode: site bit b compares lane b&3 of call b>>2.
 __device__ __forceinline__ void persite_words(const SweepArgs& a, uint32_t g, bool has_q, uint64_t& xp,
                                               uint64_t& xq)
 {
-    uint32_t lo_p = 0, hi_p = 0, lo_q = 0, hi_q = 0;
+    uint32_t wp[2], wq[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        uint32_t p = 0, q = 0;
 #pragma unroll 4
-    for (int j = 0; j < 16; ++j) {
-        const u32x4 o = philox4x32_10(g, a.t, 2u * (uint32_t)j + (uint32_t)a.parity, 0u, a.k0, a.k1);
-        const uint32_t bits_p = (uint32_t)(o.v0 < a.thr_p) | ((uint32_t)(o.v1 < a.thr_p) << 1) |
-                                ((uint32_t)(o.v2 < a.thr_p) << 2) | ((uint32_t)(o.v3 < a.thr_p) << 3);
-        if (j < 8) lo_p |= bits_p << (4 * j); else hi_p |= bits_p << (4 * (j - 8));
-        if (has_q) {
-            const uint32_t bits_q = (uint32_t)(o.v0 < a.thr_q) | ((uint32_t)(o.v1 < a.thr_q) << 1) |
-                                    ((uint32_t)(o.v2 < a.thr_q) << 2) | ((uint32_t)(o.v3 < a.thr_q) << 3);
-            if (j < 8) lo_q |= bits_q << (4 * j); else hi_q |= bits_q << (4 * (j - 8));
+        for (int j = 8 * half + 7; j >= 8 * half; --j) {  // from the top bits down
+            const u32x4 o = philox_word(g, a.t, 2u * (uint32_t)j + (uint32_t)a.parity, a.k0, a.k1);
+            p = shift_in_compares(p, o, a.thr_p);
+            if (has_q) q = shift_in_compares(q, o, a.thr_q);
         }
+        wp[half] = p;
+        wq[half] = q;
     }
-    xp = ((uint64_t)lo_p | ((uint64_t)hi_p << 32)) | a.all_p;
-    xq = has_q ? (((uint64_t)lo_q | ((uint64_t)hi_q << 32)) | a.all_q) : 0;
+    xp = ((uint64_t)wp[0] | ((uint64_t)wp[1] << 32)) | a.all_p;
+    xq = has_q ? (((uint64_t)wq[0] | ((uint64_t)wq[1] << 32)) | a.all_q) : 0;
 }
 
 // Any bitwise function of three words in one gfx950 v_bitop3_b32 per half:

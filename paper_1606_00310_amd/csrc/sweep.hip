@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void philox_rate_kernel(uint32_t k0, uint32_t 
     const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
     uint32_t acc = 0;
     for (int32_t j = 0; j < calls; ++j) {
-        const u32x4 o = philox4x32_10(g, (uint32_t)j, 0u, 0u, k0, k1);
+        const u32x4 o = philox_word(g, (uint32_t)j, 0u, k0, k1);
         acc ^= o.v0 ^ o.v1 ^ o.v2 ^ o.v3;
     }
     if (acc == k0) sink[g & 255u] = acc;
