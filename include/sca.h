@@ -100,21 +100,22 @@ int sca_init(sca_ctx** out, int64_t X, int64_t Y, uint64_t seed, void* slopes_de
 /* Advances n_mcs >= 0 MCS with deposition probability p and removal
  * probability q (Eq. (2)); each MCS is the even then the odd half-step
  * (Sec. I-A), t grows by n_mcs.  Asynchronous.
- * For X >= 8192 groups of MCS run as temporally blocked passes (all
- * half-steps of `depth` MCS in one sweep over the state, out of place into
- * the caller's pass buffer and back; see sca_set_blocking and
- * sca_set_pass_buffer), which divides the HBM traffic per MCS by about
- * 2*depth.  The passes come in an even number so that S holds the state when
- * the enqueued work has run: whole passes of `depth` MCS, then the remainder
- * r as two passes of ceil(r/2) and floor(r/2) MCS, or two half-step launches
- * when r = 1 (sca_plan_step reports the plan).  The results are bit-identical
- * to the two-launch form.  SCA_ENOBUF (nothing enqueued, t unchanged) if a
- * blocked pass is planned and no pass buffer is attached; sca_set_blocking
+ * Groups of MCS run as temporally blocked passes (all half-steps of `depth`
+ * MCS in one launch, out of place into the caller's pass buffer and back; see
+ * sca_set_blocking and sca_set_pass_buffer), which divides the HBM traffic per
+ * MCS by about 2*depth.  Lattices with X < 8192 do so only if a pass buffer is
+ * attached; small ones may run all MCS in one workgroup instead, in place and
+ * with or without a buffer.  The passes come in an even number so that S holds
+ * the state when the enqueued work has run: whole passes of `depth` MCS, then
+ * the remainder r as two passes of ceil(r/2) and floor(r/2) MCS, or two
+ * half-step launches when r = 1 (sca_plan_step reports the plan).  The results are bit-identical
+ * to the two-launch form.  SCA_ENOBUF (nothing enqueued, t unchanged) if X >=
+ * 8192, a blocked pass is planned and no pass buffer is attached; sca_set_blocking
  * with depth 0 selects the two-launch form, which needs none. */
 int sca_step(sca_ctx* ctx, int64_t n_mcs, double p, double q);
 
 /* sca_step with flags (SCA_FORCE_PERSITE, SCA_STEP_GRAPH).  With
- * SCA_STEP_GRAPH the 2*n_mcs half-step launches are captured into a hipGraph
+ * SCA_STEP_GRAPH the launches of the step are captured into a hipGraph
  * that is launched once (one launch for the whole run) and then released;
  * this call then synchronizes the stream. */
 int sca_step_ex(sca_ctx* ctx, int64_t n_mcs, double p, double q, unsigned flags);
@@ -127,7 +128,8 @@ int sca_step_ex(sca_ctx* ctx, int64_t n_mcs, double p, double q, unsigned flags)
 #define SCA_PATH_PERSITE 2
 
 /* The launches sca_step_ex(ctx, n_mcs, p, q, flags) would enqueue with the
- * context's current blocking settings. */
+ * context's current blocking settings.  All MCS in one workgroup: kernel names
+ * it, band is Y and every count of passes and unfused MCS is 0. */
 typedef struct sca_step_plan {
     int32_t path;          /* SCA_PATH_* */
     int32_t depth;         /* MCS per whole blocked pass; 0 if there is none */
@@ -231,6 +233,9 @@ int sca_get_meta(sca_ctx* ctx, int64_t* t, int64_t* h0);
  * above), 5 on 64-row bands; with random words 4 on bands of >= 128 rows and
  * 3 on 32- and 64-row bands; 2 on 16-row bands and 1 on smaller ones; the
  * per-site path (non-dyadic p or q), which is ALU-bound, is never fused.
+ * With both automatic, lattices that fall short of the tallest band take the
+ * shape of the least estimated time instead.  For X < 8192 a depth and band
+ * set here apply where one workgroup holds the band with its halo.
  * Any setting gives bit-identical results. */
 int sca_set_blocking(sca_ctx* ctx, int32_t depth, int32_t band);
 

@@ -1,8 +1,8 @@
 // api.hip -- the C ABI declared in include/sca.h.
 //
 // Host side only: argument checks, the classification of p and q into the
-// bit-mask path (dyadic) or the per-site compare path, the MCS loop of two
-// half-step launches per MCS (even then odd sublattice, Sec. I-A), and the
+// bit-mask path (dyadic) or the per-site compare path, the choice of launches
+// for a number of MCS (even then odd sublattice each, Sec. I-A), and the
 // device-to-host read-back of exact sums.
 #include <hip/hip_runtime.h>
 
@@ -21,6 +21,42 @@
 #include "sca.h"
 #include "sca_internal.hpp"
 
+namespace sca {
+
+// Acceptance parameters of one probability.
+struct ProbCode {
+    bool dyadic = false;
+    int n = 0;              // fractional binary digits (dyadic)
+    uint32_t digits = 0;    // bit i-1 = b_i
+    uint64_t all = 0;       // ~0 when r == 1
+    uint32_t thr = 0;       // per-site threshold, clamped to 32 bits
+};
+
+// What sca_step_ex runs for n_mcs MCS at (p, q): the acceptance path and the
+// pass plan.  Groups of `depth` MCS run as fused passes alternating
+// S -> pass buffer -> S (one HBM pass per group); the number of passes is
+// kept even so that the caller's S holds the state after the call: an even
+// number of `depth`-MCS passes, then the remainder r < 2*depth as two passes
+// of ceil(r/2) and floor(r/2) MCS, or, for r = 1, two half-step launches.
+// Lattices that one workgroup holds may run in place in one launch instead.
+// The per-site path is ALU-bound and runs unfused.
+struct StepPlan {
+    ProbCode P, Q;
+    bool persite = false, has_q = false, draw_free = false;
+    sca::XiMode mode = sca::XiMode::Mask;
+    int32_t ndraw = 0;
+    int32_t band = 0, depth = 0;
+    int64_t n_pass = 0;
+    int32_t tail1 = 0, tail2 = 0;
+    bool whole = false;     // the lattice in one workgroup, in place: all MCS in one launch
+    int32_t tile_rows = 0;  // rows per thread of the on-chip tiles, 0: row sweeps or half-step launches
+};
+
+}  // namespace sca
+
+using sca::ProbCode;
+using sca::StepPlan;
+
 struct sca_ctx {
     int64_t X = 0, Y = 0;
     int32_t W = 0, nb = 0;
@@ -36,6 +72,12 @@ struct sca_ctx {
     uint64_t* alt = nullptr;        // caller-owned second state for the blocked passes (sca_set_pass_buffer)
     int32_t depth = -1;             // MCS per fused pass; -1 = automatic, 0 = never fuse
     int32_t band = 0;               // rows per workgroup in a fused pass; 0 = automatic
+    // the plan of the last step, kept for the next one with the same arguments
+    // (until the blocking settings or the pass buffer change)
+    StepPlan plan;
+    int64_t plan_n = -1;
+    double plan_p = 0, plan_q = 0;
+    unsigned plan_flags = 0;
 };
 
 namespace {
@@ -74,15 +116,6 @@ int fail(sca_ctx* c)
 int64_t* ws_rows(sca_ctx* c) { return c->ws; }
 int64_t* ws_col(sca_ctx* c) { return c->ws + 3 * c->Y; }
 int64_t* ws_res(sca_ctx* c) { return c->ws + 4 * c->Y; }
-
-// Acceptance parameters of one probability.
-struct ProbCode {
-    bool dyadic = false;
-    int n = 0;              // fractional binary digits (dyadic)
-    uint32_t digits = 0;    // bit i-1 = b_i
-    uint64_t all = 0;       // ~0 when r == 1
-    uint32_t thr = 0;       // per-site threshold, clamped to 32 bits
-};
 
 ProbCode classify(double r)
 {
@@ -164,25 +197,157 @@ hipError_t run_as_graph(hipStream_t& capture, hipStream_t stream, F enqueue)
     return e != hipSuccess ? e : es;
 }
 
-// What sca_step_ex runs for n_mcs MCS at (p, q): the acceptance path and the
-// pass plan.  Groups of `depth` MCS run as fused passes alternating
-// S -> pass buffer -> S (one HBM pass per group); the number of passes is
-// kept even so that the caller's S holds the state after the call: an even
-// number of `depth`-MCS passes, then the remainder r < 2*depth as two passes
-// of ceil(r/2) and floor(r/2) MCS, or, for r = 1, two half-step launches.
-// Automatic choice: a band per workgroup with enough waves to fill the chip
-// and bands as tall as that allows; deep passes on tall bands (the halo costs
-// 4*depth rows per band), shallower ones on short bands.  The per-site path
-// is ALU-bound and runs unfused.
-struct StepPlan {
-    ProbCode P, Q;
-    bool persite = false, has_q = false, draw_free = false;
-    sca::XiMode mode = sca::XiMode::Mask;
-    int32_t ndraw = 0;
-    int32_t band = 0, depth = 0;
-    int64_t n_pass = 0;
-    int32_t tail1 = 0, tail2 = 0;
+// MCS per launch of a whole-lattice tile (a bound on how long one launch runs).
+constexpr int64_t kWholeMcs = 1 << 14;
+
+// The launch shape of a step is chosen by estimated time.  The estimates (in
+// us) are fits to measurements on MI355X over lattices from 2^6 to 2^16 sites
+// wide and high, good to some 20 %:
+//  - V is the number of vector instructions per row word and half-step;
+//  - a half-step of a tile with w waves per CU at work and N words per thread
+//    takes V N/2 (4.7 + 0.44 w) ns, from one wave (p = 1: 0.13 us, p = 1/2:
+//    0.24 us, p = 3/4, q = 1/4: 0.40 us, all latency) to sixteen (0.28, 0.58 and
+//    1.0 us, all vector issue); a launch adds 2.6 us and 0.2 us per MB moved;
+//  - a row sweep (fused.hpp) of b rows and d MCS walks b + 4d - 1 steps of
+//    0.6 us (0.35 us at d = 1) for the row to arrive and 2d half-steps, each the longer of its
+//    latency (p = 1/2 on rows of 2^16 sites: 0.21 us) and the share of the k
+//    waves on its SIMD (0.065 k us); it moves its bytes at 4.7 TB/s, or 6.5 TB/s
+//    where the caches hold both states;
+//  - a half-step launch takes 2.95 us or its state's MB at about 5 TB/s.
+// Against the rule before (bands by width alone, and none below X = 8192) 1440
+// combinations of 60 sizes, four probabilities and 1 .. 100 MCS got faster by
+// 2.3 in the geometric mean (2^10 x 2^9 at p = 1/2: 5.2 to 0.9 us per MCS; 2^12
+// squared at p = 3/4, q = 1/4: 6.1 to 2.4 us; 2^14 squared at p = 1: 12 to 6.7
+// us), and none slower by more than a tenth.
+struct CostModel {
+    double V, draws, mb;  // mb: the state in MB
+    int64_t Y;
+    int32_t W;
+    bool has_q, draw_free;
+
+    CostModel(const sca_ctx* c, const StepPlan& pl)
+        : V(30 + (pl.has_q ? 10 : 0) + 18 * pl.ndraw + 2 * pl.ndraw * (pl.has_q ? 2 : 1)), draws(pl.ndraw),
+          mb(32e-6 * (double)c->Y * c->W), Y(c->Y), W(c->W), has_q(pl.has_q), draw_free(pl.draw_free)
+    {
+    }
+    double half(double waves, int32_t words) const { return V * words / 2 * (0.0047 + 0.00044 * waves); }
+    double unfused() const { return 2 * std::max(2.95, 0.37 * (1 + 0.03 * std::max(1, W / 64) + 0.025 * draws) * mb); }
+    double whole(int64_t n) const { return 2.6 + 10 * mb + 2.0 * (double)n * half((double)((Y / 2 * W + 63) / 64), 2); }
+    double tile(int32_t N, int32_t b, int32_t d) const
+    {
+        const int I = W > 64 ? W / 64 : 1;
+        const int threads = ((b + 4 * d) / N * (W / I) + 63) / 64 * 64;
+        const int64_t per_cu = (Y / b + 255) / 256;  // workgroups on the busiest CU
+        // workgroups a CU holds: of the two-row kernels by threads, of the others by registers
+        const int64_t fit = std::max<int64_t>(1, (N == 2 ? 2048 : 1024) / threads);
+        const int64_t rounds = (per_cu + fit - 1) / fit;
+        const double busy = threads / 64 * (double)(b + 2 * d) / (b + 4 * d) * (double)std::min(per_cu, fit);
+        return 2.6 + (double)rounds * 2 * d * half(busy, N * I) + 0.2 * mb * (2 + 4.0 * d / b);
+    }
+    double sweep(int32_t b, int32_t d) const
+    {
+        const double nw = W / 64;
+        const double k = std::max(nw / 4, (double)(Y / b) * W / 65536.0);  // waves per SIMD
+        const double lat = (0.07 + 0.08 * draws) * (nw > 1 ? 1.0 : 0.7) + 0.02 * std::log2(nw);
+        const double step = draw_free ? (d >= 7 ? 0.45 + d * (0.03 + 0.025 * k) : d == 6 ? 1.25 : mb > 30 ? 1.05 : 0.75)
+                                      : (d > 1 ? 0.6 : 0.35) + 2 * d * std::max(lat, k * (0.03 + 0.035 * draws));
+        return 3.0 + std::max((b + 4.0 * d) * step, mb * (2 + 4.0 * d / b) / (mb > 100 ? 4.7 : 6.5));
+    }
 };
+
+// Splits n MCS into an even number of passes of d MCS and two passes for the
+// rest (make_plan); the estimated time of them all.
+template <typename F>
+double split_cost(int64_t n, int32_t d, F pass, double one)
+{
+    const int64_t np = (n / d) & ~(int64_t)1, rem = n - np * d;
+    double t = np > 0 ? (double)np * pass(d) : 0.0;
+    if (rem == 1) t += one;
+    if (rem >= 2) t += pass((int32_t)((rem + 1) / 2)) + pass((int32_t)(rem / 2));
+    return t;
+}
+
+// Halo rows on either side of a tile's band: the 2 d that d MCS need, whole
+// threads' worth.
+int32_t tile_halo(int32_t N, int32_t d) { return (2 * d + N - 1) / N * N; }
+
+bool tile_fits(int32_t W, int64_t Y, int32_t N, int32_t b, int32_t d)
+{
+    const int I = W > 64 ? 2 : 1;
+    return W <= 128 && (W <= 64 || N == 4) && Y >= b && b % N == 0 &&
+           (b + 2 * tile_halo(N, d)) / N * (W / I) <= (I == 1 ? 1024 : 768);
+}
+
+// The tile of a pass of d MCS.
+sca::TileShape tile_shape(const sca_ctx* c, const StepPlan& pl, int32_t d)
+{
+    if (pl.whole) return sca::TileShape{pl.tile_rows, (int32_t)c->Y, (int32_t)c->Y, 0};
+    const int32_t halo = tile_halo(pl.tile_rows, d);
+    return sca::TileShape{pl.tile_rows, pl.band + 2 * halo, pl.band, halo};
+}
+
+// The passes of n MCS at depth d: an even number of whole ones, and two for
+// the rest unless that is a single MCS.
+void set_passes(StepPlan& pl, int64_t n_mcs, bool fuse)
+{
+    pl.n_pass = fuse ? ((n_mcs / pl.depth) & ~(int64_t)1) : 0;
+    const int64_t rem = n_mcs - pl.n_pass * pl.depth;
+    pl.tail1 = (fuse && rem >= 2) ? (int32_t)((rem + 1) / 2) : 0;
+    pl.tail2 = (fuse && rem >= 2) ? (int32_t)(rem / 2) : 0;
+}
+
+// Chooses by estimated time between half-step launches, the whole lattice in
+// one workgroup, the on-chip tiles and the row sweeps.  Returns false where
+// the half-step launches win.
+bool plan_by_cost(const sca_ctx* c, int64_t n_mcs, StepPlan& pl)
+{
+    const int32_t W = c->W;
+    const int64_t Y = c->Y;
+    const CostModel m(c, pl);
+    double best = (double)n_mcs * m.unfused();
+    bool fuse = false;
+    if (W < 64 && Y / 2 * W <= 1024 && m.whole(n_mcs) < best) {
+        best = m.whole(n_mcs);
+        pl.whole = true;
+        pl.tile_rows = 2;
+    }
+    if (!c->alt || n_mcs < 2) return false;
+    auto consider = [&](double t, int32_t N, int32_t b, int32_t d) {
+        if (t >= best) return;
+        best = t;
+        fuse = true;
+        pl.whole = false;
+        pl.tile_rows = N;
+        pl.band = b;
+        pl.depth = d;
+    };
+    const int32_t dmax = sca::max_fused_depth(W, pl.mode, pl.ndraw);
+    // The sweep that the band and depth on entry describe (the shape of the
+    // larger lattices scaled down) stays unless another shape is estimated to
+    // be 15 % faster: more than the estimates err between shapes.
+    const int32_t b0 = pl.band, d0 = std::min(pl.depth, dmax);
+    if (d0 > 0 && sca::fused_supported(W, Y, b0, d0, pl.mode, pl.ndraw))
+        consider(0.85 * split_cost(n_mcs, d0, [&](int32_t e) { return m.sweep(b0, e); }, m.unfused()), 0, b0, d0);
+    // with 2 d >= n all of it is one pair of passes
+    const int32_t half = (int32_t)std::min<int64_t>((n_mcs + 1) / 2, 64);
+    for (int32_t b : {8, 16, 32, 64, 128})
+        for (int32_t dd : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
+            const int32_t d = std::min(dd, half);
+            for (int32_t N : {2, 4})
+                if (tile_fits(W, Y, N, b, d))
+                    consider(split_cost(n_mcs, d, [&](int32_t e) { return m.tile(N, b, e); }, m.unfused()), N, b, d);
+            if (d == half) break;
+        }
+    for (int32_t b : {8, 16, 32, 64, 128, 256})
+        for (int32_t dd : {1, 2, 3, 4, 6, 8, 10, 13}) {
+            const int32_t d = std::min(dd, half);
+            if (d > dmax) break;
+            if (sca::fused_supported(W, Y, b, d, pl.mode, pl.ndraw))
+                consider(split_cost(n_mcs, d, [&](int32_t e) { return m.sweep(b, e); }, m.unfused()), 0, b, d);
+            if (d == half) break;
+        }
+    return fuse;
+}
 
 StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
 {
@@ -193,6 +358,7 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
     pl.has_q = (q > 0.0);
     pl.mode = pl.persite ? sca::XiMode::PerSite : sca::XiMode::Mask;
     pl.ndraw = pl.persite ? 0 : (pl.P.n > pl.Q.n ? pl.P.n : pl.Q.n);
+    const bool automatic = c->depth < 0 && c->band == 0;
     const int64_t nw = c->W >= 512 ? 8 : (c->W >= 64 ? c->W / 64 : 1);
     // Without random words (p, q in {0, 1}) a pass costs little more than
     // a shallower one as long as its window fits the registers: 13 MCS at
@@ -201,9 +367,10 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
     // rows (about one workgroup per CU); passes with draws are ALU-bound and
     // do best at 4 MCS on bands of up to 128 rows.
     pl.draw_free = !pl.persite && pl.ndraw == 0;
+    const int32_t tall = pl.draw_free ? 256 : 128;
     int32_t band = c->band;
     if (band == 0) {
-        int64_t b = pl.draw_free ? 256 : 128;
+        int64_t b = tall;
         while (b > 8 && c->Y / b < 2048 / nw) b >>= 1;
         band = (int32_t)b;
     }
@@ -219,14 +386,29 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
                            : band >= 16 ? 2
                                         : 1;
     }
+    const bool may_fuse = !(flags & SCA_NO_FUSE) && depth > 0 && n_mcs >= 1;
+    // Lattices too small for full-height bands (and, from X = 8192 on, with
+    // the pass buffer that all their passes need) go by cost.
+    if (automatic && may_fuse && !pl.persite && c->W <= 512 && band < tall && (c->W < 64 || c->alt)) {
+        pl.depth = depth;
+        const bool fuse = plan_by_cost(c, n_mcs, pl);
+        set_passes(pl, n_mcs, fuse);
+        return pl;
+    }
+    if (c->W < 64) {
+        // explicit depth and band, where they make a tile
+        pl.depth = depth;
+        bool fuse = may_fuse && !pl.persite && n_mcs >= 2 && c->alt != nullptr;
+        if (fuse) {
+            pl.tile_rows = tile_fits(c->W, c->Y, 2, band, depth) ? 2 : tile_fits(c->W, c->Y, 4, band, depth) ? 4 : 0;
+            fuse = pl.tile_rows != 0;
+        }
+        set_passes(pl, n_mcs, fuse);
+        return pl;
+    }
     if (depth > dmax) depth = dmax;
     pl.depth = depth;
-    const bool fuse = !(flags & SCA_NO_FUSE) && depth > 0 && n_mcs >= 2 &&
-                      sca::fused_supported(c->W, c->Y, band, depth, pl.mode, pl.ndraw);
-    pl.n_pass = fuse ? ((n_mcs / depth) & ~(int64_t)1) : 0;
-    const int64_t rem = n_mcs - pl.n_pass * depth;
-    pl.tail1 = (fuse && rem >= 2) ? (int32_t)((rem + 1) / 2) : 0;
-    pl.tail2 = (fuse && rem >= 2) ? (int32_t)(rem / 2) : 0;
+    set_passes(pl, n_mcs, may_fuse && n_mcs >= 2 && sca::fused_supported(c->W, c->Y, band, depth, pl.mode, pl.ndraw));
     return pl;
 }
 
@@ -319,7 +501,14 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
         return SCA_EINVAL;
     if (c->t + n_mcs > (int64_t)UINT32_MAX) return SCA_EINVAL;
     if (n_mcs == 0) return SCA_OK;
-    const StepPlan pl = make_plan(c, n_mcs, p, q, flags);
+    if (n_mcs != c->plan_n || p != c->plan_p || q != c->plan_q || flags != c->plan_flags) {
+        c->plan = make_plan(c, n_mcs, p, q, flags);
+        c->plan_n = n_mcs;
+        c->plan_p = p;
+        c->plan_q = q;
+        c->plan_flags = flags;
+    }
+    const StepPlan& pl = c->plan;
     // the blocked passes alternate between S and the caller's pass buffer
     if (pl.n_pass + (pl.tail1 ? 2 : 0) > 0 && !c->alt) return SCA_ENOBUF;
     DeviceGuard dg(c->device);
@@ -329,13 +518,25 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
     const int64_t t0 = c->t;
     const int64_t n_fused = pl.n_pass * pl.depth + pl.tail1 + pl.tail2;
     auto enqueue = [&](hipStream_t st) -> hipError_t {
+        if (pl.whole) {
+            for (int64_t i = 0; i < n_mcs; i += kWholeMcs) {
+                a.t = (uint32_t)(t0 + i);
+                const hipError_t e = sca::launch_tile(a, pl.mode, pl.has_q, c->S, c->S, tile_shape(c, pl, 0),
+                                                      (int32_t)std::min(kWholeMcs, n_mcs - i), st);
+                if (e != hipSuccess) return e;
+            }
+            return hipSuccess;
+        }
         for (int64_t i = 0; i < pl.n_pass + (pl.tail1 ? 2 : 0); ++i) {
             const bool tail = i >= pl.n_pass;
             const int32_t d = !tail ? pl.depth : (i == pl.n_pass ? pl.tail1 : pl.tail2);
             a.t = (uint32_t)(t0 + (!tail ? i * pl.depth : pl.n_pass * pl.depth + (i == pl.n_pass ? 0 : pl.tail1)));
             const bool fwd = (i & 1) == 0;
-            const hipError_t e = sca::launch_mcs_fused(a, pl.mode, pl.has_q, fwd ? c->S : c->alt,
-                                                       fwd ? c->alt : c->S, pl.band, d, st);
+            const uint64_t* src = fwd ? c->S : c->alt;
+            uint64_t* dst = fwd ? c->alt : c->S;
+            const hipError_t e =
+                pl.tile_rows > 0 ? sca::launch_tile(a, pl.mode, pl.has_q, src, dst, tile_shape(c, pl, d), d, st)
+                                 : sca::launch_mcs_fused(a, pl.mode, pl.has_q, src, dst, pl.band, d, st);
             if (e != hipSuccess) return e;
         }
         for (int64_t i = n_fused; i < n_mcs; ++i) {
@@ -362,16 +563,20 @@ int sca_plan_step(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned 
     const StepPlan pl = make_plan(c, n_mcs, p, q, flags);
     std::memset(out, 0, sizeof *out);
     out->path = pl.persite ? SCA_PATH_PERSITE : (pl.draw_free ? SCA_PATH_DRAWFREE : SCA_PATH_MASK);
-    out->band = pl.band;
+    out->band = pl.whole ? (int32_t)c->Y : pl.band;
     out->n_pass = pl.n_pass;
     out->depth = pl.n_pass > 0 ? pl.depth : 0;
     out->tail1 = pl.tail1;
     out->tail2 = pl.tail2;
-    out->n_unfused = n_mcs - (pl.n_pass * pl.depth + pl.tail1 + pl.tail2);
+    out->n_unfused = pl.whole ? 0 : n_mcs - (pl.n_pass * pl.depth + pl.tail1 + pl.tail2);
     const sca::SweepArgs a = sweep_args(c, pl);
-    if (pl.n_pass > 0) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.depth, out->kernel, sizeof out->kernel);
+    if (pl.whole || (pl.n_pass > 0 && pl.tile_rows > 0))
+        sca::tile_kernel_name(a, pl.has_q, pl.tile_rows, out->kernel, sizeof out->kernel);
+    else if (pl.n_pass > 0) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.depth, out->kernel, sizeof out->kernel);
     else std::snprintf(out->kernel, sizeof out->kernel, "none");
-    if (pl.tail1) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.tail1, out->tail_kernel, sizeof out->tail_kernel);
+    if (pl.tail1 && pl.tile_rows > 0)
+        sca::tile_kernel_name(a, pl.has_q, pl.tile_rows, out->tail_kernel, sizeof out->tail_kernel);
+    else if (pl.tail1) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.tail1, out->tail_kernel, sizeof out->tail_kernel);
     else std::snprintf(out->tail_kernel, sizeof out->tail_kernel, "none");
     sca::halfstep_kernel_name(c->W, pl.mode, pl.has_q, out->halfstep_kernel, sizeof out->halfstep_kernel);
     return SCA_OK;
@@ -384,11 +589,13 @@ int sca_set_pass_buffer(sca_ctx* c, void* pass_dev, size_t bytes)
     const size_t need = sizeof(uint64_t) * (size_t)(4 * c->Y * c->W);
     if (!pass_dev) {
         c->alt = nullptr;
+        c->plan_n = -1;
         return SCA_OK;
     }
     const uintptr_t a0 = (uintptr_t)pass_dev, s0 = (uintptr_t)c->S;
     if (bytes < need || (pass_dev && a0 < s0 + need && s0 < a0 + need)) return SCA_EINVAL;
     c->alt = static_cast<uint64_t*>(pass_dev);
+    c->plan_n = -1;
     return SCA_OK;
 }
 
@@ -587,6 +794,7 @@ int sca_set_blocking(sca_ctx* c, int32_t depth, int32_t band)
         return SCA_EINVAL;
     c->depth = depth;
     c->band = band;
+    c->plan_n = -1;
     return SCA_OK;
 }
 

@@ -26,6 +26,20 @@ hipError_t launch_mcs_fused(const SweepArgs& a, XiMode mode, bool has_q, const u
 void fused_kernel_name(const SweepArgs& a, XiMode mode, bool has_q, int32_t depth, char* out, size_t n);
 void halfstep_kernel_name(int32_t W, XiMode mode, bool has_q, char* out, size_t n);
 
+// A tile of the on-chip sweep (tile.hpp): `rows` rows per workgroup, of which
+// the `band` rows behind the first `halo` are written; halo = 0: the tile is
+// the whole lattice (rows = band = Y), in place and for any number of MCS.
+// Otherwise halo >= 2 n_mcs, src and dst are different states and the bands
+// partition Y.
+struct TileShape {
+    int32_t rows_per_thread = 0;  // 0: no tile serves the lattice
+    int32_t rows = 0, band = 0, halo = 0;
+};
+hipError_t launch_tile(const SweepArgs& a, XiMode mode, bool has_q, const uint64_t* src, uint64_t* dst,
+                       const TileShape& s, int32_t n_mcs, hipStream_t stream);
+
+void tile_kernel_name(const SweepArgs& a, bool has_q, int32_t rows_per_thread, char* out, size_t n);
+
 // Flat initial surface into S and h0 = 0.
 hipError_t launch_flat_init(uint64_t* S, int64_t Y, int32_t W, int32_t nb, int64_t* h0,
                             hipStream_t stream);

@@ -26,18 +26,17 @@ class Lattice:
         self.W = max(1, self.X // 128)
         self.slopes = torch.empty((2, 2, self.Y, self.W), dtype=torch.int64, device=self.device)
         self.aux = torch.zeros(L.SCA_AUX_LEN, dtype=torch.int64, device=self.device)
-        # the temporally blocked passes (X >= 8192) run out of place into a
-        # second buffer of the state's size
-        self.pass_buffer = torch.empty_like(self.slopes) if self.X >= 8192 else None
+        # passes of several MCS run out of place into a second buffer of the
+        # state's size
+        self.pass_buffer = torch.empty_like(self.slopes)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         ctx = ctypes.c_void_p()
         with torch.cuda.device(self.device):
             L.check(L.lib().sca_init(ctypes.byref(ctx), self.X, self.Y, self.seed, self.slopes.data_ptr(),
                                      self.aux.data_ptr(), self.stream.cuda_stream), "sca_init")
         self._ctx = ctx
-        if self.pass_buffer is not None:
-            L.check(L.lib().sca_set_pass_buffer(ctx, self.pass_buffer.data_ptr(),
-                                                self.pass_buffer.numel() * 8), "sca_set_pass_buffer")
+        L.check(L.lib().sca_set_pass_buffer(ctx, self.pass_buffer.data_ptr(), self.pass_buffer.numel() * 8),
+                "sca_set_pass_buffer")
 
     # ------------------------------------------------------------------ steps
     def step(self, n_mcs: int, p: float, q: float = 0.0, force_persite: bool = False, graph: bool = False,
