@@ -8,12 +8,15 @@
 // Row y's x-slopes interleave two words per 128 sites: even x in the x-array
 // of parity y&1, odd x in that of parity 1-(y&1), bit x>>1.
 //
-// Moments decompose exactly: for a 128-site word with base B (= P at the
-// site before it) and local prefix d_i,
-//   sum (B + d_i) = n B + sum d_i,   sum (B + d_i)^2 = n B^2 + 2 B sum d_i + sum d_i^2,
-// so each lane forms int32 local sums, a wave scan forms the bases, and the
-// per-row int64 results are combined with c(y) by one workgroup in 128-bit
-// integer arithmetic.  Nothing is rounded at any stage.
+// Moments decompose exactly.  Eight consecutive sites are looked up at once: a
+// table in LDS gives, for their eight slope bits, the running counts c_1..c_8
+// of rises as eight nibbles, so that with the height K in front of them the
+// heights are K + 2 c_i - i and every sum over them is a v_dot8_u32_u4 of
+// nibbles:  sum c = c.(1..1),  sum c^2 = c.c,  sum i c = c.(1,2,..8), and for
+// two states  sum c_t c_s = c_t.c_s.  Words, rows and blocks of rows then
+// combine by
+//   sum (B + d_i) = n B + sum d_i,   sum (B + d_i)^2 = n B^2 + 2 B sum d_i + sum d_i^2
+// in int64, and the blocks in 128 bits.  Nothing is rounded at any stage.
 #include "sca_internal.hpp"
 
 namespace sca {
@@ -47,306 +50,490 @@ __global__ __launch_bounds__(kBlock) void flat_init_many_kernel(const FlatItem* 
     }
 }
 
-// Local sums of one word pair (even-x word E, odd-x word O) over its 2*nb
-// sites; the global site x = 0 contributes no step (skip0).
-struct WordSums {
-    int32_t tot;  // sum of the steps e_i
-    int32_t sd;   // sum of prefixes d_i
-    int32_t sd2;  // sum of d_i^2
-};
+// ---------------------------------------------------------------- sums of one word pair
+// Eight nibbles 1 and the nibbles 1..8.
+constexpr uint32_t kOnes = 0x11111111u, kRamp = 0x87654321u;
 
-__device__ __forceinline__ WordSums word_sums(uint64_t E, uint64_t O, int nb, bool skip0)
+// The running counts of rises over the eight sites whose even-x slopes are the
+// low four bits of `byte` and whose odd-x slopes the high four.
+__device__ __forceinline__ uint32_t running_counts(uint32_t byte)
 {
-    int32_t d = 0, sd = 0, sd2 = 0;
-    for (int k = 0; k < nb; ++k) {
-        if (!(skip0 && k == 0)) d += 2 * (int32_t)((E >> k) & 1ull) - 1;
-        sd += d;
-        sd2 += d * d;
-        d += 2 * (int32_t)((O >> k) & 1ull) - 1;
-        sd += d;
-        sd2 += d * d;
+    uint32_t c = 0, out = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        c += (byte >> k) & 1u;
+        out |= c << (8 * k);
+        c += (byte >> (4 + k)) & 1u;
+        out |= c << (8 * k + 4);
     }
-    return {d, sd, sd2};
+    return out;
 }
 
-// Two-time version: prefixes of two states in lockstep and their product sum.
-__device__ __forceinline__ void word_sums2(uint64_t Et, uint64_t Ot, uint64_t Es, uint64_t Os, int nb, bool skip0,
-                                           int32_t& tt, int32_t& sdt, int32_t& ts, int32_t& sds, int32_t& sdd)
+__device__ __forceinline__ uint32_t dot8(uint32_t a, uint32_t b, uint32_t acc)
 {
-    int32_t dt = 0, ds = 0;
-    sdt = sds = sdd = 0;
-    for (int k = 0; k < nb; ++k) {
-        if (!(skip0 && k == 0)) {
-            dt += 2 * (int32_t)((Et >> k) & 1ull) - 1;
-            ds += 2 * (int32_t)((Es >> k) & 1ull) - 1;
-        }
-        sdt += dt; sds += ds; sdd += dt * ds;
-        dt += 2 * (int32_t)((Ot >> k) & 1ull) - 1;
-        ds += 2 * (int32_t)((Os >> k) & 1ull) - 1;
-        sdt += dt; sds += ds; sdd += dt * ds;
+    return __builtin_amdgcn_udot8(a, b, acc, false);
+}
+
+// The table indices of a half word pair's eight chunks, in site order: byte m
+// of `even` is chunk 2m, of `odd` chunk 2m+1.
+struct ChunkBytes {
+    uint32_t even, odd;
+    __device__ __forceinline__ ChunkBytes(uint32_t e, uint32_t o)
+        : even((e & 0x0f0f0f0fu) | ((o & 0x0f0f0f0fu) << 4)), odd(((e >> 4) & 0x0f0f0f0fu) | (o & 0xf0f0f0f0u))
+    {
     }
-    tt = dt;
-    ts = ds;
+    __device__ __forceinline__ uint32_t operator[](int j) const
+    {
+        return (((j & 1) ? odd : even) >> (8 * (j >> 1))) & 255u;
+    }
+};
+
+// Sums over the 8 * chunks sites of a word pair (even-x word E, odd-x word O)
+// of the heights d_i relative to the site in front of the first.
+struct WordSums {
+    int32_t tot;  // d of the last site
+    int32_t s1;   // sum of d_i
+    int32_t s2;   // sum of d_i^2, or of d_i d'_i for two states
+};
+
+// Eight sites behind height B: sum d = 8 B + 2 s - 36 and sum d^2 = 8 B^2 +
+// 2 B (2 s - 36) + 4 c.c - 4 c.ramp + 204 with s = c.(1..1).
+__device__ __forceinline__ WordSums word_sums(const uint32_t* lut, uint64_t E, uint64_t O, int chunks)
+{
+    int32_t B = 0, sB = 0, sBB = 0, sBs = 0;
+    uint32_t S = 0, cc = 0, cr = 0;
+    auto half = [&](uint32_t e, uint32_t o, int n) {
+        const ChunkBytes idx(e, o);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (j >= n) break;
+            const uint32_t c = lut[idx[j]];
+            const uint32_t s = dot8(c, kOnes, 0);
+            cc = dot8(c, c, cc);
+            cr = dot8(c, kRamp, cr);
+            S += s;
+            sB += B;
+            sBB += B * B;
+            sBs += B * (int32_t)s;
+            B += 2 * (int32_t)(c >> 28) - 8;
+        }
+    };
+    if (chunks == 16) {
+        half((uint32_t)E, (uint32_t)O, 8);
+        half((uint32_t)(E >> 32), (uint32_t)(O >> 32), 8);
+    } else {
+        half((uint32_t)E, (uint32_t)O, chunks);
+    }
+    return {B, 8 * sB + 2 * (int32_t)S - 36 * chunks,
+            8 * sBB + 4 * sBs - 72 * sB + 4 * (int32_t)cc - 4 * (int32_t)cr + 204 * chunks};
+}
+
+// Two states t and s: sum d_t d_s = 8 Bt Bs + Bt (2 ss - 36) + Bs (2 st - 36)
+// + 4 ct.cs - 2 ct.ramp - 2 cs.ramp + 204.
+__device__ __forceinline__ void word_sums2(const uint32_t* lut, uint64_t Et, uint64_t Ot, uint64_t Es, uint64_t Os,
+                                           int chunks, WordSums& t, WordSums& s)
+{
+    int32_t Bt = 0, Bs = 0, sBt = 0, sBs = 0, m = 0;
+    uint32_t St = 0, Ss = 0, cc = 0, cr = 0;
+    auto half = [&](uint32_t et, uint32_t ot, uint32_t es, uint32_t os, int n) {
+        const ChunkBytes it(et, ot), is(es, os);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (j >= n) break;
+            const uint32_t ct = lut[it[j]], cs = lut[is[j]];
+            const uint32_t st = dot8(ct, kOnes, 0), ss = dot8(cs, kOnes, 0);
+            cc = dot8(ct, cs, cc);
+            cr = dot8(cs, kRamp, dot8(ct, kRamp, cr));
+            St += st;
+            Ss += ss;
+            sBt += Bt;
+            sBs += Bs;
+            m += Bt * (4 * Bs + (int32_t)ss) + Bs * (int32_t)st;
+            Bt += 2 * (int32_t)(ct >> 28) - 8;
+            Bs += 2 * (int32_t)(cs >> 28) - 8;
+        }
+    };
+    if (chunks == 16) {
+        half((uint32_t)Et, (uint32_t)Ot, (uint32_t)Es, (uint32_t)Os, 8);
+        half((uint32_t)(Et >> 32), (uint32_t)(Ot >> 32), (uint32_t)(Es >> 32), (uint32_t)(Os >> 32), 8);
+    } else {
+        half((uint32_t)Et, (uint32_t)Ot, (uint32_t)Es, (uint32_t)Os, chunks);
+    }
+    t = {Bt, 8 * sBt + 2 * (int32_t)St - 36 * chunks,
+         2 * m - 36 * (sBt + sBs) + 4 * (int32_t)cc - 2 * (int32_t)cr + 204 * chunks};
+    s = {Bs, 8 * sBs + 2 * (int32_t)Ss - 36 * chunks, 0};
+}
+
+// Two sites per word (X = 4): too few for a table entry.
+__device__ __forceinline__ void four_sites(uint64_t E, uint64_t O, int32_t (&d)[4])
+{
+    int32_t h = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        h += 2 * (int32_t)((((k & 1) ? O : E) >> (k >> 1)) & 1ull) - 1;
+        d[k] = h;
+    }
 }
 
 // Inclusive scan across the G lanes of a row group.
 template <int G>
-__device__ __forceinline__ int64_t group_incl_scan(int64_t v, int gl)
+__device__ __forceinline__ int32_t group_incl_scan(int32_t v, int gl)
 {
 #pragma unroll
     for (int off = 1; off < G; off <<= 1) {
-        const int64_t o = __shfl_up(v, off, G);
+        const int32_t o = __shfl_up(v, off, G);
         if (gl >= off) v += o;
     }
     return v;
 }
 
-template <int G>
-__device__ __forceinline__ int64_t group_sum(int64_t v)
+// ---------------------------------------------------------------- moments
+constexpr int kSumBlock = 1024;              // threads of a block of rows
+constexpr int kSumRows = 1024;               // rows of a block at most
+constexpr int kPartial = kMomentsPartial;    // int64 per block
+
+// Heights of column 0 for the R rows from y0 on, relative to the row in front
+// of the block (to row 0's own height in the block with row 0), less the slope
+// at x = 0: what a row's path from x = 0 on, that slope included, starts from.
+// col: the last row's height of column 0.  One row per thread.
+__device__ __forceinline__ void row_bases(const uint64_t* S, int64_t plane, int32_t W, int64_t y0, int R, int32_t* rb,
+                                          int32_t* col, int32_t* waves)
 {
-#pragma unroll
-    for (int off = G / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, G);
-    return v;
-}
-
-// rows[3y..3y+2]: {sum P_t, sum P_t^2, 0} or, with a snapshot,
-// {sum P_t, sum P_t P_s, sum P_s}.
-template <int G, bool TWO>
-__global__ __launch_bounds__(kBlock) void row_sums_kernel(const uint64_t* S, const uint64_t* snap, int64_t Y,
-                                                         int32_t W, int32_t nb, int64_t plane, int64_t* rows)
-{
-    const int lane = threadIdx.x & 63;
-    const int gl = lane & (G - 1);
-    const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    const int64_t y_raw = wave * (64 / G) + lane / G;
-    const bool active = y_raw < Y;
-    const int64_t y = active ? y_raw : 0;
-    const int pe = (int)(y & 1);
-    const uint64_t* Et = S + (int64_t)pe * plane + y * W;        // x-slopes of even x
-    const uint64_t* Ot = S + (int64_t)(1 - pe) * plane + y * W;  // x-slopes of odd x
-    const uint64_t* Es = TWO ? snap + (int64_t)pe * plane + y * W : nullptr;
-    const uint64_t* Os = TWO ? snap + (int64_t)(1 - pe) * plane + y * W : nullptr;
-
-    int64_t acc1 = 0, acc2 = 0, acc3 = 0, carry_t = 0, carry_s = 0;
-    for (int c = 0; c < W / G; ++c) {
-        const int w = c * G + gl;
-        const int64_t n = 2 * (int64_t)nb - (w == 0 ? 1 : 0);
-        if constexpr (!TWO) {
-            const WordSums s = word_sums(Et[w], Ot[w], nb, w == 0);
-            const int64_t incl = group_incl_scan<G>((int64_t)s.tot, gl);
-            const int64_t b = carry_t + incl - s.tot;
-            carry_t += __shfl(incl, (lane & ~(G - 1)) + G - 1);
-            acc1 += n * b + s.sd;
-            acc2 += n * b * b + 2 * b * s.sd + s.sd2;
-        } else {
-            int32_t tt, sdt, ts, sds, sdd;
-            word_sums2(Et[w], Ot[w], Es[w], Os[w], nb, w == 0, tt, sdt, ts, sds, sdd);
-            const int64_t it = group_incl_scan<G>((int64_t)tt, gl);
-            const int64_t is = group_incl_scan<G>((int64_t)ts, gl);
-            const int64_t bt = carry_t + it - tt;
-            const int64_t bs = carry_s + is - ts;
-            carry_t += __shfl(it, (lane & ~(G - 1)) + G - 1);
-            carry_s += __shfl(is, (lane & ~(G - 1)) + G - 1);
-            acc1 += n * bt + sdt;
-            acc2 += n * bt * bs + bt * sds + bs * sdt + sdd;
-            acc3 += n * bs + sds;
-        }
-    }
-    acc1 = group_sum<G>(acc1);
-    acc2 = group_sum<G>(acc2);
-    acc3 = group_sum<G>(acc3);
-    if (active && gl == 0) {
-        rows[3 * y + 0] = acc1;
-        rows[3 * y + 1] = acc2;
-        rows[3 * y + 2] = acc3;
-    }
-}
-
-constexpr int kCombine = 1024;
-
-// Exclusive block-wide scan of one int64 per thread (1024 threads).
-__device__ int64_t block_excl_scan(int64_t v, int64_t* lds_waves)
-{
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int64_t incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-    }
-    if (lane == 63) lds_waves[wid] = incl;
+    const int r = (int)threadIdx.x, lane = r & 63, wv = r >> 6;
+    const int64_t y = y0 + (r < R ? r : 0);
+    const int64_t base = (y & 1) * plane + y * W;
+    const uint64_t x0 = S[base], yw = S[2 * plane + base];  // the even-x word holds x = 0
+    const int32_t step = (y == 0 || r >= R) ? 0 : 2 * (int32_t)(yw & 1ull) - 1;
+    const int32_t incl = group_incl_scan<64>(step, lane);
+    if (lane == 63) waves[wv] = incl;
     __syncthreads();
-    int64_t before = 0;
-    for (int k = 0; k < wid; ++k) before += lds_waves[k];
+    int32_t before = 0;
+    for (int k = 0; k < wv; ++k) before += waves[k];
+    if (r < R) rb[r] = before + incl - (2 * (int32_t)(x0 & 1ull) - 1);
+    if (r == R - 1) *col = before + incl;
     __syncthreads();
-    return before + incl - v;
 }
 
-// Column prefix c(y) for every row (written to col) and the exact totals:
-//   moments:   res = {sum h, sum h^2, 0}
-//   two-time:  res = {sum h_t, sum h_t h_s, sum h_s}
-// each as a (lo, hi) pair of a 128-bit integer.
-__global__ __launch_bounds__(kCombine) void combine_kernel(const uint64_t* S, const int64_t* h0, const uint64_t* snap,
-                                                          const int64_t* snap_h0, int64_t X, int64_t Y, int32_t W,
-                                                          int64_t plane, const int64_t* rows, int64_t* col,
-                                                          int64_t* res)
+struct Sums128 {
+    __int128 v[3];
+};
+
+// Adds one block's sums (relative to its first row's predecessor) at the
+// absolute heights Ct, Cs: {sum h, sum h^2, 0} or {sum h_t, sum h_t h_s, sum h_s}.
+__device__ __forceinline__ void add_block(Sums128& t, const int64_t* p, int64_t n, int64_t Ct, int64_t Cs, bool two)
 {
-    __shared__ int64_t lds_waves[kCombine / 64];
-    __shared__ __int128 lds_red[kCombine / 64][3];
-    const bool two = (snap != nullptr);
-    const int64_t per = (Y + kCombine - 1) / kCombine;
-    const int64_t ya = (int64_t)threadIdx.x * per;
-    const int64_t yb = ya + per < Y ? ya + per : Y;
-
-    // steps down column 0: e_y = 2 sy(0,y) - 1 for y >= 1; sy(0,y) is bit 0 of
-    // word 0 of row y in the y-array of parity y&1.
-    auto step = [&](const uint64_t* base, int64_t yy) -> int64_t {
-        if (yy == 0) return 0;
-        const uint64_t wrd = base[(int64_t)(2 + (yy & 1)) * plane + yy * W];
-        return 2 * (int64_t)(wrd & 1ull) - 1;
-    };
-    int64_t loc_t = 0, loc_s = 0;
-    for (int64_t yy = ya; yy < yb; ++yy) {
-        loc_t += step(S, yy);
-        if (two) loc_s += step(snap, yy);
+    const int64_t a1 = p[0], a2 = p[1], a3 = p[2];
+    t.v[0] += (__int128)n * Ct + a1;
+    if (!two) {
+        t.v[1] += (__int128)n * Ct * Ct + (__int128)2 * Ct * a1 + a2;
+    } else {
+        t.v[1] += (__int128)n * Ct * Cs + (__int128)Ct * a3 + (__int128)Cs * a1 + a2;
+        t.v[2] += (__int128)n * Cs + a3;
     }
-    const int64_t ex_t = block_excl_scan(loc_t, lds_waves);
-    const int64_t ex_s = two ? block_excl_scan(loc_s, lds_waves) : 0;
+}
 
-    int64_t ct = *h0 + ex_t;
-    int64_t cs = two ? *snap_h0 + ex_s : 0;
-    __int128 t1 = 0, t2 = 0, t3 = 0;
-    for (int64_t yy = ya; yy < yb; ++yy) {
-        ct += step(S, yy);
-        if (col) col[yy] = ct;
-        const int64_t r1 = rows ? rows[3 * yy] : 0, r2 = rows ? rows[3 * yy + 1] : 0, r3 = rows ? rows[3 * yy + 2] : 0;
-        if (!two) {
-            t1 += (__int128)X * ct + r1;
-            t2 += (__int128)X * ct * ct + (__int128)2 * ct * r1 + r2;
-        } else {
-            cs += step(snap, yy);
-            t1 += (__int128)X * ct + r1;
-            t2 += (__int128)X * ct * cs + (__int128)ct * r3 + (__int128)cs * r1 + r2;
-            t3 += (__int128)X * cs + r3;
-        }
-    }
-    if (!res) return;
-    // block reduction of the three 128-bit sums
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    __int128 v[3] = {t1, t2, t3};
+__device__ __forceinline__ void store_sums(const Sums128& t, int64_t* res, const int32_t* flag)
+{
     for (int k = 0; k < 3; ++k) {
-        int64_t lo = (int64_t)(uint64_t)v[k];
-        int64_t hi = (int64_t)(v[k] >> 64);
-        // reduce as 128-bit via lane shuffles of both halves
-        for (int off = 32; off > 0; off >>= 1) {
-            const uint64_t olo = (uint64_t)__shfl_down(lo, off, 64);
-            const int64_t ohi = __shfl_down(hi, off, 64);
-            const __int128 a = ((__int128)hi << 64) | (uint64_t)lo;
-            const __int128 b = ((__int128)ohi << 64) | olo;
-            const __int128 s = (lane + off < 64) ? a + b : a;
-            lo = (int64_t)(uint64_t)s;
-            hi = (int64_t)(s >> 64);
-        }
-        if (lane == 0) lds_red[wid][k] = ((__int128)hi << 64) | (uint64_t)lo;
+        res[2 * k] = (int64_t)(uint64_t)t.v[k];
+        res[2 * k + 1] = (int64_t)(t.v[k] >> 64);
+    }
+    res[6] = flag ? *flag : 0;
+}
+
+constexpr int kCombine = 256;  // blocks of rows at most
+
+// The blocks' sums at their absolute heights, in 128 bits: one block of rows
+// per thread.
+__global__ __launch_bounds__(kCombine) void combine_kernel(const int64_t* h0, const int64_t* snap_h0, bool two,
+                                                          const int64_t* partials, int32_t blocks, int64_t sites,
+                                                          int64_t* res, const int32_t* flag)
+{
+    __shared__ int32_t colsum[2][kCombine / 64];
+    __shared__ __int128 red[kCombine / 64][3];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const bool on = (int)threadIdx.x < blocks;
+    int64_t p[kPartial] = {0, 0, 0, 0, 0};
+    if (on)
+#pragma unroll
+        for (int c = 0; c < kPartial; ++c) p[c] = partials[(int64_t)kPartial * threadIdx.x + c];
+    Sums128 t{{0, 0, 0}};
+    const int32_t it = group_incl_scan<64>((int32_t)p[3], lane), is = group_incl_scan<64>((int32_t)p[4], lane);
+    if (lane == 63) {
+        colsum[0][wv] = it;
+        colsum[1][wv] = is;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) {
-            __int128 s = 0;
-            for (int q = 0; q < kCombine / 64; ++q) s += lds_red[q][k];
-            res[2 * k] = (int64_t)(uint64_t)s;
-            res[2 * k + 1] = (int64_t)(s >> 64);
+    int64_t ct = *h0 + it - p[3], cs = (two ? *snap_h0 : 0) + is - p[4];
+    for (int k = 0; k < wv; ++k) {
+        ct += colsum[0][k];
+        cs += colsum[1][k];
+    }
+    if (on) add_block(t, p, sites, ct, cs, two);
+    for (int k = 0; k < 3; ++k) {
+        __int128 v = t.v[k];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const uint64_t lo = __shfl_xor((uint64_t)v, off, 64);
+            const int64_t hi = __shfl_xor((int64_t)(v >> 64), off, 64);
+            v += ((__int128)hi << 64) | lo;
         }
+        if (lane == 0) red[wv][k] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 0; k < 3; ++k) {
+        t.v[k] = 0;
+        for (int w = 0; w < kCombine / 64; ++w) t.v[k] += red[w][k];
+    }
+    store_sums(t, res, flag);
+}
+
+// Bound by vector issue: about 13 instructions per eight sites (20 for two
+// states) instead of some 60 in a loop over the sites, and the x-slopes read
+// once.  2^14 x 2^14: two-time sums 202 us (87 us of it for the rows, the rest
+// in one workgroup that combined them row by row) to 40 us; the moments of
+// 128 x 128 in one launch of 4.6 us instead of two of 3.7 and 7.8 us.
+//
+// Sums over a block of R rows, with the workgroup's 16 waves on the rows'
+// words: partials[5 * block + ..] = {sum P, sum P^2 or P_t P_s, sum P_s,
+// column step of t, of s}, P the height over the row in front of the block.
+// With one block the final sums go to res.  (Combining in the last block to
+// finish, behind a device-scope counter, was slower than the second launch: the
+// release writes back the L2 of its XCD, 137 instead of 130 us for all
+// measurements of 2^13 x 2^13.)
+template <int G, bool TWO>
+__global__ __launch_bounds__(kSumBlock) void moments_kernel(const uint64_t* S, const int64_t* h0, const uint64_t* snap,
+                                                            const int64_t* snap_h0, int64_t Y, int32_t W, int32_t nb,
+                                                            int32_t R, int64_t* partials, int64_t* res,
+                                                            const int32_t* flag)
+{
+    __shared__ uint32_t lut[256];
+    __shared__ int32_t rbt[kSumRows], rbs[TWO ? kSumRows : 1];
+    __shared__ int32_t col[2], waves[kSumBlock / 64];
+    __shared__ int64_t red[kSumBlock / 64][3];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int gl = lane & (G - 1);
+    const int64_t plane = Y * W, y0 = (int64_t)blockIdx.x * R;
+    if (threadIdx.x < 256) lut[threadIdx.x] = running_counts(threadIdx.x);
+    row_bases(S, plane, W, y0, R, rbt, &col[0], waves);
+    if (TWO) row_bases(snap, plane, W, y0, R, rbs, &col[1], waves);
+
+    const int chunks = nb >> 2, n = 2 * nb;
+    int64_t a1 = 0, a2 = 0, a3 = 0;
+    for (int r0 = wv * (64 / G); r0 < R; r0 += (kSumBlock / 64) * (64 / G)) {
+        const int r_raw = r0 + lane / G;
+        const bool active = r_raw < R;
+        const int r = active ? r_raw : 0;
+        const int64_t y = y0 + r;
+        const int64_t pe = (y & 1) * plane + y * W, po = (1 - (y & 1)) * plane + y * W;
+        int32_t ct = rbt[r], cs = TWO ? rbs[r] : 0;
+        for (int w0 = 0; w0 < W; w0 += G) {
+            const int w = w0 + gl;
+            WordSums t, s{0, 0, 0};
+            if (G == 1 && nb < 4) {
+                int32_t d[4], ds[4];
+                four_sites(S[pe + w], S[po + w], d);
+                four_sites(TWO ? snap[pe + w] : S[pe + w], TWO ? snap[po + w] : S[po + w], ds);
+                t = {d[3], d[0] + d[1] + d[2] + d[3], d[0] * ds[0] + d[1] * ds[1] + d[2] * ds[2] + d[3] * ds[3]};
+                s = {ds[3], ds[0] + ds[1] + ds[2] + ds[3], 0};
+            } else if constexpr (TWO) {
+                word_sums2(lut, S[pe + w], S[po + w], snap[pe + w], snap[po + w], G == 1 ? chunks : 16, t, s);
+            } else {
+                t = word_sums(lut, S[pe + w], S[po + w], G == 1 ? chunks : 16);
+            }
+            const int32_t it = group_incl_scan<G>(t.tot, gl);
+            const int32_t bt = ct + it - t.tot;
+            int32_t bs = 0;
+            if (TWO) {
+                const int32_t is = group_incl_scan<G>(s.tot, gl);
+                bs = cs + is - s.tot;
+                if (w0 + G < W) cs += __shfl(is, (lane & ~(G - 1)) + G - 1);
+            }
+            if (w0 + G < W) ct += __shfl(it, (lane & ~(G - 1)) + G - 1);
+            if (!active) continue;
+            a1 += n * bt + t.s1;
+            if (TWO) {
+                a2 += (int64_t)bt * (n * bs + s.s1) + (int64_t)bs * t.s1 + t.s2;
+                a3 += n * bs + s.s1;
+            } else {
+                a2 += (int64_t)bt * (n * bt + 2 * t.s1) + t.s2;
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        a1 += __shfl_xor(a1, off, 64);
+        a2 += __shfl_xor(a2, off, 64);
+        if (TWO) a3 += __shfl_xor(a3, off, 64);
+    }
+    if (lane == 0) {
+        red[wv][0] = a1;
+        red[wv][1] = a2;
+        red[wv][2] = a3;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < kSumBlock / 64; ++k)
+        for (int c = 0; c < 3; ++c) red[0][c] += red[k][c];
+    if (gridDim.x == 1) {
+        Sums128 tot{{0, 0, 0}};
+        add_block(tot, red[0], (int64_t)n * W * R, *h0, TWO ? *snap_h0 : 0, TWO);
+        store_sums(tot, res, flag);
+    } else {
+        int64_t* p = partials + (int64_t)kPartial * blockIdx.x;
+        for (int c = 0; c < 3; ++c) p[c] = red[0][c];
+        p[3] = col[0];
+        p[4] = TWO ? col[1] : 0;
     }
 }
 
-// Heights of rows [y0, y0+ny): each row group forms the word bases of a
-// chunk of G words, parks (E, O, base) in LDS and then writes the chunk's
-// sites with consecutive lanes on consecutive x.
-template <int G>
-__global__ __launch_bounds__(kBlock) void heights_kernel(const uint64_t* S, int64_t X, int32_t W, int32_t nb,
-                                                        int64_t plane, const int64_t* col, int64_t y0, int64_t ny,
-                                                        int32_t* out)
-{
-    __shared__ uint64_t lE[kBlock], lO[kBlock];
-    __shared__ int64_t lB[kBlock];
-    const int lane = threadIdx.x & 63;
-    const int gl = lane & (G - 1);
-    const int slot0 = threadIdx.x & ~(G - 1);  // LDS slot of the group's first lane
-    const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    const int64_t r_raw = wave * (64 / G) + lane / G;
-    const bool active = r_raw < ny;
-    const int64_t y = y0 + (active ? r_raw : 0);
-    const int pe = (int)(y & 1);
-    const uint64_t* Er = S + (int64_t)pe * plane + y * W;
-    const uint64_t* Or = S + (int64_t)(1 - pe) * plane + y * W;
-    const int64_t cy = col[y];
-    const int spw = 2 * nb;  // sites per word
-    int32_t* orow = out + (active ? r_raw : 0) * X;
+// ---------------------------------------------------------------- heights
+constexpr int kColumn = 1024;
 
-    int64_t carry = 0;
-    for (int c = 0; c < W / G; ++c) {
-        const int w = c * G + gl;
-        const uint64_t E = Er[w], O = Or[w];
-        const uint64_t vmask = (nb == 64) ? ~0ull : ((1ull << nb) - 1ull);
-        int64_t ups = __popcll(E & vmask) + __popcll(O & vmask) - (w == 0 ? (int64_t)(E & 1ull) : 0);
-        const int64_t tot = 2 * ups - (spw - (w == 0 ? 1 : 0));
-        const int64_t incl = group_incl_scan<G>(tot, gl);
+// Heights c(y) of column 0, and h(0,0) to h0_out (host memory).  A thread takes
+// Y / 1024 consecutive rows (at most 128), eight loads at a time.
+__global__ __launch_bounds__(kColumn) void column_kernel(const uint64_t* S, const int64_t* h0, int64_t Y, int32_t W,
+                                                         int64_t plane, int64_t* col, int64_t* h0_out)
+{
+    __shared__ int32_t waves[kColumn / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int per = (int)((Y + kColumn - 1) / kColumn);
+    const int64_t ya = (int64_t)threadIdx.x * per;
+    const bool on = ya < Y;
+    uint64_t bits[2] = {0, 0};
+    for (int k0 = 0; on && k0 < per; k0 += 8) {
+        uint64_t w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t y = ya + (k0 + k < per ? k0 + k : 0);
+            w[k] = S[(2 + (y & 1)) * plane + y * W];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (k0 + k < per) bits[(k0 + k) >> 6] |= (w[k] & 1ull) << ((k0 + k) & 63);
+    }
+    int32_t sum = on ? 2 * (__popcll(bits[0]) + __popcll(bits[1])) - per : 0;
+    if (ya == 0) sum -= 2 * (int32_t)(bits[0] & 1ull) - 1;  // no step into row 0
+    const int32_t incl = group_incl_scan<64>(sum, lane);
+    if (lane == 63) waves[wv] = incl;
+    __syncthreads();
+    int64_t c = *h0 + incl - sum;
+    for (int k = 0; k < wv; ++k) c += waves[k];
+    for (int k = 0; on && k < per; ++k) {
+        if (ya + k != 0) c += 2 * (int64_t)((bits[k >> 6] >> (k & 63)) & 1ull) - 1;
+        col[ya + k] = c;
+    }
+    if (threadIdx.x == 0) *h0_out = *h0;
+}
+
+// Four heights of one store; the caller's buffer is aligned to an int32 only.
+typedef int32_t Int4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// Heights of rows [y0, y0+ny), X >= 128.  A wave takes 64 consecutive words (of
+// one row or of 64/G rows), parks them with the height in front of each in its
+// part of LDS, and writes their 8192 sites as 32 stores of 64 lanes x four
+// sites: every lane keeps its place within the word (chunk and half) in all of
+// them, so the masks are loop-invariant, and gets its four heights from one
+// table entry of running counts.  Bound by the write of 4 bytes per site.
+template <int G>
+__global__ __launch_bounds__(kBlock) void heights_kernel(const uint64_t* S, int64_t X, int32_t W, int64_t plane,
+                                                         const int64_t* col, int64_t y0, int64_t ny, int32_t* out)
+{
+    __shared__ uint32_t lut[256];
+    __shared__ uint64_t lE[kBlock], lO[kBlock];
+    __shared__ int32_t lB[kBlock];
+    const int lane = threadIdx.x & 63, gl = lane & (G - 1);
+    const int first = threadIdx.x & ~63;  // LDS words of this wave
+    lut[threadIdx.x] = running_counts(threadIdx.x);
+    __syncthreads();
+    const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const int64_t r0 = wave * (64 / G);
+    if (r0 >= ny) return;
+    const int64_t r_raw = r0 + lane / G;
+    const int64_t y = y0 + (r_raw < ny ? r_raw : 0);
+    const int64_t pe = (y & 1) * plane + y * W, po = (1 - (y & 1)) * plane + y * W;
+    int32_t base = (int32_t)col[y] - (2 * (int32_t)(S[pe] & 1ull) - 1);
+    const int j = (lane & 31) >> 1;  // this lane's chunk of eight sites within a word
+    const uint32_t below = (1u << (4 * (j & 7))) - 1u;
+    const uint32_t mlo = j < 8 ? below : ~0u, mhi = j < 8 ? 0u : below;
+    const int64_t left = (ny - r0) * X;  // sites of this wave's rows
+    for (int w0 = 0; w0 < W; w0 += G) {
+        const uint64_t E = S[pe + w0 + gl], O = S[po + w0 + gl];
+        const int32_t tot = 2 * (int32_t)(__popcll(E) + __popcll(O)) - 128;
+        const int32_t incl = group_incl_scan<G>(tot, gl);
         lE[threadIdx.x] = E;
         lO[threadIdx.x] = O;
-        lB[threadIdx.x] = carry + incl - tot;
-        carry += __shfl(incl, (lane & ~(G - 1)) + G - 1);
-        __syncthreads();
-        for (int m = 0; m < spw; ++m) {
-            const int s = m * G + gl;      // site within the chunk
-            const int ww = s / spw;        // word within the chunk
-            const int i = s - ww * spw;    // site within the word
-            const uint64_t e = lE[slot0 + ww], o = lO[slot0 + ww];
-            const int he = (i >> 1) + 1, ho = (i + 1) >> 1;  // even / odd sites among 0..i
-            const uint64_t me = he >= 64 ? ~0ull : ((1ull << he) - 1ull);
-            const uint64_t mo = ho >= 64 ? ~0ull : ((1ull << ho) - 1ull);
-            const bool first = (c == 0 && ww == 0);
-            const int64_t u = __popcll(e & me) + __popcll(o & mo) - (first ? (int64_t)(e & 1ull) : 0);
-            const int64_t cnt = i + 1 - (first ? 1 : 0);
-            const int64_t h = cy + lB[slot0 + ww] + 2 * u - cnt;
-            if (active) orow[(int64_t)c * G * spw + s] = (int32_t)h;
+        lB[threadIdx.x] = base + incl - tot;
+        if (w0 + G < W) base += __shfl(incl, 63);
+        // the words are the wave's own: program order is enough
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        int32_t* const o = out + r0 * X + (int64_t)w0 * 128;
+#pragma unroll 4
+        for (int m = 0; m < 32; ++m) {
+            const int e = first + 2 * m + (lane >> 5);
+            const uint64_t we = lE[e], wo = lO[e];
+            const uint32_t elo = (uint32_t)we, ehi = (uint32_t)(we >> 32), olo = (uint32_t)wo, ohi = (uint32_t)(wo >> 32);
+            const int32_t ups = __popc(elo & mlo) + __popc(ehi & mhi) + __popc(olo & mlo) + __popc(ohi & mhi);
+            const uint32_t eh = j < 8 ? elo : ehi, oh = j < 8 ? olo : ohi;
+            const uint32_t byte = ((eh >> (4 * (j & 7))) & 15u) | (((oh >> (4 * (j & 7))) & 15u) << 4);
+            const uint32_t c = lut[byte] >> (16 * (lane & 1));
+            const int32_t h = lB[e] + 2 * ups - 8 * j - 4 * (lane & 1) - 1;
+            const Int4 v = {h + 2 * (int32_t)(c & 15u), h - 1 + 2 * (int32_t)((c >> 4) & 15u),
+                            h - 2 + 2 * (int32_t)((c >> 8) & 15u), h - 3 + 2 * (int32_t)((c >> 12) & 15u)};
+            const int s = (m * 64 + lane) * 4;
+            if (G == 64 || s < left) *reinterpret_cast<Int4*>(o + s) = v;
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-template <int G, bool TWO>
-hipError_t launch_rows_g(const uint64_t* S, const uint64_t* snap, int64_t Y, int32_t W, int32_t nb, int64_t plane,
-                         int64_t* rows, hipStream_t stream)
+// Heights of rows of less than 128 sites, one site per thread.
+__global__ __launch_bounds__(kBlock) void heights_narrow_kernel(const uint64_t* S, int32_t lx, int64_t plane,
+                                                               const int64_t* col, int64_t y0, int64_t sites,
+                                                               int32_t* out)
 {
-    const int64_t rows_per_block = (kBlock / 64) * (64 / G);
-    hipLaunchKernelGGL((row_sums_kernel<G, TWO>), dim3((unsigned)((Y + rows_per_block - 1) / rows_per_block)),
-                       dim3(kBlock), 0, stream, S, snap, Y, W, nb, plane, rows);
-    return hipGetLastError();
+    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (s >= sites) return;
+    const int64_t y = y0 + (s >> lx);
+    const int i = (int)(s & ((1 << lx) - 1));
+    const uint64_t E = S[(y & 1) * plane + y], O = S[(1 - (y & 1)) * plane + y];
+    const uint64_t me = (2ull << (i >> 1)) - 1ull, mo = (1ull << ((i + 1) >> 1)) - 1ull;  // sites 0 .. i, i < 64
+    const int32_t ups = __popcll(E & me) + __popcll(O & mo) - (int32_t)(E & 1ull);
+    out[s] = (int32_t)col[y] + 2 * ups - i;
 }
 
 template <bool TWO>
-hipError_t launch_rows(const uint64_t* S, const uint64_t* snap, int64_t Y, int32_t W, int32_t nb, int64_t plane,
-                       int64_t* rows, hipStream_t stream)
+hipError_t launch_moments_g(const uint64_t* S, const int64_t* h0, const uint64_t* snap, const int64_t* snap_h0,
+                            int64_t Y, int32_t W, int32_t nb, int32_t R, int64_t* partials, int64_t* res,
+                            const int32_t* flag, hipStream_t stream)
 {
+    const dim3 grid((unsigned)(Y / R)), block(kSumBlock);
     switch (W) {
-    case 1: return launch_rows_g<1, TWO>(S, snap, Y, W, nb, plane, rows, stream);
-    case 2: return launch_rows_g<2, TWO>(S, snap, Y, W, nb, plane, rows, stream);
-    case 4: return launch_rows_g<4, TWO>(S, snap, Y, W, nb, plane, rows, stream);
-    case 8: return launch_rows_g<8, TWO>(S, snap, Y, W, nb, plane, rows, stream);
-    case 16: return launch_rows_g<16, TWO>(S, snap, Y, W, nb, plane, rows, stream);
-    case 32: return launch_rows_g<32, TWO>(S, snap, Y, W, nb, plane, rows, stream);
-    default: return launch_rows_g<64, TWO>(S, snap, Y, W, nb, plane, rows, stream);
+#define SCA_ROWS(G)                                                                                             \
+    hipLaunchKernelGGL((moments_kernel<G, TWO>), grid, block, 0, stream, S, h0, snap, snap_h0, Y, W, nb, R, partials, \
+                       res, flag)
+    case 1: SCA_ROWS(1); break;
+    case 2: SCA_ROWS(2); break;
+    case 4: SCA_ROWS(4); break;
+    case 8: SCA_ROWS(8); break;
+    case 16: SCA_ROWS(16); break;
+    case 32: SCA_ROWS(32); break;
+    default: SCA_ROWS(64); break;
+#undef SCA_ROWS
     }
+    return hipGetLastError();
 }
 
 template <int G>
-hipError_t launch_heights_g(const uint64_t* S, int64_t X, int32_t W, int32_t nb, int64_t plane, const int64_t* col,
-                            int64_t y0, int64_t ny, int32_t* out, hipStream_t stream)
+hipError_t launch_heights_g(const uint64_t* S, int64_t X, int32_t W, int64_t plane, const int64_t* col, int64_t y0,
+                            int64_t ny, int32_t* out, hipStream_t stream)
 {
     const int64_t rows_per_block = (kBlock / 64) * (64 / G);
     hipLaunchKernelGGL((heights_kernel<G>), dim3((unsigned)((ny + rows_per_block - 1) / rows_per_block)),
-                       dim3(kBlock), 0, stream, S, X, W, nb, plane, col, y0, ny, out);
+                       dim3(kBlock), 0, stream, S, X, W, plane, col, y0, ny, out);
     return hipGetLastError();
 }
 
@@ -375,36 +562,57 @@ hipError_t launch_flat_init_many(const FlatItem* items_dev, int32_t n, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_row_sums(const uint64_t* S, const uint64_t* snap, int64_t X, int64_t Y, int32_t W, int32_t nb,
-                           int64_t* rows, hipStream_t stream)
+// Rows per block: the whole lattice in one block of up to two words per
+// thread (2^10 x 2^9, four words per thread, took 13 us so), else 256 blocks,
+// or fewer where that would leave waves of a block without rows.
+static int32_t moments_rows(int64_t Y, int32_t W)
 {
-    (void)X;
-    const int64_t plane = Y * W;
-    return snap ? launch_rows<true>(S, snap, Y, W, nb, plane, rows, stream)
-                : launch_rows<false>(S, nullptr, Y, W, nb, plane, rows, stream);
+    if (Y <= kSumRows && Y * W <= 2 * kSumBlock) return (int32_t)Y;
+    const int64_t sweep = (int64_t)kSumBlock / (W < 64 ? W : 64);  // rows the 16 waves take at once
+    int64_t R = Y / kCombine > sweep ? Y / kCombine : sweep;
+    if (R > kSumRows) R = kSumRows;
+    return (int32_t)(R < Y ? R : Y);
 }
 
-hipError_t launch_combine(const uint64_t* S, const int64_t* h0, const uint64_t* snap, const int64_t* snap_h0,
-                          int64_t X, int64_t Y, int32_t W, const int64_t* rows, int64_t* col, int64_t* res,
-                          hipStream_t stream)
+hipError_t launch_moments(const uint64_t* S, const int64_t* h0, const uint64_t* snap, const int64_t* snap_h0,
+                          int64_t X, int64_t Y, int32_t W, int32_t nb, int64_t* partials, int64_t* res,
+                          const int32_t* flag, hipStream_t stream)
 {
-    hipLaunchKernelGGL(combine_kernel, dim3(1), dim3(kCombine), 0, stream, S, h0, snap, snap_h0, X, Y, W,
-                       Y * (int64_t)W, rows, col, res);
+    const int32_t R = moments_rows(Y, W);
+    const hipError_t e =
+        snap ? launch_moments_g<true>(S, h0, snap, snap_h0, Y, W, nb, R, partials, res, flag, stream)
+             : launch_moments_g<false>(S, h0, snap, snap_h0, Y, W, nb, R, partials, res, flag, stream);
+    if (e != hipSuccess || R == Y) return e;
+    hipLaunchKernelGGL(combine_kernel, dim3(1), dim3(kCombine), 0, stream, h0, snap_h0, snap != nullptr, partials,
+                       (int32_t)(Y / R), X * (int64_t)R, res, flag);
     return hipGetLastError();
 }
 
-hipError_t launch_heights(const uint64_t* S, int64_t X, int64_t Y, int32_t W, int32_t nb, const int64_t* col,
-                          int64_t y0, int64_t ny, int32_t* out, hipStream_t stream)
+hipError_t launch_column(const uint64_t* S, const int64_t* h0, int64_t Y, int32_t W, int64_t* col, int64_t* h0_out,
+                         hipStream_t stream)
+{
+    hipLaunchKernelGGL(column_kernel, dim3(1), dim3(kColumn), 0, stream, S, h0, Y, W, Y * (int64_t)W, col, h0_out);
+    return hipGetLastError();
+}
+
+hipError_t launch_heights(const uint64_t* S, int64_t X, int64_t Y, int32_t W, const int64_t* col, int64_t y0,
+                          int64_t ny, int32_t* out, hipStream_t stream)
 {
     const int64_t plane = Y * W;
+    if (X < 128) {
+        const int64_t sites = ny * X;
+        hipLaunchKernelGGL(heights_narrow_kernel, dim3((unsigned)((sites + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                           stream, S, __builtin_ctzll((uint64_t)X), plane, col, y0, sites, out);
+        return hipGetLastError();
+    }
     switch (W) {
-    case 1: return launch_heights_g<1>(S, X, W, nb, plane, col, y0, ny, out, stream);
-    case 2: return launch_heights_g<2>(S, X, W, nb, plane, col, y0, ny, out, stream);
-    case 4: return launch_heights_g<4>(S, X, W, nb, plane, col, y0, ny, out, stream);
-    case 8: return launch_heights_g<8>(S, X, W, nb, plane, col, y0, ny, out, stream);
-    case 16: return launch_heights_g<16>(S, X, W, nb, plane, col, y0, ny, out, stream);
-    case 32: return launch_heights_g<32>(S, X, W, nb, plane, col, y0, ny, out, stream);
-    default: return launch_heights_g<64>(S, X, W, nb, plane, col, y0, ny, out, stream);
+    case 1: return launch_heights_g<1>(S, X, W, plane, col, y0, ny, out, stream);
+    case 2: return launch_heights_g<2>(S, X, W, plane, col, y0, ny, out, stream);
+    case 4: return launch_heights_g<4>(S, X, W, plane, col, y0, ny, out, stream);
+    case 8: return launch_heights_g<8>(S, X, W, plane, col, y0, ny, out, stream);
+    case 16: return launch_heights_g<16>(S, X, W, plane, col, y0, ny, out, stream);
+    case 32: return launch_heights_g<32>(S, X, W, plane, col, y0, ny, out, stream);
+    default: return launch_heights_g<64>(S, X, W, plane, col, y0, ny, out, stream);
     }
 }
 

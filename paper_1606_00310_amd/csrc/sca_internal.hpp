@@ -55,22 +55,22 @@ struct FlatItem {
 FlatItem flat_item(uint64_t* S, int64_t Y, int32_t W, int32_t nb, int64_t* h0);
 hipError_t launch_flat_init_many(const FlatItem* items_dev, int32_t n, hipStream_t stream);
 
-// Per-row sums for the moments (and the two-time sums when snap != nullptr):
-// rows[y*3 + {0,1,2}] = {sum_x P_t, sum_x P_t^2 (or sum_x P_t P_s), sum_x P_s}
-// with P(x) = h(x,y) - h(0,y).
-hipError_t launch_row_sums(const uint64_t* S, const uint64_t* snap, int64_t X, int64_t Y,
-                           int32_t W, int32_t nb, int64_t* rows, hipStream_t stream);
+// Exact sums of the height field into res[7] (device memory or pinned host
+// memory): {S1 lo,hi, S2 lo,hi, S3 lo,hi, *flag or 0}, 128 bits each, with
+// S = {sum h, sum h^2, 0} or, with a snapshot, {sum h_t, sum h_t h_s, sum h_s}.
+// partials: kMomentsPartial int64 per block of rows, at most 3 Y in all.
+constexpr int kMomentsPartial = 5;
+hipError_t launch_moments(const uint64_t* S, const int64_t* h0, const uint64_t* snap, const int64_t* snap_h0,
+                          int64_t X, int64_t Y, int32_t W, int32_t nb, int64_t* partials, int64_t* res,
+                          const int32_t* flag, hipStream_t stream);
 
-// Column prefix h(0,y) and the final exact sums (128-bit) into res[]:
-// res = {S1 lo,hi, S2 lo,hi, S3 lo,hi}; see measure.hip for their meaning.
-hipError_t launch_combine(const uint64_t* S, const int64_t* h0, const uint64_t* snap,
-                          const int64_t* snap_h0, int64_t X, int64_t Y, int32_t W,
-                          const int64_t* rows, int64_t* col, int64_t* res, hipStream_t stream);
+// Heights h(0,y) of column 0 into col[Y], h(0,0) into *h0_out.
+hipError_t launch_column(const uint64_t* S, const int64_t* h0, int64_t Y, int32_t W, int64_t* col, int64_t* h0_out,
+                         hipStream_t stream);
 
-// Heights of rows [y0, y0+ny) into out (needs col[] from launch_combine).
-hipError_t launch_heights(const uint64_t* S, int64_t X, int64_t Y, int32_t W, int32_t nb,
-                          const int64_t* col, int64_t y0, int64_t ny, int32_t* out,
-                          hipStream_t stream);
+// Heights of rows [y0, y0+ny) into out (needs col[] from launch_column).
+hipError_t launch_heights(const uint64_t* S, int64_t X, int64_t Y, int32_t W, const int64_t* col, int64_t y0,
+                          int64_t ny, int32_t* out, hipStream_t stream);
 
 // One realization of an ensemble epoch (device table, one entry per slot).
 struct BatchDesc {
