@@ -39,7 +39,7 @@ struct ProbCode {
 // number of `depth`-MCS passes, then the remainder r < 2*depth as two passes
 // of ceil(r/2) and floor(r/2) MCS, or, for r = 1, two half-step launches.
 // Lattices that one workgroup holds may run in place in one launch instead.
-// The per-site path is ALU-bound and runs unfused.
+// The per-site path runs unfused from X = 8192 on, where it is ALU-bound.
 struct StepPlan {
     ProbCode P, Q;
     bool persite = false, has_q = false, draw_free = false;
@@ -257,6 +257,9 @@ constexpr int64_t kWholeMcs = 1 << 14;
 //    takes V N/2 (4.7 + 0.44 w) ns, from one wave (p = 1: 0.13 us, p = 1/2:
 //    0.24 us, p = 3/4, q = 1/4: 0.40 us, all latency) to sixteen (0.28, 0.58 and
 //    1.0 us, all vector issue); a launch adds 2.6 us and 0.2 us per MB moved;
+//  - a half-step of a per-site tile takes 0.5 us and 5.8 ns (6.6 ns with
+//    removals) for every word a CU draws for; unfused it takes 3.7 us, or the
+//    vector issue of the chip, 24 us per 2^20 words;
 //  - a row sweep (fused.hpp) of b rows and d MCS walks b + 4d - 1 steps of
 //    0.6 us (0.35 us at d = 1) for the row to arrive and 2d half-steps, each the longer of its
 //    latency (p = 1/2 on rows of 2^16 sites: 0.21 us) and the share of the k
@@ -272,21 +275,34 @@ struct CostModel {
     double V, draws, mb;  // mb: the state in MB
     int64_t Y;
     int32_t W;
-    bool has_q, draw_free;
+    bool has_q, draw_free, persite;
 
     CostModel(const sca_ctx* c, const StepPlan& pl)
         : V(30 + (pl.has_q ? 10 : 0) + 18 * pl.ndraw + 2 * pl.ndraw * (pl.has_q ? 2 : 1)), draws(pl.ndraw),
-          mb(32e-6 * (double)c->Y * c->W), Y(c->Y), W(c->W), has_q(pl.has_q), draw_free(pl.draw_free)
+          mb(32e-6 * (double)c->Y * c->W), Y(c->Y), W(c->W), has_q(pl.has_q), draw_free(pl.draw_free), persite(pl.persite)
     {
     }
     double half(double waves, int32_t words) const { return V * words / 2 * (0.0047 + 0.00044 * waves); }
-    double unfused() const { return 2 * std::max(2.95, 0.37 * (1 + 0.03 * std::max(1, W / 64) + 0.025 * draws) * mb); }
-    double whole(int64_t n) const { return 2.6 + 10 * mb + 2.0 * (double)n * half((double)((Y / 2 * W + 63) / 64), 2); }
+    // a half-step of a per-site tile with `words` words per CU to draw for
+    double draw(double words) const { return words * (has_q ? 0.0066 : 0.0058); }
+    double unfused() const
+    {
+        if (persite) return 2 * std::max(3.7, 2.2 + (double)Y * W * (has_q ? 3.0e-5 : 2.4e-5));
+        return 2 * std::max(2.95, 0.37 * (1 + 0.03 * std::max(1, W / 64) + 0.025 * draws) * mb);
+    }
+    double whole(int64_t n) const
+    {
+        if (persite) return 2.6 + 2.0 * (double)n * (0.5 + draw((double)Y * W));
+        return 2.6 + 10 * mb + 2.0 * (double)n * half((double)((Y / 2 * W + 63) / 64), 2);
+    }
     double tile(int32_t N, int32_t b, int32_t d) const
     {
         const int I = W > 64 ? W / 64 : 1;
         const int threads = ((b + 4 * d) / N * (W / I) + 63) / 64 * 64;
         const int64_t per_cu = (Y / b + 255) / 256;  // workgroups on the busiest CU
+        if (persite)
+            return 2.6 + 2 * d * (0.5 * (double)((per_cu + 1) / 2) + draw((double)per_cu * (b + 2 * d) * W)) +
+                   0.2 * mb * (2 + 4.0 * d / b);
         // workgroups a CU holds: of the two-row kernels by threads, of the others by registers
         const int64_t fit = std::max<int64_t>(1, (N == 2 ? 2048 : 1024) / threads);
         const int64_t rounds = (per_cu + fit - 1) / fit;
@@ -316,13 +332,18 @@ double split_cost(int64_t n, int32_t d, F pass, double one)
     return t;
 }
 
+// Words of a per-site tile at most: 32 KiB of acceptance words with removals.
+constexpr int32_t kPersiteWords = 1024;
+
 // Halo rows on either side of a tile's band: the 2 d that d MCS need, whole
 // threads' worth.
 int32_t tile_halo(int32_t N, int32_t d) { return (2 * d + N - 1) / N * N; }
 
-bool tile_fits(int32_t W, int64_t Y, int32_t N, int32_t b, int32_t d)
+bool tile_fits(int32_t W, int64_t Y, int32_t N, int32_t b, int32_t d, bool persite)
 {
     const int I = W > 64 ? 2 : 1;
+    // per site, the acceptance words of the whole tile lie in LDS twice
+    if (persite && (N != 2 || W > 32 || (b + 4 * d) * W > kPersiteWords)) return false;
     return W <= 128 && (W <= 64 || N == 4) && Y >= b && b % N == 0 &&
            (b + 2 * tile_halo(N, d)) / N * (W / I) <= (I == 1 ? 1024 : 768);
 }
@@ -355,7 +376,7 @@ bool plan_by_cost(const sca_ctx* c, int64_t n_mcs, StepPlan& pl)
     const CostModel m(c, pl);
     double best = (double)n_mcs * m.unfused();
     bool fuse = false;
-    if (W < 64 && Y / 2 * W <= 1024 && m.whole(n_mcs) < best) {
+    if (W < 64 && Y / 2 * W <= 1024 && (!pl.persite || Y * W <= kPersiteWords) && m.whole(n_mcs) < best) {
         best = m.whole(n_mcs);
         pl.whole = true;
         pl.tile_rows = 2;
@@ -379,11 +400,11 @@ bool plan_by_cost(const sca_ctx* c, int64_t n_mcs, StepPlan& pl)
         consider(0.85 * split_cost(n_mcs, d0, [&](int32_t e) { return m.sweep(b0, e); }, m.unfused()), 0, b0, d0);
     // with 2 d >= n all of it is one pair of passes
     const int32_t half = (int32_t)std::min<int64_t>((n_mcs + 1) / 2, 64);
-    for (int32_t b : {8, 16, 32, 64, 128})
+    for (int32_t b : {4, 8, 16, 32, 64, 128})
         for (int32_t dd : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
             const int32_t d = std::min(dd, half);
             for (int32_t N : {2, 4})
-                if (tile_fits(W, Y, N, b, d))
+                if (tile_fits(W, Y, N, b, d, pl.persite))
                     consider(split_cost(n_mcs, d, [&](int32_t e) { return m.tile(N, b, e); }, m.unfused()), N, b, d);
             if (d == half) break;
         }
@@ -435,10 +456,10 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
                            : band >= 16 ? 2
                                         : 1;
     }
-    const bool may_fuse = !(flags & SCA_NO_FUSE) && depth > 0 && n_mcs >= 1;
-    // Lattices too small for full-height bands (and, from X = 8192 on, with
-    // the pass buffer that all their passes need) go by cost.
-    if (automatic && may_fuse && !pl.persite && c->W <= 512 && band < tall && (c->W < 64 || c->alt)) {
+    const bool may_fuse = !(flags & SCA_NO_FUSE) && (c->W < 64 ? c->depth != 0 : depth > 0) && n_mcs >= 1;
+    // Lattices too small for full-height bands (and, from X = 8192 on, with the
+    // pass buffer that all their passes need) go by cost.
+    if (automatic && may_fuse && c->W <= 512 && band < tall && (c->W < 64 || (c->alt && !pl.persite))) {
         pl.depth = depth;
         const bool fuse = plan_by_cost(c, n_mcs, pl);
         set_passes(pl, n_mcs, fuse);
@@ -447,9 +468,11 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
     if (c->W < 64) {
         // explicit depth and band, where they make a tile
         pl.depth = depth;
-        bool fuse = may_fuse && !pl.persite && n_mcs >= 2 && c->alt != nullptr;
+        bool fuse = may_fuse && depth > 0 && n_mcs >= 2 && c->alt != nullptr;
         if (fuse) {
-            pl.tile_rows = tile_fits(c->W, c->Y, 2, band, depth) ? 2 : tile_fits(c->W, c->Y, 4, band, depth) ? 4 : 0;
+            pl.tile_rows = tile_fits(c->W, c->Y, 2, band, depth, pl.persite)   ? 2
+                           : tile_fits(c->W, c->Y, 4, band, depth, pl.persite) ? 4
+                                                                               : 0;
             fuse = pl.tile_rows != 0;
         }
         set_passes(pl, n_mcs, fuse);
@@ -621,11 +644,11 @@ int sca_plan_step(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned 
     out->n_unfused = pl.whole ? 0 : n_mcs - (pl.n_pass * pl.depth + pl.tail1 + pl.tail2);
     const sca::SweepArgs a = sweep_args(c, pl);
     if (pl.whole || (pl.n_pass > 0 && pl.tile_rows > 0))
-        sca::tile_kernel_name(a, pl.has_q, pl.tile_rows, out->kernel, sizeof out->kernel);
+        sca::tile_kernel_name(a, pl.mode, pl.has_q, pl.tile_rows, out->kernel, sizeof out->kernel);
     else if (pl.n_pass > 0) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.depth, out->kernel, sizeof out->kernel);
     else std::snprintf(out->kernel, sizeof out->kernel, "none");
     if (pl.tail1 && pl.tile_rows > 0)
-        sca::tile_kernel_name(a, pl.has_q, pl.tile_rows, out->tail_kernel, sizeof out->tail_kernel);
+        sca::tile_kernel_name(a, pl.mode, pl.has_q, pl.tile_rows, out->tail_kernel, sizeof out->tail_kernel);
     else if (pl.tail1) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.tail1, out->tail_kernel, sizeof out->tail_kernel);
     else std::snprintf(out->tail_kernel, sizeof out->tail_kernel, "none");
     sca::halfstep_kernel_name(c->W, pl.mode, pl.has_q, out->halfstep_kernel, sizeof out->halfstep_kernel);

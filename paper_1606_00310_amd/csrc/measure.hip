@@ -391,40 +391,49 @@ __global__ __launch_bounds__(kSumBlock) void moments_kernel(const uint64_t* S, c
 // ---------------------------------------------------------------- heights
 constexpr int kColumn = 1024;
 
-// Heights c(y) of column 0, and h(0,0) to h0_out (host memory).  A thread takes
-// Y / 1024 consecutive rows (at most 128), eight loads at a time.
+// Heights c(y) of column 0, and h(0,0) to h0_out (host memory).  Eight times
+// 1024 rows at a time, row 1024 k + thread, so that the stores lie side by side
+// and all loads of a round are in flight at once; the 128 wave sums are scanned
+// by every wave for itself.  Bound by the lines one CU takes in, one per row of
+// eight words or more: 8192 rows in 11.4 us (14.1 us with consecutive rows per
+// thread).
 __global__ __launch_bounds__(kColumn) void column_kernel(const uint64_t* S, const int64_t* h0, int64_t Y, int32_t W,
                                                          int64_t plane, int64_t* col, int64_t* h0_out)
 {
-    __shared__ int32_t waves[kColumn / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int per = (int)((Y + kColumn - 1) / kColumn);
-    const int64_t ya = (int64_t)threadIdx.x * per;
-    const bool on = ya < Y;
-    uint64_t bits[2] = {0, 0};
-    for (int k0 = 0; on && k0 < per; k0 += 8) {
-        uint64_t w[8];
+    constexpr int K = 8, WAVES = kColumn / 64;
+    static_assert(K * WAVES == 128, "two sums per lane");
+    __shared__ int32_t sums[2][K * WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const uint64_t upto = (2ull << lane) - 1ull;  // this lane and those below
+    int64_t c0 = *h0;
+    int buf = 0;
+    for (int64_t y0 = 0; y0 < Y; y0 += (int64_t)K * kColumn, buf ^= 1) {
+        uint64_t w[K], ups[K], on[K];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int64_t y = ya + (k0 + k < per ? k0 + k : 0);
-            w[k] = S[(2 + (y & 1)) * plane + y * W];
+        for (int k = 0; k < K; ++k) {
+            const int64_t y = y0 + k * kColumn + tid;
+            w[k] = S[(2 + (tid & 1)) * plane + (y < Y ? y : (int64_t)(tid & 1)) * W];
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (k0 + k < per) bits[(k0 + k) >> 6] |= (w[k] & 1ull) << ((k0 + k) & 63);
+        for (int k = 0; k < K; ++k) {
+            const int64_t y = y0 + k * kColumn + tid;
+            on[k] = __ballot(y < Y && y != 0);  // no step into row 0
+            ups[k] = __ballot((w[k] & 1ull) != 0) & on[k];
+            if (lane == 0) sums[buf][k * WAVES + wv] = 2 * __popcll(ups[k]) - __popcll(on[k]);
+        }
+        __syncthreads();
+        const int32_t a = sums[buf][2 * lane], b = sums[buf][2 * lane + 1];
+        const int32_t incl = group_incl_scan<64>(a + b, lane);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int i = k * WAVES + wv;  // sum i: the first or second of lane i / 2
+            const int32_t before = __shfl((i & 1) ? incl - b : incl - a - b, i >> 1);
+            const int64_t y = y0 + k * kColumn + tid;
+            if (y < Y) col[y] = c0 + before + 2 * __popcll(ups[k] & upto) - __popcll(on[k] & upto);
+        }
+        c0 += __shfl(incl, 63);
     }
-    int32_t sum = on ? 2 * (__popcll(bits[0]) + __popcll(bits[1])) - per : 0;
-    if (ya == 0) sum -= 2 * (int32_t)(bits[0] & 1ull) - 1;  // no step into row 0
-    const int32_t incl = group_incl_scan<64>(sum, lane);
-    if (lane == 63) waves[wv] = incl;
-    __syncthreads();
-    int64_t c = *h0 + incl - sum;
-    for (int k = 0; k < wv; ++k) c += waves[k];
-    for (int k = 0; on && k < per; ++k) {
-        if (ya + k != 0) c += 2 * (int64_t)((bits[k >> 6] >> (k & 63)) & 1ull) - 1;
-        col[ya + k] = c;
-    }
-    if (threadIdx.x == 0) *h0_out = *h0;
+    if (tid == 0) *h0_out = *h0;
 }
 
 // Four heights of one store; the caller's buffer is aligned to an int32 only.

@@ -38,7 +38,7 @@ struct TileShape {
 hipError_t launch_tile(const SweepArgs& a, XiMode mode, bool has_q, const uint64_t* src, uint64_t* dst,
                        const TileShape& s, int32_t n_mcs, hipStream_t stream);
 
-void tile_kernel_name(const SweepArgs& a, bool has_q, int32_t rows_per_thread, char* out, size_t n);
+void tile_kernel_name(const SweepArgs& a, XiMode mode, bool has_q, int32_t rows_per_thread, char* out, size_t n);
 
 // Flat initial surface into S and h0 = 0.
 hipError_t launch_flat_init(uint64_t* S, int64_t Y, int32_t W, int32_t nb, int64_t* h0,

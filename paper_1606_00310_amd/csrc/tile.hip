@@ -1,5 +1,6 @@
 // tile.hip -- launches of the on-chip tiles (tile.hpp) for one lattice: the
 // whole lattice in one workgroup, or one band per workgroup with its halo.
+#include <algorithm>
 #include <cstdio>
 
 #include "sca_internal.hpp"
@@ -57,9 +58,14 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
 #pragma unroll
             for (int k = 0; k < I; ++k) {
                 const int64_t w = (int64_t)th.g[i] + 64 * k;
-                th.x[i][p][k] = L.src[(int64_t)p * a.plane + w];
-                th.y[i][p][k] = L.src[(int64_t)(2 + p) * a.plane + w];
+                th.x[i][p][k] = active ? L.src[(int64_t)p * a.plane + w] : 0ull;
+                th.y[i][p][k] = active ? L.src[(int64_t)(2 + p) * a.plane + w] : 0ull;
             }
+    }
+    if constexpr (MODE == XiMode::PerSite) {
+        const int used = a.nb > 8 ? 31 - __builtin_clz((unsigned)a.nb) - 3 : 0;
+        th.ps = PerSiteTile{ly + 2 * T, L.rows << L2G, L2G, used, (int)blockIdx.x * L.band - L.halo, ymask, HASQ};
+        th.xrow = active ? (r0 << L2G) + gl : 0;
     }
 #pragma unroll
     for (int p = 0; p < 2; ++p)
@@ -70,14 +76,14 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
     const int w0 = __builtin_amdgcn_readfirstlane(tid);
     const int wlo = (w0 >> L2G) * N, whi = ((w0 + 63) >> L2G) * N + N - 1;
     int lo = L.halo > 0 ? L.halo - 2 * L.n : 0;
-    int hi = L.halo > 0 ? L.halo + L.band + 2 * L.n - 2 : L.rows;
+    int hi = L.halo > 0 ? L.halo + L.band + 2 * L.n - 2 : L.rows - 1;
     const int shrink = L.halo > 0 ? 1 : 0;
     SweepArgs ah = a;
     for (int m = 0; m < L.n; ++m) {
-        th.template halfstep<0>(ah, ly, whi < lo || wlo > hi);
+        th.template halfstep<0>(ah, ly, lo, hi, whi < lo || wlo > hi);
         lo += shrink;
         hi -= shrink;
-        th.template halfstep<1>(ah, ly, whi < lo || wlo > hi);
+        th.template halfstep<1>(ah, ly, lo, hi, whi < lo || wlo > hi);
         lo += shrink;
         hi -= shrink;
         ++ah.t;
@@ -106,12 +112,22 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
 template <int G, int N, int I, XiMode MODE, bool HASQ, Draws DR>
 hipError_t launch(const TileLaunch& L, hipStream_t stream)
 {
-    const int threads = (L.rows / N * (G == 0 ? 1 : G) + 63) / 64 * 64;
+    int threads = (L.rows / N * (G == 0 ? 1 : G) + 63) / 64 * 64;
+    size_t lds = 0;
+    if (MODE == XiMode::PerSite) {
+        // helpers for the acceptance words: a thread for each byte of the rows a
+        // half-step needs on average
+        const int words = L.rows * (G == 0 ? 1 : G);
+        const int bytes = (L.rows - L.halo) * (G == 0 ? 1 : G) * 8;
+        threads = std::max(threads, std::min(1024, (bytes + 63) / 64 * 64));
+        lds = (size_t)(HASQ ? 4 : 2) * words * sizeof(uint64_t);
+    }
     const int grid = L.a.Y / L.band;
     if (threads > kTileThreads<I> || L.rows % N != 0 || L.a.Y % L.band != 0 || L.rows < L.band + 2 * L.halo ||
         (L.halo == 0 ? (grid != 1 || L.rows != L.a.Y) : (L.halo % 2 != 0 || L.halo < 2 * L.n)))
         return hipErrorInvalidValue;
-    const size_t lds = (size_t)2 * I * threads * sizeof(uint64_t);
+    lds += (size_t)2 * I * threads * sizeof(uint64_t);
+    if (lds > 65536) return hipErrorInvalidValue;
     hipLaunchKernelGGL((tile_kernel<G, N, I, MODE, HASQ, DR>), dim3((unsigned)grid), dim3((unsigned)threads), lds,
                        stream, L);
     return hipGetLastError();
@@ -120,6 +136,11 @@ hipError_t launch(const TileLaunch& L, hipStream_t stream)
 template <int G, int N, int I>
 hipError_t launch_mode(const TileLaunch& L, XiMode mode, bool has_q, hipStream_t stream)
 {
+    if (mode == XiMode::PerSite) {
+        if constexpr (N == 2 && G < 64)
+            return has_q ? launch<G, N, I, XiMode::PerSite, true, Draws::Any>(L, stream)
+                         : launch<G, N, I, XiMode::PerSite, false, Draws::Any>(L, stream);
+    }
     if (mode != XiMode::Mask) return hipErrorInvalidValue;
     if (L.a.ndraw == 0)
         return has_q ? launch<G, N, I, XiMode::Fixed, true, Draws::Any>(L, stream)
@@ -162,11 +183,11 @@ hipError_t launch_tile(const SweepArgs& a, XiMode mode, bool has_q, const uint64
 }
 
 // The kernel launch_tile runs (see launch_width and launch_mode).
-void tile_kernel_name(const SweepArgs& a, bool has_q, int32_t rows_per_thread, char* out, size_t n)
+void tile_kernel_name(const SweepArgs& a, XiMode mode, bool has_q, int32_t rows_per_thread, char* out, size_t n)
 {
     const int G = a.W == 1 && a.nb < 64 ? 0 : (a.W < 64 ? a.W : 64);
     std::snprintf(out, n, "tile_kernel<%d,%d,%d,%s,%s>", G, rows_per_thread, a.W > 64 ? a.W / 64 : 1,
-                  a.ndraw == 0 ? "Fixed" : ((a.ndraw & 1) ? "Mask,OddTail" : "Mask,Even"), has_q ? "true" : "false");
+                  mode == XiMode::PerSite ? "PerSite" : a.ndraw == 0 ? "Fixed" : ((a.ndraw & 1) ? "Mask,OddTail" : "Mask,Even"), has_q ? "true" : "false");
 }
 
 }  // namespace sca

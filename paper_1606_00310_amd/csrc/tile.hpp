@@ -213,6 +213,45 @@ __device__ __forceinline__ void tile_row(const RowLanes& rl, uint64_t (&A)[I], u
     }
 }
 
+// Per-site acceptance words of a tile (one word per lane).  A word takes 16
+// Philox calls, too many for the few waves that hold a small tile's rows, so
+// the whole workgroup forms them, eight sites (two calls) of a word per thread
+// and byte, into one of two buffers in LDS; the barrier that starts the
+// half-step orders them like the slopes, and the buffer of the half-step before
+// is free again behind it.  Bound by vector issue beyond a few hundred words per
+// CU: 1024 x 1024 at p = 0.95, 20 MCS and moments, took 255 us in half-step
+// launches of 4.3 us (one lane per word, two waves on half of the CUs) and takes
+// 69 us.
+struct PerSiteTile {
+    uint64_t* xi;   // [sublattice][p, q][tile row][word]
+    int words;      // words of the tile
+    int lw;         // log2 of the words per row
+    int lk;         // log2 of the bytes in use per word
+    int y0, ymask;  // lattice row of tile row 0
+    bool has_q;
+
+    __device__ __forceinline__ uint64_t* buffer(int parity) const { return xi + (parity ? (has_q ? 2 : 1) * words : 0); }
+
+    // The words of tile rows lo .. hi for sublattice a.parity at MCS a.t.
+    template <bool HASQ>
+    __device__ __forceinline__ void generate(const SweepArgs& a, int lo, int hi) const
+    {
+        uint8_t* const out = reinterpret_cast<uint8_t*>(buffer(a.parity));
+        const int end = (hi + 1) << (lw + lk);
+        for (int i = (lo << (lw + lk)) + (int)threadIdx.x; i < end; i += (int)blockDim.x) {
+            const int w = i >> lk, k = i & ((1 << lk) - 1);
+            const int row = (y0 + (w >> lw)) & ymask;
+            const uint32_t g = ((uint32_t)row << lw) + (uint32_t)(w & ((1 << lw) - 1));
+            const uint32_t c2 = 4u * (uint32_t)k + (uint32_t)a.parity;  // calls 2k and 2k+1
+            const u32x4 o1 = philox4x32_10(g, a.t, c2 + 2u, 0u, a.k0, a.k1);
+            const u32x4 o0 = philox4x32_10(g, a.t, c2, 0u, a.k0, a.k1);
+            out[8 * w + k] = (uint8_t)shift_in_compares(shift_in_compares(0u, o1, a.thr_p), o0, a.thr_p);
+            if (HASQ)
+                out[8 * (words + w) + k] = (uint8_t)shift_in_compares(shift_in_compares(0u, o1, a.thr_q), o0, a.thr_q);
+        }
+    }
+};
+
 // The rows of one thread and the half-step over them.
 template <int G, int N, int I, XiMode MODE, bool HASQ, Draws DR>
 struct TileThread {
@@ -220,8 +259,9 @@ struct TileThread {
     static_assert(I == 1 || G == 64, "a row of several words per lane fills a wave");
     // Rows whose random words are formed together: two words' worth.  With two
     // words per thread those are all of a half-step, formed before the barrier
-    // it starts with and so off the path from write to read.
-    static constexpr bool PRE = N * I <= 2;
+    // it starts with and so off the path from write to read.  Per-site words
+    // come from LDS behind the barrier.
+    static constexpr bool PRE = N * I <= 2 && MODE != XiMode::PerSite;
     static constexpr int NX = 2 / I;
     static constexpr bool TAIL = DR == Draws::OddTail && MODE == XiMode::Mask;
 
@@ -234,6 +274,8 @@ struct TileThread {
     int stride;           // LDS words per (sublattice, i)
     uint32_t org[N / 2];  // 1 in the lane and even row that hold site (0,0) (never in a halo row)
     int32_t lifts;        // (lifts - drops) of site (0,0)
+    PerSiteTile ps;       // per-site mode
+    int xrow;             // index of the first row's word in a buffer of acceptance words
 
     // Acceptance words of rows i0 .. i0+NX-1.
     __device__ __forceinline__ void words(const SweepArgs& a, int i0, uint64_t (&xp)[NX][I], uint64_t (&xq)[NX][I])
@@ -253,21 +295,25 @@ struct TileThread {
         } else {
 #pragma unroll
             for (int m = 0; m < NX * I; ++m) {
-                uint64_t p = a.all_p, q = a.all_q;
-                if constexpr (MODE == XiMode::PerSite) persite_words(a, g[i0 + m / I] + 64u * (m % I), HASQ, p, q);
-                xp[m / I][m % I] = p;
-                xq[m / I][m % I] = q;
+                xp[m / I][m % I] = a.all_p;
+                xq[m / I][m % I] = a.all_q;
+                if constexpr (MODE == XiMode::PerSite) {
+                    const uint64_t* x = ps.buffer(a.parity) + xrow + ((i0 + m) << ps.lw);
+                    xp[m][0] |= x[0];
+                    if (HASQ) xq[m][0] |= x[ps.words];
+                }
             }
         }
     }
 
-    // Half-step of sublattice PI at MCS a.t; `skip` (scalar): none of the
-    // wave's rows has to be right any more.
+    // Half-step of sublattice PI at MCS a.t; tile rows lo .. hi have to be
+    // right, and `skip` (scalar): none of the wave's rows are among them.
     template <int PI>
-    __device__ __forceinline__ void halfstep(SweepArgs a, uint64_t* ly, bool skip)
+    __device__ __forceinline__ void halfstep(SweepArgs a, uint64_t* ly, int lo, int hi, bool skip)
     {
         a.parity = PI;
         uint64_t xp[NX][I], xq[NX][I];
+        if constexpr (MODE == XiMode::PerSite) ps.generate<HASQ>(a, lo, hi);
         if constexpr (PRE) {
             if (!skip) words(a, 0, xp, xq);
         }

@@ -96,7 +96,7 @@ def test_bands(orc, sca, X, Y, depth, band, p, q):
 
 @pytest.mark.parametrize("X,Y", [(512, 4096), (1024, 16384), (4096, 4096), (8192, 64), (8192, 2048), (16384, 128),
                                  (16384, 4096), (32768, 1024), (65536, 512), (65536, 4096)])
-@pytest.mark.parametrize("p,q", [(0.5, 0.0), (0.75, 0.25), (1.0, 0.0)])
+@pytest.mark.parametrize("p,q", [(0.5, 0.0), (0.75, 0.25), (1.0, 0.0), (0.93, 0.07)])
 def test_automatic_shapes(sca, X, Y, p, q):
     """Whatever shape the cost estimates choose: the two-launch form's bits,
     for numbers of MCS with and without remainders, from a rough state."""
@@ -108,6 +108,31 @@ def test_automatic_shapes(sca, X, Y, p, q):
         a.step(n, p, q)
         b.step(n, p, q, fuse=False)
         assert torch.equal(a.slopes, b.slopes) and a.meta() == b.meta()
+
+
+# per-site words through LDS: words of one, two, four and eight bytes in use,
+# whole lattices and bands up to the most words a tile holds, p below and at the
+# ends of the threshold's range, dyadic values forced onto the path
+PERSITE = [(4, 4, 0, 0), (16, 32, 0, 0), (32, 8, 0, 0), (64, 64, 0, 0), (128, 128, 0, 0), (512, 128, 0, 0),
+           (2048, 64, 0, 0), (4096, 32, 0, 0), (32, 64, 3, 8), (128, 512, 5, 16), (256, 64, 4, 4), (1024, 256, 4, 4),
+           (1024, 128, 8, 32), (2048, 64, 2, 8), (4096, 64, 4, 16), (4096, 128, 1, 4)]
+
+
+@pytest.mark.parametrize("X,Y,depth,band", PERSITE)
+@pytest.mark.parametrize("p,q", [(0.95, 0.0), (0.93, 0.07), (1.0 - 2.0**-33, 2.0**-40), (0.5, 0.25), (1.0, 0.3)])
+def test_persite_tiles(orc, sca, X, Y, depth, band, p, q):
+    _say(f"[per-site] {X}x{Y} depth={depth} band={band} p={p} q={q}")
+    n = 2 * depth + 3
+    st, lat = rough_pair(orc, sca, X, Y, seed=21 + X + depth)
+    if depth:
+        lat.set_blocking(depth, band)
+    else:
+        detach_pass_buffer(lat)
+    plan = lat.plan(n, p, q, force_persite=True)
+    assert "PerSite" in plan["kernel"] or Y * max(1, X // 128) > 256  # a large one may still go by half-steps
+    lat.step(n, p, q, force_persite=True)
+    orc.run(st, n, p, q, seed=21 + X + depth, force_persite=True)
+    assert_same(orc, lat, st)
 
 
 def test_without_pass_buffer(sca):
