@@ -269,12 +269,16 @@ void sca_destroy(sca_ctx* ctx);
 /* Ensembles: many independent realizations in one persistent launch.       */
 /* ------------------------------------------------------------------------ */
 /* A batch advances thousands of independent lattices of uneven size in one
- * persistent, hipGraph-captured kernel launch per epoch.  Each realization
+ * persistent kernel launch per epoch: realizations with dyadic p, q that the
+ * registers of up to eight compute units hold (up to 2^23 sites) stay on chip
+ * for the epoch, the others go through a second, hipGraph-captured persistent
+ * kernel.  Each realization
  * draws from its own seed with the same counters as the single-lattice path,
  * so its state after any number of MCS is bit-identical to a solo run of the
  * same (X, Y, p, q, seed) -- independent of the schedule and configuration.
  * States live in a caller-owned device arena; the library keeps a small
- * table of per-slot descriptors on the device. */
+ * table of per-slot descriptors on the device (and, once a realization needs
+ * several compute units, 3 MiB for the messages between them). */
 
 typedef struct sca_batch sca_batch;
 
@@ -289,14 +293,16 @@ typedef struct sca_req {
     uint32_t reserved; /* must be 0 */
 } sca_req;
 
-/* Launch shape and schedule of the persistent kernel.  Every setting gives
- * bit-identical results; only the speed differs. */
+/* Launch shape and schedule of the second persistent kernel; lds_bytes = 0
+ * sends every realization to it.  Every setting gives bit-identical results;
+ * only the speed differs. */
 typedef struct sca_batch_config {
     int32_t block_threads; /* workgroup size: 256, 512 or 1024 */
     int32_t blocks_per_cu; /* persistent workgroups per compute unit, 1..8 */
     int32_t lds_bytes;     /* realizations with 32*X*Y/128 <= lds_bytes bytes of
                               state (X >= 128; 4*Y*8 bytes for X < 128) run
-                              from LDS; 0 = never; at most 65536 */
+                              from LDS; 0 = never, and no realization stays
+                              on chip; at most 65536 */
     int32_t order;         /* 0: longest remaining work first, 1: slot order */
     int32_t words_per_lane;/* word tile: 64-site words per lane in a row, 1 or 2 */
     int32_t depth;         /* realizations in global memory with dyadic p, q and

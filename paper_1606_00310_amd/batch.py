@@ -1,5 +1,5 @@
-"""Ensembles of independent realizations advanced by one persistent,
-graph-captured launch per epoch (sca_batch_* in include/sca.h).
+"""Ensembles of independent realizations advanced by persistent launches, one
+per epoch for those that stay on chip (sca_batch_* in include/sca.h).
 
 The states live in one caller-owned device arena (a torch int64 tensor) whose
 size is the HBM budget; admission fails with SCA_EBUSY when slots or arena

@@ -1021,6 +1021,8 @@ struct sca_batch {
     int64_t save_words = 0;         // per workgroup (and per part) in the captured graph
     int32_t resident = 0;           // workgroups of the captured launch that run at once
     int32_t* d_sync = nullptr;      // barrier counters of split realizations (one per part slot of the grid)
+    uint64_t* d_team = nullptr;     // posts and messages of on-chip teams (allocated on first use)
+    int32_t cu_grid = 0;            // workgroups of the on-chip launch: one per compute unit, 0 if it does not fit
     int32_t* d_err = nullptr;       // set by a barrier wait that gave up
     int32_t* h_err = nullptr;       // pinned copy of d_err, written after each launch
     hipEvent_t err_copied = nullptr;
@@ -1028,7 +1030,7 @@ struct sca_batch {
     // device (library-owned)
     sca::BatchDesc* d_desc = nullptr;
     int32_t* d_order = nullptr;
-    int32_t* d_counters = nullptr;  // [0] item count, [1] work queue
+    int32_t* d_counters = nullptr;  // kCounters words, see below
     int64_t* d_ws = nullptr;        // moments workspace for Y up to 131072
     int64_t* pinned = nullptr;      // result slot of sca_batch_roughness, or nullptr
     // pinned staging
@@ -1047,6 +1049,11 @@ struct sca_batch {
 };
 
 namespace {
+
+// The launch counters, staged and copied with the order: the persistent
+// kernel's item count and queue, then the on-chip kernel's four list lengths
+// and queues (the copy zeroes the queues).
+enum { kItems = 0, kQueue = 1, kOnChipCount = 4, kOnChipQueue = 8, kCounters = 12 };
 
 int bfail(sca_batch* b)
 {
@@ -1070,6 +1077,7 @@ void batch_free(sca_batch* b)
     (void)hipFree(b->d_ws);
     (void)hipFree(b->d_save);
     (void)hipFree(b->d_sync);
+    (void)hipFree(b->d_team);
     (void)hipFree(b->d_err);
     (void)hipHostFree(b->h_err);
     if (b->err_copied) (void)hipEventDestroy(b->err_copied);
@@ -1111,11 +1119,11 @@ hipError_t capture_epoch_graph(sca_batch* b)
     b->save_words = depth > 0 ? save_words : 0;
     const int occ = sca::ensemble_occupancy(b->cfg.block_threads, b->cfg.words_per_lane, b->cfg.lds_bytes, depth);
     b->resident = std::min(grid, occ * b->num_cus);
-    sca::BatchLaunch L{b->d_desc, b->d_order, b->d_counters, b->d_counters + 1, b->cfg.lds_bytes,
+    sca::BatchLaunch L{b->d_desc, b->d_order, b->d_counters + kItems, b->d_counters + kQueue, b->cfg.lds_bytes,
                        depth,     b->d_save,  save_words,    b->d_sync,         grid,
                        b->d_err};
     if (hipStreamBeginCapture(b->capture, hipStreamCaptureModeRelaxed) != hipSuccess) return hipErrorUnknown;
-    hipError_t e1 = sca::launch_counter_reset(b->d_counters + 1, b->d_sync, grid, b->capture);
+    hipError_t e1 = sca::launch_counter_reset(b->d_counters + kQueue, b->d_sync, grid, b->capture);
     if (e1 == hipSuccess)
         e1 = sca::launch_ensemble(L, b->cfg.block_threads, b->cfg.words_per_lane, grid, b->capture);
     hipGraph_t graph = nullptr;
@@ -1169,11 +1177,11 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     const size_t nd = sizeof(sca::BatchDesc) * (size_t)max_slots,
                  no = sizeof(int32_t) * ((size_t)max_slots + (size_t)b->num_cus * 8);
     if (hipMalloc(&b->d_desc, nd) != hipSuccess || hipMalloc(&b->d_order, no) != hipSuccess ||
-        hipMalloc(&b->d_counters, 2 * sizeof(int32_t)) != hipSuccess ||
+        hipMalloc(&b->d_counters, kCounters * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(&b->d_ws, sizeof(int64_t) * (size_t)(4 * 131072 + 8)) != hipSuccess ||
         hipHostMalloc(&b->h_desc, nd, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc(&b->h_order, no, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&b->h_count, sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(&b->h_count, kCounters * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&b->staged, hipEventDisableTiming) != hipSuccess ||
         hipMalloc(&b->d_flat, sizeof(sca::FlatItem) * (size_t)max_slots) != hipSuccess ||
         hipHostMalloc(&b->h_flat, sizeof(sca::FlatItem) * (size_t)max_slots, hipHostMallocDefault) != hipSuccess ||
@@ -1190,6 +1198,7 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     std::memset(b->h_desc, 0, nd);
     *b->h_err = 0;
     b->pinned = g_slots.take();
+    b->cu_grid = sca::onchip_occupancy() > 0 ? b->num_cus : 0;
     *out = b;
     return SCA_OK;
 }
@@ -1322,15 +1331,23 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     // the staging buffers are free once the previous epoch's copies have run
     if (b->staged_pending && hipEventSynchronize(b->staged) != hipSuccess) return bfail(b);
     b->staged_pending = false;
-    // The save areas and the depth of the captured graph decide which
-    // realizations can run blocked, so the graph is made first.
-    if (!b->exec && capture_epoch_graph(b) != hipSuccess) return bfail(b);
-    const int32_t grid = b->num_cus * b->cfg.blocks_per_cu;
-    const int32_t max_depth = b->save_words > 0 ? b->cfg.depth : 0;
     int32_t count = 0, hi = -1;
-    std::vector<std::pair<int64_t, int32_t>> work;
+    std::vector<std::pair<int64_t, int32_t>> work, chip[4];
     std::vector<int64_t> runs((size_t)b->max_slots, 0);
-    int64_t total = 0;
+    int64_t total = 0, rest_total = 0;
+    // On chip (unless the configuration keeps states in the arena) go the
+    // bit-mask realizations that up to eight workgroups hold, with as few
+    // workgroups as do, or more where each would have more than half of the
+    // average work per compute unit and its rows per thread can still be halved.
+    // Work is counted in vector instructions (p = 15/16 takes more than twice
+    // those of p = 1/2 per site).  512 realizations of 2^6 to 2^11 squared: 3.7 ms;
+    // with sites for work and a whole average as the line 5.2 ms, the longest
+    // realization with eight workgroups alone 3.6 ms.
+    auto cost = [](const SlotHost& s, int64_t run) {
+        const int64_t nd = s.desc.mode == 0 ? s.desc.ndraw : 32, q = s.desc.has_q;
+        return run * s.req.Y * s.W * (30 + 10 * q + 18 * nd + 2 * nd * (1 + q));
+    };
+    int32_t active = 0;
     for (int32_t slot = 0; slot < b->max_slots; ++slot) {
         SlotHost& s = b->slots[(size_t)slot];
         if (!s.used) continue;
@@ -1339,6 +1356,29 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         if (run > left) run = left;
         if (run < 0) run = 0;
         runs[(size_t)slot] = run;
+        if (run > 0) {
+            total += cost(s, run);
+            ++active;
+        }
+    }
+    const int64_t chip_share = b->cu_grid > 0 ? total / (2 * b->cu_grid) : 0;
+    auto chip_parts = [&](const SlotHost& s, int64_t w, int32_t* rows) {
+        const int Y = (int)s.req.Y;
+        for (int32_t P = 1; P <= sca::kOnChipMaxParts && P <= b->cu_grid; P *= 2) {
+            const int N = sca::onchip_rows(s.W, Y, P);
+            if (N == 0) continue;
+            const bool more = b->cfg.order == 0 && w / P > chip_share && N > 2 && 2 * P <= sca::kOnChipMaxParts &&
+                              2 * P <= b->cu_grid;
+            if (more && sca::onchip_rows(s.W, Y, 2 * P) > 0) continue;
+            *rows = N;
+            return P;
+        }
+        return 0;
+    };
+    for (int32_t slot = 0; slot < b->max_slots; ++slot) {
+        SlotHost& s = b->slots[(size_t)slot];
+        if (!s.used) continue;
+        const int64_t run = runs[(size_t)slot], w = run * s.req.X * s.req.Y;
         sca::BatchDesc d = s.desc;
         d.t = (uint32_t)s.t;
         d.n_run = (uint32_t)run;
@@ -1347,20 +1387,39 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         d.parts = 1;
         d.sync_idx = 0;
         d.save = nullptr;
-        if (d.mode == 0 && run > 0)
-            (void)sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, 1, &d.depth, &d.bands);
+        if (run > 0) {
+            int32_t rows = 0;
+            const int32_t P = (b->cfg.lds_bytes > 0 && d.mode == 0) ? chip_parts(s, cost(s, run), &rows) : 0;
+            if (P > 0) {
+                d.parts = P;
+                d.bands = rows;
+                chip[P == 8 ? 0 : P == 4 ? 1 : P == 2 ? 2 : 3].emplace_back(cost(s, run), slot);
+            } else {
+                work.emplace_back(w, slot);
+                rest_total += w;
+            }
+        }
         b->h_desc[slot] = d;
         hi = slot;
-        if (run > 0) {
-            work.emplace_back(run * s.req.X * s.req.Y, slot);
-            total += run * s.req.X * s.req.Y;
-        }
     }
-    if (b->cfg.order == 0)
-        std::stable_sort(work.begin(), work.end(),
-                         [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
-                             return x.first > y.first;
-                         });
+    const auto longer = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
+        return x.first > y.first;
+    };
+    // The save areas and the depth of the captured graph decide which
+    // realizations can run blocked, so the graph is made first.
+    if (!work.empty() && !b->exec && capture_epoch_graph(b) != hipSuccess) return bfail(b);
+    const int32_t grid = b->num_cus * b->cfg.blocks_per_cu;
+    const int32_t max_depth = b->save_words > 0 ? b->cfg.depth : 0;
+    for (const auto& w : work) {
+        sca::BatchDesc& d = b->h_desc[w.second];
+        const SlotHost& s = b->slots[(size_t)w.second];
+        if (d.mode == 0)
+            (void)sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, 1, &d.depth, &d.bands);
+    }
+    if (b->cfg.order == 0) {
+        std::stable_sort(work.begin(), work.end(), longer);
+        for (auto& list : chip) std::stable_sort(list.begin(), list.end(), longer);
+    }
     // Realizations that run as temporally blocked passes go first (the
     // persistent kernel takes them in a phase of their own), and among them
     // the split ones: a blocked realization with more work than the average
@@ -1372,7 +1431,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     std::stable_partition(work.begin(), work.end(), [b](const std::pair<int64_t, int32_t>& w) {
         return b->h_desc[w.second].depth > 0;
     });
-    const int64_t avg = total / grid;
+    const int64_t avg = rest_total / grid;
     int32_t parts_used = 0, n_split = 0;
     std::vector<std::pair<int64_t, int32_t>> split, rest;
     for (const auto& w : work) {
@@ -1405,25 +1464,48 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         for (int32_t m = 0; m < b->h_desc[w.second].parts; ++m)
             b->h_order[count++] = w.second | (m << sca::kItemSlotBits);
     for (const auto& w : rest) b->h_order[count++] = w.second;
-    if (active_out) *active_out = (int32_t)work.size();
+    const int32_t items = count;
+    std::memset(b->h_count, 0, kCounters * sizeof(int32_t));
+    b->h_count[kItems] = items;
+    for (int i = 0; i < 4; ++i) {
+        b->h_count[kOnChipCount + i] = (int32_t)chip[i].size();
+        for (const auto& w : chip[i]) b->h_order[count++] = w.second;
+    }
+    const bool teams = !chip[0].empty() || !chip[1].empty() || !chip[2].empty();
+    if (active_out) *active_out = active;
     if (count == 0) return SCA_OK;
-    *b->h_count = count;
+    if (teams && !b->d_team &&
+        hipMalloc(&b->d_team, sizeof(uint64_t) * (size_t)(sca::onchip_mail_words(b->cu_grid) +
+                                                          sca::onchip_message_words(b->cu_grid))) != hipSuccess)
+        return bfail(b);
     if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1), hipMemcpyHostToDevice,
                        b->stream) != hipSuccess ||
         hipMemcpyAsync(b->d_order, b->h_order, sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, b->stream) !=
             hipSuccess ||
-        hipMemcpyAsync(b->d_counters, b->h_count, sizeof(int32_t), hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+        hipMemcpyAsync(b->d_counters, b->h_count, kCounters * sizeof(int32_t), hipMemcpyHostToDevice, b->stream) !=
+            hipSuccess ||
         hipEventRecord(b->staged, b->stream) != hipSuccess)
         return bfail(b);
     b->staged_pending = true;
-    if (hipGraphLaunch(b->exec, b->stream) != hipSuccess) return bfail(b);
-    if (n_split > 0 && !b->err_pending) {
+    if (count > items) {
+        const sca::OnChipLaunch L{b->d_desc,
+                                  b->d_order + items,
+                                  b->d_counters + kOnChipCount,
+                                  b->d_counters + kOnChipQueue,
+                                  b->d_team,
+                                  b->d_team + (teams ? sca::onchip_mail_words(b->cu_grid) : 0),
+                                  b->d_err};
+        if (sca::launch_onchip(L, b->cu_grid, teams, b->stream) != hipSuccess) return bfail(b);
+    }
+    if (items > 0 && hipGraphLaunch(b->exec, b->stream) != hipSuccess) return bfail(b);
+    if ((n_split > 0 || teams) && !b->err_pending) {
         if (hipMemcpyAsync(b->h_err, b->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, b->stream) != hipSuccess ||
             hipEventRecord(b->err_copied, b->stream) != hipSuccess)
             return bfail(b);
         b->err_pending = true;
     }
-    for (const auto& w : work) b->slots[(size_t)w.second].t += runs[(size_t)w.second];
+    for (int32_t slot = 0; slot < b->max_slots; ++slot)
+        if (b->slots[(size_t)slot].used) b->slots[(size_t)slot].t += runs[(size_t)slot];
     return SCA_OK;
 }
 

@@ -171,6 +171,38 @@ hipError_t launch_counter_reset(int32_t* counter, int32_t* sync, int32_t n_sync,
 // holds at once (0 if unknown).
 int ensemble_occupancy(int block_threads, int words_per_lane, int lds_bytes, int depth);
 
+// Realizations that stay on chip for an epoch (onchip.hip): bit-mask mode, in
+// a team of d.parts workgroups of kOnChipThreads threads with d.bands rows of
+// one word column per thread.
+constexpr int kOnChipThreads = 1024;
+constexpr int kOnChipMaxParts = 8;
+struct OnChipLaunch {
+    const BatchDesc* desc;
+    const int32_t* order;  // slots: the lists for teams of 8, 4, 2 and 1 workgroups, one after another
+    const int32_t* count;  // [4] entries of each list
+    int32_t* queue;        // [4] entries taken, 0 before the launch
+    uint64_t* mail;        // onchip_mail_words(grid), and behind them
+    uint64_t* xch;         // onchip_message_words(grid); neither without teams
+    int32_t* err;          // set if a wait ran out of patience
+};
+int64_t onchip_mail_words(int grid);
+int64_t onchip_message_words(int grid);
+// grid: workgroups, at most as many as run at once; teams: a list other than
+// the last has entries.
+hipError_t launch_onchip(const OnChipLaunch& L, int grid, bool teams, hipStream_t stream);
+int onchip_occupancy();
+
+// Rows per thread (2, 4 or 8) with which `parts` workgroups hold a lattice of Y
+// rows of W words, or 0.
+inline int onchip_rows(int W, int Y, int parts)
+{
+    if (W > 64 || Y % parts != 0) return 0;
+    const int R = Y / parts;
+    for (int N = 2; N <= 8; N *= 2)
+        if (R % N == 0 && R / N * W <= kOnChipThreads) return N;
+    return 0;
+}
+
 hipError_t launch_philox_rate(int64_t threads, int32_t calls, uint32_t* sink, hipStream_t stream);
 
 hipError_t launch_philox_test(const uint32_t* ctr, uint32_t k0, uint32_t k1, int64_t n,

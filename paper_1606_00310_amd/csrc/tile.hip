@@ -38,7 +38,7 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
     const bool active = grp < groups;
 
     TileThread<G, N, I, MODE, HASQ, DR> th;
-    th.rl = RowLanes{a.nb, gl == 0, gl == GL - 1, (tid & 32) != 0};
+    th.rl = RowLanes{GL, a.nb, gl == 0, gl == GL - 1, (tid & 32) != 0};
     // idle threads of the last wave (fewer groups than fit) keep an LDS word of
     // their own beside the tile's
     th.own = tid;
@@ -48,16 +48,18 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
     const int r0 = grp * N;                       // first tile row of this thread
     const int y0 = (int)blockIdx.x * L.band - L.halo + r0;
     const int ymask = a.Y - 1;
+    // (y0 is a multiple of N: a thread's rows do not wrap)
+    th.W = (uint32_t)a.W;
+    th.g0 = (uint32_t)(y0 & ymask) * th.W + (uint32_t)gl;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const int y = (y0 + i) & ymask;
-        th.g[i] = (uint32_t)y * (uint32_t)a.W + (uint32_t)gl;
+        const int y = (y0 & ymask) + i;
         if (i % 2 == 0) th.org[i / 2] = active && y == 0 && gl == 0 && r0 + i >= L.halo && r0 + i < L.halo + L.band;
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
             for (int k = 0; k < I; ++k) {
-                const int64_t w = (int64_t)th.g[i] + 64 * k;
+                const int64_t w = (int64_t)th.g(i) + 64 * k;
                 th.x[i][p][k] = active ? L.src[(int64_t)p * a.plane + w] : 0ull;
                 th.y[i][p][k] = active ? L.src[(int64_t)(2 + p) * a.plane + w] : 0ull;
             }
@@ -79,11 +81,12 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
     int hi = L.halo > 0 ? L.halo + L.band + 2 * L.n - 2 : L.rows - 1;
     const int shrink = L.halo > 0 ? 1 : 0;
     SweepArgs ah = a;
+    NoEdge edge;
     for (int m = 0; m < L.n; ++m) {
-        th.template halfstep<0>(ah, ly, lo, hi, whi < lo || wlo > hi);
+        th.template halfstep<0>(ah, ly, lo, hi, whi < lo || wlo > hi, edge);
         lo += shrink;
         hi -= shrink;
-        th.template halfstep<1>(ah, ly, lo, hi, whi < lo || wlo > hi);
+        th.template halfstep<1>(ah, ly, lo, hi, whi < lo || wlo > hi, edge);
         lo += shrink;
         hi -= shrink;
         ++ah.t;
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
         for (int p = 0; p < 2; ++p)
 #pragma unroll
             for (int k = 0; k < I; ++k) {
-                const int64_t w = (int64_t)th.g[i] + 64 * k;
+                const int64_t w = (int64_t)th.g(i) + 64 * k;
                 L.dst[(int64_t)p * a.plane + w] = th.x[i][p][k];
                 L.dst[(int64_t)(2 + p) * a.plane + w] = th.y[i][p][k];
             }

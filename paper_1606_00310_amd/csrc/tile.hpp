@@ -38,9 +38,9 @@ namespace sca {
 namespace {
 
 // The lanes of a row.  G lanes hold it (a power of two up to 64); G = 0: one
-// lane whose word has fewer than 64 bits in use.
+// lane whose word has fewer than 64 bits in use; G = -1: known at run time.
 struct RowLanes {
-    int nb;            // used bits per word (G = 0)
+    int G, nb;         // run-time G and the used bits per word (scalars; G = -1, nb also G = 0)
     bool first, last;  // this lane holds the row's first / last word
     bool upper;        // lane 32 or above
 };
@@ -70,6 +70,17 @@ __device__ __forceinline__ uint32_t group_next(uint32_t v, const RowLanes& r)
     }
     if constexpr (G == 16) return dpp<0x12f /* row_ror:15 */>(v);
     if constexpr (G == 64) return from_next_lane(v);
+    if constexpr (G < 0) {
+        switch (r.G) {
+        case 1: return v;
+        case 2: return group_next<2>(v, r);
+        case 4: return group_next<4>(v, r);
+        case 8: return group_next<8>(v, r);
+        case 16: return group_next<16>(v, r);
+        case 32: return group_next<32>(v, r);
+        default: return group_next<64>(v, r);
+        }
+    }
     if constexpr (G == 32) {
         const uint32_t n = from_next_lane(v);
         const uint32_t v0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
@@ -91,6 +102,17 @@ __device__ __forceinline__ uint32_t group_prev(uint32_t v, const RowLanes& r)
     }
     if constexpr (G == 16) return dpp<0x121 /* row_ror:1 */>(v);
     if constexpr (G == 64) return from_prev_lane(v);
+    if constexpr (G < 0) {
+        switch (r.G) {
+        case 1: return v;
+        case 2: return group_prev<2>(v, r);
+        case 4: return group_prev<4>(v, r);
+        case 8: return group_prev<8>(v, r);
+        case 16: return group_prev<16>(v, r);
+        case 32: return group_prev<32>(v, r);
+        default: return group_prev<64>(v, r);
+        }
+    }
     if constexpr (G == 32) {
         const uint32_t p = from_prev_lane(v);
         const uint32_t v31 = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
@@ -158,9 +180,9 @@ __device__ __forceinline__ void tile_row(const RowLanes& rl, uint64_t (&A)[I], u
     if constexpr (!SH) {
 #pragma unroll
         for (int i = 0; i < I; ++i) XP[i] = D[i];
-    } else if constexpr (G == 0) {
+    } else if (G == 0 || (G < 0 && rl.nb < 64)) {
         XP[0] = (D[0] >> 1) | ((D[0] & 1ull) << (rl.nb - 1));
-    } else {
+    } else if constexpr (G != 0) {
         uint32_t nl[I];
 #pragma unroll
         for (int i = 0; i < I; ++i) nl[i] = group_next<G>((uint32_t)D[i], rl);
@@ -193,9 +215,9 @@ __device__ __forceinline__ void tile_row(const RowLanes& rl, uint64_t (&A)[I], u
     if constexpr (!SH) {
 #pragma unroll
         for (int i = 0; i < I; ++i) D[i] ^= M[i];
-    } else if constexpr (G == 0) {
+    } else if (G == 0 || (G < 0 && rl.nb < 64)) {
         D[0] ^= ((M[0] << 1) | (M[0] >> (rl.nb - 1))) & ((1ull << rl.nb) - 1ull);
-    } else {
+    } else if constexpr (G != 0) {
         uint32_t ph[I];
 #pragma unroll
         for (int i = 0; i < I; ++i) ph[i] = group_prev<G>((uint32_t)(M[i] >> 32), rl);
@@ -252,6 +274,23 @@ struct PerSiteTile {
     }
 };
 
+// What a half-step does at the tile's first and last row beyond the tile:
+// nothing, where the tile wraps or its halo runs out.
+struct NoEdge {
+    template <int I>
+    __device__ __forceinline__ void take(uint64_t (&)[I], uint64_t (&)[I])
+    {
+    }
+    template <int I>
+    __device__ __forceinline__ void give_first(const uint64_t (&)[I])
+    {
+    }
+    template <int I>
+    __device__ __forceinline__ void give_last(const uint64_t (&)[I])
+    {
+    }
+};
+
 // The rows of one thread and the half-step over them.
 template <int G, int N, int I, XiMode MODE, bool HASQ, Draws DR>
 struct TileThread {
@@ -262,13 +301,19 @@ struct TileThread {
     // it starts with and so off the path from write to read.  Per-site words
     // come from LDS behind the barrier.
     static constexpr bool PRE = N * I <= 2 && MODE != XiMode::PerSite;
-    static constexpr int NX = 2 / I;
+    static constexpr int NX = N >= 8 ? 1 : 2 / I;
+    // The shared last draw of an odd number of draws waits for the odd
+    // half-step in registers, or in LDS (one word per thread and row) where the
+    // rows leave none.
     static constexpr bool TAIL = DR == Draws::OddTail && MODE == XiMode::Mask;
+    static constexpr bool TAIL_LDS = TAIL && N >= 8;
 
     uint64_t x[N][2][I];  // x-slopes by sublattice
     uint64_t y[N][2][I];  // y-slopes; row 0 only within a half-step
-    uint64_t tail[TAIL ? N * I : NX * I];
-    uint32_t g[N];        // canonical index of word 0 of each row
+    uint64_t tail[TAIL && !TAIL_LDS ? N : 1][I];
+    uint64_t* kept;       // of row 0, blockDim.x words apart (TAIL_LDS)
+    uint32_t g0;          // canonical index of row 0's word 0 (the rows lie W apart)
+    uint32_t W;
     RowLanes rl;
     int own, nxt;         // LDS index of this thread's first row and of the next thread's (stride words apart per i)
     int stride;           // LDS words per (sublattice, i)
@@ -277,18 +322,41 @@ struct TileThread {
     PerSiteTile ps;       // per-site mode
     int xrow;             // index of the first row's word in a buffer of acceptance words
 
-    // Acceptance words of rows i0 .. i0+NX-1.
-    __device__ __forceinline__ void words(const SweepArgs& a, int i0, uint64_t (&xp)[NX][I], uint64_t (&xq)[NX][I])
+    // The rows of a half-step are independent; they go first, last, then the
+    // ones between, so that the two that a neighbouring tile waits for come
+    // early.
+    static constexpr __device__ int row(int m) { return m == 0 ? 0 : m == 1 ? N - 1 : m - 1; }
+
+    __device__ __forceinline__ uint32_t g(int i) const { return g0 + (uint32_t)i * W; }
+
+    // Acceptance words of rows row(m0) .. row(m0 + NX - 1).
+    __device__ __forceinline__ void words(const SweepArgs& a, int m0, uint64_t (&xp)[NX][I], uint64_t (&xq)[NX][I])
     {
         if constexpr (MODE == XiMode::Mask) {
             uint32_t gg[NX * I];
-            uint64_t p[NX * I], q[NX * I];
+            uint64_t p[NX * I], q[NX * I], t[NX * I];
 #pragma unroll
-            for (int m = 0; m < NX * I; ++m) gg[m] = g[i0 + m / I] + 64u * (m % I);
-            uint64_t(&t)[NX * I] = *reinterpret_cast<uint64_t(*)[NX * I]>(&tail[TAIL ? i0 * I : 0]);
+            for (int m = 0; m < NX * I; ++m) {
+                gg[m] = g(row(m0 + m / I)) + 64u * (m % I);
+                // With many rows per thread the products of the word index that
+                // every Philox call starts with are formed anew each time: kept
+                // across the half-steps they take four registers per row.
+                if constexpr (N >= 4) asm volatile("" : "+v"(gg[m]));
+                t[m] = 0;
+                if constexpr (TAIL_LDS) {
+                    if (a.parity == 1) t[m] = kept[row(m0 + m) * (int)blockDim.x];
+                } else if constexpr (TAIL) {
+                    t[m] = tail[row(m0 + m / I)][m % I];
+                }
+            }
             mask_words_side_by_side<DR, HASQ>(a, gg, p, q, t);
 #pragma unroll
             for (int m = 0; m < NX * I; ++m) {
+                if constexpr (TAIL_LDS) {
+                    if (a.parity == 0) kept[row(m0 + m) * (int)blockDim.x] = t[m];
+                } else if constexpr (TAIL) {
+                    tail[row(m0 + m / I)][m % I] = t[m];
+                }
                 xp[m / I][m % I] = p[m];
                 xq[m / I][m % I] = q[m];
             }
@@ -298,9 +366,9 @@ struct TileThread {
                 xp[m / I][m % I] = a.all_p;
                 xq[m / I][m % I] = a.all_q;
                 if constexpr (MODE == XiMode::PerSite) {
-                    const uint64_t* x = ps.buffer(a.parity) + xrow + ((i0 + m) << ps.lw);
-                    xp[m][0] |= x[0];
-                    if (HASQ) xq[m][0] |= x[ps.words];
+                    const uint64_t* w = ps.buffer(a.parity) + xrow + (row(m0 + m) << ps.lw);
+                    xp[m][0] |= w[0];
+                    if (HASQ) xq[m][0] |= w[ps.words];
                 }
             }
         }
@@ -308,8 +376,8 @@ struct TileThread {
 
     // Half-step of sublattice PI at MCS a.t; tile rows lo .. hi have to be
     // right, and `skip` (scalar): none of the wave's rows are among them.
-    template <int PI>
-    __device__ __forceinline__ void halfstep(SweepArgs a, uint64_t* ly, int lo, int hi, bool skip)
+    template <int PI, class Edge>
+    __device__ __forceinline__ void halfstep(SweepArgs a, uint64_t* ly, int lo, int hi, bool skip, Edge& edge)
     {
         a.parity = PI;
         uint64_t xp[NX][I], xq[NX][I];
@@ -327,18 +395,20 @@ struct TileThread {
             y[0][PI][k] = lB[k * stride + own];
             Cn[k] = lC[k * stride + nxt];
         }
+        edge.take(y[0][PI], Cn);
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
+        for (int m = 0; m < N; ++m) {
+            constexpr bool even_shifted = PI != 0;  // rows of even i are shifted in the odd half-step
+            const int i = row(m);
             uint64_t mp0 = 0, mq0 = 0;
             if constexpr (!PRE)
-                if (i % NX == 0) words(a, i, xp, xq);
+                if (m % NX == 0) words(a, m, xp, xq);
             uint64_t(&C)[I] = i + 1 < N ? y[i + 1 < N ? i + 1 : 0][1 - PI] : Cn;
-            constexpr bool even_shifted = PI != 0;  // rows of even i are shifted in the odd half-step
             if ((i & 1) == 0)
-                tile_row<G, even_shifted, I, HASQ>(rl, x[i][PI], y[i][PI], C, x[i][1 - PI], xp[i % NX], xq[i % NX],
+                tile_row<G, even_shifted, I, HASQ>(rl, x[i][PI], y[i][PI], C, x[i][1 - PI], xp[m % NX], xq[m % NX],
                                                    mp0, mq0);
             else
-                tile_row<G, !even_shifted, I, HASQ>(rl, x[i][PI], y[i][PI], C, x[i][1 - PI], xp[i % NX], xq[i % NX],
+                tile_row<G, !even_shifted, I, HASQ>(rl, x[i][PI], y[i][PI], C, x[i][1 - PI], xp[m % NX], xq[m % NX],
                                                     mp0, mq0);
             // Pin the new slopes here, or the compiler interleaves the rows and
             // keeps the masks of all of them live.
@@ -351,6 +421,8 @@ struct TileThread {
                 lifts += (int32_t)((uint32_t)mp0 & org[i / 2]);
                 if (HASQ) lifts -= (int32_t)((uint32_t)mq0 & org[i / 2]);
             }
+            if (m == 0) edge.give_first(y[0][PI]);
+            if (m == 1) edge.give_last(Cn);
         }
 #pragma unroll
         for (int k = 0; k < I; ++k) {

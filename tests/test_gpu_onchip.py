@@ -1,0 +1,139 @@
+"""Ensemble realizations that stay on chip for an epoch, in one workgroup or in
+a team of them, against their solo runs and the oracle, bit for bit."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def sca():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1606_00310_amd as P
+
+    P.lib()
+    return P
+
+
+def run_batch(reals, epochs=(), **config):
+    from paper_1606_00310_amd.batch import Batch, state_bytes
+
+    b = Batch(max_slots=len(reals), arena_bytes=sum(state_bytes(r.X, r.Y) for r in reals), config=config or None)
+    slots = b.admit(reals)
+    for e in epochs:
+        b.run(e)
+    while b.run(1 << 20):
+        pass
+    torch.cuda.synchronize()
+    return b, slots
+
+
+def check_solo(sca, b, slots, reals):
+    for r, s in zip(reals, slots):
+        lat = sca.Lattice(r.X, r.Y, seed=r.seed)
+        lat.step(r.n_mcs, r.p, r.q, fuse=False)
+        S, h0 = b.state(s)
+        assert torch.equal(S, lat.slopes), r
+        assert (b.info(s).t, int(h0[0])) == lat.meta(), r
+        assert b.roughness(s) == lat.roughness(), r
+        lat.close()
+    b.close()
+
+
+PROBS = [(0.5, 0.0), (0.5, 0.5), (0.75, 0.25), (0.9375, 0.0), (1.0, 0.0), (0.0, 1.0)]
+
+# workgroups and rows per thread: partial words and idle waves; 2, 4 and 8 rows
+# in one workgroup; teams of 2, 4 and 8 with 8 rows; the widest and the narrowest
+# rows; too large for a team (128 MCS of 8192 x 2048 cost little), which the
+# blocked passes take
+SIZES = [(4, 4, 9), (16, 64, 9), (64, 64, 9), (128, 8, 9), (64, 2048, 7), (256, 256, 9), (512, 512, 7), (1024, 512, 7),
+         (1024, 1024, 7), (128, 8192, 5), (2048, 1024, 7), (2048, 2048, 7), (4096, 2048, 5), (8192, 1024, 5),
+         (8192, 128, 5), (512, 16384, 5), (8192, 2048, 3)]
+
+
+@pytest.mark.parametrize("X,Y,n", SIZES)
+def test_alone(sca, X, Y, n):
+    """One realization at a time and probability pair: one workgroup, or one
+    team with all its row groups at the edge of another's."""
+    from paper_1606_00310_amd.batch import Realization as R
+
+    for k, (p, q) in enumerate(PROBS):
+        _say(f"[on chip] {X}x{Y} p={p} q={q}")
+        reals = [R(X, Y, p, q, n, 50 + k)]
+        b, slots = run_batch(reals, epochs=(1, 2))
+        check_solo(sca, b, slots, reals)
+
+
+def test_against_oracle(orc):
+    from paper_1606_00310_amd.batch import Realization as R
+
+    reals = [R(2048, 2048, 0.75, 0.25, 5, 1), R(2048, 2048, 0.5, 0.0, 6, 2), R(64, 128, 0.9375, 0.0, 40, 3),
+             R(1024, 1024, 0.5, 0.5, 5, 4), R(32, 64, 0.5, 0.25, 30, 5)]
+    b, slots = run_batch(reals)
+    for r, s in zip(reals, slots):
+        st = orc.flat(r.X, r.Y)
+        orc.run(st, r.n_mcs, r.p, r.q, seed=r.seed)
+        S, h0 = b.state(s)
+        assert np.array_equal(S.cpu().numpy().view(np.uint64), orc.pack(st)), r
+        assert int(h0[0]) == st.h0, r
+    b.close()
+
+
+def test_every_team_size_in_one_epoch(sca):
+    """Long and short realizations for eight, four, two and one workgroups, more
+    than there are teams, epochs of one MCS among them (a team may then be a
+    realization ahead of its slowest member), beside per-site and oversized ones
+    that the persistent kernel runs."""
+    from paper_1606_00310_amd.batch import Realization as R
+
+    reals = []
+    for k in range(48):
+        p, q = PROBS[k % len(PROBS)]
+        reals.append(R(*[(4096, 2048), (2048, 2048), (2048, 1024), (1024, 1024), (64, 64), (4096, 1024)][k % 6], p, q,
+                       1 + (7 * k) % 11, 900 + k))
+    reals += [R(256, 256, 0.3, 0.1, 4, 77), R(8192, 2048, 0.5, 0.0, 3, 78), R(512, 64, 0.95, 0.0, 12, 79)]
+    b, slots = run_batch(reals, epochs=(1, 1, 3))
+    check_solo(sca, b, slots, reals)
+
+
+def test_many_single_mcs_epochs(sca):
+    """Teams of eight and four through a long list of one-MCS items, many
+    launches in a row."""
+    from paper_1606_00310_amd.batch import Realization as R
+
+    reals = [R(2048, 2048, 0.5, 0.0, 12, 300 + k) for k in range(70)] + \
+        [R(4096, 2048, 0.75, 0.0, 12, 400 + k) for k in range(40)]
+    b, slots = run_batch(reals, epochs=(1,) * 12)
+    check_solo(sca, b, [slots[i] for i in (0, 33, 69, 70, 109)], [reals[i] for i in (0, 33, 69, 70, 109)])
+
+
+def test_two_batches_on_two_streams(sca):
+    """Two ensembles with teams at once: the second waits for compute units, and
+    both end with the bits of their solo runs."""
+    from paper_1606_00310_amd.batch import Batch, Realization as R, state_bytes
+
+    sets, batches = [], []
+    for k in range(2):
+        reals = [R(2048, 2048, 0.75, 0.25, 60, 10 * k + j) for j in range(6)] + [R(512, 512, 0.5, 0.0, 90, 70 + k)]
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            b = Batch(max_slots=len(reals), arena_bytes=sum(state_bytes(r.X, r.Y) for r in reals), stream=stream)
+            slots = b.admit(reals)
+        sets.append(reals)
+        batches.append((b, slots))
+    for _ in range(3):
+        for b, _slots in batches:
+            b.run(30)
+    torch.cuda.synchronize()
+    for (b, slots), reals in zip(batches, sets):
+        check_solo(sca, b, slots, reals)
