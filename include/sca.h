@@ -38,9 +38,10 @@
  *    and, for the temporally blocked passes, a second buffer of the size of
  *    S (sca_set_pass_buffer).  The library keeps non-owning pointers, so the
  *    caller keeps them alive until sca_destroy.  The library owns only a
- *    small device workspace for the moment sums (about 32*Y bytes),
- *    allocated by sca_init and freed by sca_destroy; sca_step allocates
- *    nothing.
+ *    small device workspace: about 32*Y bytes for the moment sums and, for
+ *    lattices of 2^25 to 2^28 sites with 2048 <= X <= 16384, 1 or 2 MB of
+ *    messages between workgroups.  sca_init allocates it and sca_destroy
+ *    frees it; sca_step allocates nothing.
  *  - Streams: all work is enqueued on the stream given to sca_init.  Only
  *    calls that return numbers to the host synchronize that stream.
  *  - Errors: functions return SCA_OK or a negative code; an invalid argument
@@ -105,7 +106,11 @@ int sca_init(sca_ctx** out, int64_t X, int64_t Y, uint64_t seed, void* slopes_de
  * sca_set_blocking and sca_set_pass_buffer), which divides the HBM traffic per
  * MCS by about 2*depth.  Lattices with X < 8192 do so only if a pass buffer is
  * attached; small ones may run all MCS in one workgroup instead, in place and
- * with or without a buffer.  The passes come in an even number so that S holds
+ * with or without a buffer.  With a buffer attached, lattices of 2^25 to 2^28
+ * sites may run all MCS in one launch and in place, on chip in a team of
+ * workgroups, one per compute unit; a team that other streams' kernels keep from
+ * forming for a millisecond runs the same half-steps in memory, and the context
+ * launches no more of them.  (Not under stream capture.)  The passes come in an even number so that S holds
  * the state when the enqueued work has run: whole passes of `depth` MCS, then
  * the remainder r as two passes of ceil(r/2) and floor(r/2) MCS, or two
  * half-step launches when r = 1 (sca_plan_step reports the plan).  The results are bit-identical
@@ -129,7 +134,8 @@ int sca_step_ex(sca_ctx* ctx, int64_t n_mcs, double p, double q, unsigned flags)
 
 /* The launches sca_step_ex(ctx, n_mcs, p, q, flags) would enqueue with the
  * context's current blocking settings.  All MCS in one workgroup: kernel names
- * it, band is Y and every count of passes and unfused MCS is 0. */
+ * it, band is Y and every count of passes and unfused MCS is 0; all MCS in a
+ * team of workgroups: band is the rows of each of them. */
 typedef struct sca_step_plan {
     int32_t path;          /* SCA_PATH_* */
     int32_t depth;         /* MCS per whole blocked pass; 0 if there is none */

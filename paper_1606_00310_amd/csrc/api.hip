@@ -50,6 +50,7 @@ struct StepPlan {
     int32_t tail1 = 0, tail2 = 0;
     bool whole = false;     // the lattice in one workgroup, in place: all MCS in one launch
     int32_t tile_rows = 0;  // rows per thread of the on-chip tiles, 0: row sweeps or half-step launches
+    int32_t team_rows = 0;  // rows per thread of a team that holds the lattice; 0: no team
 };
 
 }  // namespace sca
@@ -79,6 +80,14 @@ struct sca_ctx {
     int64_t plan_n = -1;
     double plan_p = 0, plan_q = 0;
     unsigned plan_flags = 0;
+    bool plan_team = false;
+    // Teams (team.hip), for the lattices they serve: control words and messages
+    // in device memory (library-owned; nullptr: no teams), workgroups, and the
+    // launches and half-steps so far.  The slot `pinned` has two flags of theirs.
+    uint64_t* team_ctl = nullptr;
+    int32_t team_parts = 0;
+    uint64_t team_epoch = 0;
+    uint32_t team_tag = 0;
 };
 
 namespace {
@@ -112,6 +121,22 @@ int fail(sca_ctx* c)
 {
     if (c) c->failed = true;
     return SCA_EDEVICE;
+}
+
+// The word of a context's result slot that the team kernel sets: a wait ran out
+// of patience [0], the team could not form [1].
+int32_t* team_flags(const sca_ctx* c) { return reinterpret_cast<int32_t*>(c->pinned + 7); }
+
+bool team_flag(const sca_ctx* c, int i)
+{
+    return c->team_ctl && reinterpret_cast<const volatile int32_t*>(c->pinned + 7)[i] != 0;
+}
+
+// Whether steps with these flags may run as a team.  Not as part of a graph:
+// every launch has its number.
+bool may_team(const sca_ctx* c, unsigned flags)
+{
+    return c->team_ctl && !team_flag(c, 1) && !(flags & SCA_STEP_GRAPH);
 }
 
 int64_t* ws_col(sca_ctx* c) { return c->ws + 3 * c->Y; }
@@ -260,6 +285,9 @@ constexpr int64_t kWholeMcs = 1 << 14;
 //  - a half-step of a per-site tile takes 0.5 us and 5.8 ns (6.6 ns with
 //    removals) for every word a CU draws for; unfused it takes 3.7 us, or the
 //    vector issue of the chip, 24 us per 2^20 words;
+//  - a half-step of a team (team.hpp) of N words per thread takes 0.12 us and the
+//    vector issue of its 16 waves per CU, 8.25 V N ns, or the 1.27 us of a
+//    message; a launch adds 6 us and 0.4 us per MB of state;
 //  - a row sweep (fused.hpp) of b rows and d MCS walks b + 4d - 1 steps of
 //    0.6 us (0.35 us at d = 1) for the row to arrive and 2d half-steps, each the longer of its
 //    latency (p = 1/2 on rows of 2^16 sites: 0.21 us) and the share of the k
@@ -281,6 +309,10 @@ struct CostModel {
         : V(30 + (pl.has_q ? 10 : 0) + 18 * pl.ndraw + 2 * pl.ndraw * (pl.has_q ? 2 : 1)), draws(pl.ndraw),
           mb(32e-6 * (double)c->Y * c->W), Y(c->Y), W(c->W), has_q(pl.has_q), draw_free(pl.draw_free), persite(pl.persite)
     {
+    }
+    double team(int64_t n, int32_t words) const
+    {
+        return 6 + 0.4 * mb + 2.0 * (double)n * std::max(1.27, 0.00825 * V * words + 0.12);
     }
     double half(double waves, int32_t words) const { return V * words / 2 * (0.0047 + 0.00044 * waves); }
     // a half-step of a per-site tile with `words` words per CU to draw for
@@ -367,9 +399,9 @@ void set_passes(StepPlan& pl, int64_t n_mcs, bool fuse)
 }
 
 // Chooses by estimated time between half-step launches, the whole lattice in
-// one workgroup, the on-chip tiles and the row sweeps.  Returns false where
+// one workgroup or in a team of them, the on-chip tiles and the row sweeps.  Returns false where
 // the half-step launches win.
-bool plan_by_cost(const sca_ctx* c, int64_t n_mcs, StepPlan& pl)
+bool plan_by_cost(const sca_ctx* c, int64_t n_mcs, bool team, StepPlan& pl)
 {
     const int32_t W = c->W;
     const int64_t Y = c->Y;
@@ -416,10 +448,28 @@ bool plan_by_cost(const sca_ctx* c, int64_t n_mcs, StepPlan& pl)
                 consider(split_cost(n_mcs, d, [&](int32_t e) { return m.sweep(b, e); }, m.unfused()), 0, b, d);
             if (d == half) break;
         }
+    // A team where it is estimated to be a tenth faster, or a fifth on narrow
+    // rows, whose tiles are estimated a little slow.  Without draws a
+    // half-step is little more than its message, which eight words per thread
+    // hide, and narrow rows leave the tiles little to repeat: 2^14 squared gets
+    // faster by 1.7 (p = 1, 64 MCS: 379 to 224 us), 2^11 x 2^17 slower by 1.24.
+    const int32_t N = team && !pl.persite ? sca::team_rows(W, Y, c->team_parts) : 0;
+    const int32_t words = N * (W > 64 ? 2 : 1);
+    if (N > 0 && (!pl.draw_free || (words == 8 && W >= 64))) {
+        const int64_t rest = n_mcs % sca::kTeamMaxMcs;
+        if ((double)(n_mcs / sca::kTeamMaxMcs) * m.team(sca::kTeamMaxMcs, words) + (rest ? m.team(rest, words) : 0) <
+            (W < 64 ? 0.8 : 0.9) * best) {
+            fuse = false;
+            pl.tile_rows = 0;
+            pl.whole = false;
+            pl.team_rows = N;
+        }
+    }
     return fuse;
 }
 
-StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
+// team: the step may run as a team.
+StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags, bool team)
 {
     StepPlan pl;
     pl.P = classify(p);
@@ -461,7 +511,7 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
     // pass buffer that all their passes need) go by cost.
     if (automatic && may_fuse && c->W <= 512 && band < tall && (c->W < 64 || (c->alt && !pl.persite))) {
         pl.depth = depth;
-        const bool fuse = plan_by_cost(c, n_mcs, pl);
+        const bool fuse = plan_by_cost(c, n_mcs, team, pl);
         set_passes(pl, n_mcs, fuse);
         return pl;
     }
@@ -482,6 +532,45 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
     pl.depth = depth;
     set_passes(pl, n_mcs, may_fuse && n_mcs >= 2 && sca::fused_supported(c->W, c->Y, band, depth, pl.mode, pl.ndraw));
     return pl;
+}
+
+// Memory for teams, from 2^25 sites on (below, tiles are faster) up to what the
+// compute units hold.  A context that gets none goes without.
+void init_team(sca_ctx* c)
+{
+    int cus = 0;
+    if (!c->pinned || c->W < 16 || c->X * c->Y < (1ll << 25) ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
+        return;
+    int parts = sca::kTeamMaxParts;
+    while (parts > cus) parts /= 2;
+    if (parts < 4 || sca::team_rows(c->W, c->Y, parts) == 0) return;
+    uint64_t* ctl = nullptr;
+    if (hipMalloc(&ctl, sizeof(uint64_t) * (size_t)sca::team_words(c->W, parts)) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (sca::launch_team_clear(ctl, c->W, parts, c->stream) != hipSuccess) {
+        (void)hipFree(ctl);
+        return;
+    }
+    team_flags(c)[0] = team_flags(c)[1] = 0;
+    c->team_ctl = ctl;
+    c->team_parts = parts;
+}
+
+hipError_t launch_team_step(sca_ctx* c, const sca::SweepArgs& a, const StepPlan& pl, int64_t n, hipStream_t stream)
+{
+    sca::TeamLaunch L{};
+    L.a = a;
+    L.n = n;
+    L.ctl = c->team_ctl;
+    L.epoch = ++c->team_epoch;
+    L.tag = c->team_tag;
+    L.err = team_flags(c);
+    L.apart = team_flags(c) + 1;
+    c->team_tag += 2u * (uint32_t)n;
+    return sca::launch_team(L, pl.has_q, c->team_parts, pl.team_rows, stream);
 }
 
 sca::SweepArgs sweep_args(const sca_ctx* c, const StepPlan& pl)
@@ -561,6 +650,7 @@ int sca_init(sca_ctx** out, int64_t X, int64_t Y, uint64_t seed, void* slopes_de
         return SCA_EDEVICE;
     }
     c->pinned = g_slots.take();
+    init_team(c);
     *out = c;
     return SCA_OK;
 }
@@ -574,12 +664,23 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
         return SCA_EINVAL;
     if (c->t + n_mcs > (int64_t)UINT32_MAX) return SCA_EINVAL;
     if (n_mcs == 0) return SCA_OK;
-    if (n_mcs != c->plan_n || p != c->plan_p || q != c->plan_q || flags != c->plan_flags) {
-        c->plan = make_plan(c, n_mcs, p, q, flags);
+    if (team_flag(c, 0)) return fail(c);
+    bool team = may_team(c, flags);
+    if (team) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
+            (void)hipGetLastError();
+            team = false;
+        }
+        team = team && capture == hipStreamCaptureStatusNone;
+    }
+    if (n_mcs != c->plan_n || p != c->plan_p || q != c->plan_q || flags != c->plan_flags || team != c->plan_team) {
+        c->plan = make_plan(c, n_mcs, p, q, flags, team);
         c->plan_n = n_mcs;
         c->plan_p = p;
         c->plan_q = q;
         c->plan_flags = flags;
+        c->plan_team = team;
     }
     const StepPlan& pl = c->plan;
     // the blocked passes alternate between S and the caller's pass buffer
@@ -596,6 +697,14 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
                 a.t = (uint32_t)(t0 + i);
                 const hipError_t e = sca::launch_tile(a, pl.mode, pl.has_q, c->S, c->S, tile_shape(c, pl, 0),
                                                       (int32_t)std::min(kWholeMcs, n_mcs - i), st);
+                if (e != hipSuccess) return e;
+            }
+            return hipSuccess;
+        }
+        if (pl.team_rows > 0) {
+            for (int64_t i = 0; i < n_mcs; i += sca::kTeamMaxMcs) {
+                a.t = (uint32_t)(t0 + i);
+                const hipError_t e = launch_team_step(c, a, pl, std::min(sca::kTeamMaxMcs, n_mcs - i), st);
                 if (e != hipSuccess) return e;
             }
             return hipSuccess;
@@ -633,17 +742,18 @@ int sca_plan_step(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned 
     if (!c || !out || n_mcs < 0 || !valid_prob(p) || !valid_prob(q) ||
         (flags & ~(SCA_FORCE_PERSITE | SCA_STEP_GRAPH | SCA_NO_FUSE)))
         return SCA_EINVAL;
-    const StepPlan pl = make_plan(c, n_mcs, p, q, flags);
+    const StepPlan pl = make_plan(c, n_mcs, p, q, flags, may_team(c, flags));
     std::memset(out, 0, sizeof *out);
     out->path = pl.persite ? SCA_PATH_PERSITE : (pl.draw_free ? SCA_PATH_DRAWFREE : SCA_PATH_MASK);
-    out->band = pl.whole ? (int32_t)c->Y : pl.band;
+    out->band = pl.whole ? (int32_t)c->Y : pl.team_rows > 0 ? (int32_t)(c->Y / c->team_parts) : pl.band;
     out->n_pass = pl.n_pass;
     out->depth = pl.n_pass > 0 ? pl.depth : 0;
     out->tail1 = pl.tail1;
     out->tail2 = pl.tail2;
-    out->n_unfused = pl.whole ? 0 : n_mcs - (pl.n_pass * pl.depth + pl.tail1 + pl.tail2);
+    out->n_unfused = pl.whole || pl.team_rows > 0 ? 0 : n_mcs - (pl.n_pass * pl.depth + pl.tail1 + pl.tail2);
     const sca::SweepArgs a = sweep_args(c, pl);
-    if (pl.whole || (pl.n_pass > 0 && pl.tile_rows > 0))
+    if (pl.team_rows > 0) sca::team_kernel_name(a, pl.has_q, pl.team_rows, out->kernel, sizeof out->kernel);
+    else if (pl.whole || (pl.n_pass > 0 && pl.tile_rows > 0))
         sca::tile_kernel_name(a, pl.mode, pl.has_q, pl.tile_rows, out->kernel, sizeof out->kernel);
     else if (pl.n_pass > 0) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.depth, out->kernel, sizeof out->kernel);
     else std::snprintf(out->kernel, sizeof out->kernel, "none");
@@ -748,7 +858,7 @@ int sca_roughness(sca_ctx* c, int64_t out3[3], double* w2)
     DeviceGuard dg(c->device);
     if (!dg.ok) return fail(c);
     const int rc = moments_of(c->S, c->aux, c->X, c->Y, c->W, c->nb, c->ws, c->pinned, c->stream, out3, w2);
-    if (rc == SCA_EDEVICE) return fail(c);
+    if (rc == SCA_EDEVICE || team_flag(c, 0)) return fail(c);
     return rc;
 }
 
@@ -833,7 +943,7 @@ int sca_autocorr(sca_ctx* c, const void* snap_dev, int64_t out4[4], double* c_ts
     int64_t r[7];
     if (sca::launch_moments(c->S, c->aux, snap, snap_h0, c->X, c->Y, c->W, c->nb, c->ws, res, nullptr, c->stream) !=
             hipSuccess ||
-        fetch(c->stream, res, c->pinned != nullptr, r, 7) != hipSuccess)
+        fetch(c->stream, res, c->pinned != nullptr, r, 7) != hipSuccess || team_flag(c, 0))
         return fail(c);
     const __int128 st = join128(r[0], r[1]), sts = join128(r[2], r[3]), ss = join128(r[4], r[5]);
     if (!fits64(st) || !fits64(sts) || !fits64(ss)) return SCA_EOVERFLOW;
@@ -857,7 +967,7 @@ int sca_get_meta(sca_ctx* c, int64_t* t, int64_t* h0)
         int64_t* res = c->pinned ? c->pinned : c->aux;
         if (c->pinned && hipMemcpyAsync(res, c->aux, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream) != hipSuccess)
             return fail(c);
-        if (fetch(c->stream, res, c->pinned != nullptr, h0, 1) != hipSuccess) return fail(c);
+        if (fetch(c->stream, res, c->pinned != nullptr, h0, 1) != hipSuccess || team_flag(c, 0)) return fail(c);
     }
     return SCA_OK;
 }
@@ -891,7 +1001,7 @@ int sca_heights(sca_ctx* c, int64_t y0, int64_t ny, int32_t* out_dev)
     int64_t h0 = 0;
     int64_t* res = c->pinned ? c->pinned : ws_res(c);
     if (sca::launch_column(c->S, c->aux, c->Y, c->W, ws_col(c), res, c->stream) != hipSuccess ||
-        fetch(c->stream, res, c->pinned != nullptr, &h0, 1) != hipSuccess)
+        fetch(c->stream, res, c->pinned != nullptr, &h0, 1) != hipSuccess || team_flag(c, 0))
         return fail(c);
     // |h(x,y) - h(0,0)| <= x + y for any slope field
     if (h0 > INT32_MAX - c->X - c->Y || h0 < INT32_MIN + c->X + c->Y) return SCA_EOVERFLOW;
@@ -907,6 +1017,7 @@ void sca_destroy(sca_ctx* c)
         DeviceGuard dg(c->device);
         (void)hipStreamSynchronize(c->stream);
         (void)hipFree(c->ws);
+        (void)hipFree(c->team_ctl);
         if (c->capture) (void)hipStreamDestroy(c->capture);
     }
     g_slots.give(c->pinned);
@@ -1365,11 +1476,11 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     auto chip_parts = [&](const SlotHost& s, int64_t w, int32_t* rows) {
         const int Y = (int)s.req.Y;
         for (int32_t P = 1; P <= sca::kOnChipMaxParts && P <= b->cu_grid; P *= 2) {
-            const int N = sca::onchip_rows(s.W, Y, P);
+            const int N = sca::team_rows(s.W, Y, P);
             if (N == 0) continue;
             const bool more = b->cfg.order == 0 && w / P > chip_share && N > 2 && 2 * P <= sca::kOnChipMaxParts &&
                               2 * P <= b->cu_grid;
-            if (more && sca::onchip_rows(s.W, Y, 2 * P) > 0) continue;
+            if (more && sca::team_rows(s.W, Y, 2 * P) > 0) continue;
             *rows = N;
             return P;
         }

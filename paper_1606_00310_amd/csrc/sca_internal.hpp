@@ -171,10 +171,43 @@ hipError_t launch_counter_reset(int32_t* counter, int32_t* sync, int32_t n_sync,
 // holds at once (0 if unknown).
 int ensemble_occupancy(int block_threads, int words_per_lane, int lds_bytes, int depth);
 
+// A lattice in the registers of a team of workgroups (team.hpp).
+constexpr int kTeamThreads = 1024;
+constexpr int kTeamMessage = 128;  // 64-bit words per message and word of a lane: two for each of 64 lanes
+
+// Rows per thread (2, 4 or 8; at most eight words) with which `parts` workgroups
+// hold a lattice of Y rows of W words, or 0.
+inline int team_rows(int W, int64_t Y, int parts)
+{
+    if (W > 128 || Y % parts != 0) return 0;
+    const int64_t R = Y / parts;
+    for (int N = 2; N <= (W > 64 ? 4 : 8); N *= 2)
+        if (R % N == 0 && R / N * (W > 64 ? 64 : W) <= kTeamThreads) return N;
+    return 0;
+}
+
+// n <= kTeamMaxMcs MCS of one lattice (bit-mask mode, 16 <= W) in place by `parts`
+// workgroups (4 <= parts <= kTeamMaxParts) of `rows` = team_rows rows per thread.
+// The launches that share `ctl` follow one another on one stream and are not
+// captured: each is given its number.
+constexpr int kTeamMaxParts = 256;
+constexpr int64_t kTeamMaxMcs = 1 << 14;
+struct TeamLaunch {
+    SweepArgs a;     // a.S, a.t: the state and its MCS
+    int64_t n;
+    uint64_t* ctl;   // team_words(W, parts), zero before the first launch
+    uint64_t epoch;  // 1 for the first launch on ctl, 2 for the next, ...
+    uint32_t tag;    // twice the MCS of the launches on ctl so far
+    int32_t* err;    // (host memory) set if a wait ran out of patience
+    int32_t* apart;  // (host memory) set if the team could not form
+};
+int64_t team_words(int32_t W, int parts);
+hipError_t launch_team_clear(uint64_t* ctl, int32_t W, int parts, hipStream_t stream);
+hipError_t launch_team(const TeamLaunch& L, bool has_q, int parts, int rows, hipStream_t stream);
+void team_kernel_name(const SweepArgs& a, bool has_q, int rows, char* out, size_t n);
+
 // Realizations that stay on chip for an epoch (onchip.hip): bit-mask mode, in
-// a team of d.parts workgroups of kOnChipThreads threads with d.bands rows of
-// one word column per thread.
-constexpr int kOnChipThreads = 1024;
+// a team of d.parts workgroups with d.bands = team_rows rows per thread.
 constexpr int kOnChipMaxParts = 8;
 struct OnChipLaunch {
     const BatchDesc* desc;
@@ -191,17 +224,6 @@ int64_t onchip_message_words(int grid);
 // the last has entries.
 hipError_t launch_onchip(const OnChipLaunch& L, int grid, bool teams, hipStream_t stream);
 int onchip_occupancy();
-
-// Rows per thread (2, 4 or 8) with which `parts` workgroups hold a lattice of Y
-// rows of W words, or 0.
-inline int onchip_rows(int W, int Y, int parts)
-{
-    if (W > 64 || Y % parts != 0) return 0;
-    const int R = Y / parts;
-    for (int N = 2; N <= 8; N *= 2)
-        if (R % N == 0 && R / N * W <= kOnChipThreads) return N;
-    return 0;
-}
 
 hipError_t launch_philox_rate(int64_t threads, int32_t calls, uint32_t* sink, hipStream_t stream);
 

@@ -291,8 +291,9 @@ struct NoEdge {
     }
 };
 
-// The rows of one thread and the half-step over them.
-template <int G, int N, int I, XiMode MODE, bool HASQ, Draws DR>
+// The rows of one thread and the half-step over them.  KEEP: draws kept from
+// one half-step to the next wait in LDS instead of registers.
+template <int G, int N, int I, XiMode MODE, bool HASQ, Draws DR, bool KEEP = false>
 struct TileThread {
     static_assert(N % 2 == 0, "the alignment of row i is that of i");
     static_assert(I == 1 || G == 64, "a row of several words per lane fills a wave");
@@ -302,16 +303,14 @@ struct TileThread {
     // come from LDS behind the barrier.
     static constexpr bool PRE = N * I <= 2 && MODE != XiMode::PerSite;
     static constexpr int NX = N >= 8 ? 1 : 2 / I;
-    // The shared last draw of an odd number of draws waits for the odd
-    // half-step in registers, or in LDS (one word per thread and row) where the
-    // rows leave none.
+    // The shared last draw of an odd number of draws waits for the odd half-step.
     static constexpr bool TAIL = DR == Draws::OddTail && MODE == XiMode::Mask;
-    static constexpr bool TAIL_LDS = TAIL && N >= 8;
+    static constexpr bool TAIL_LDS = TAIL && KEEP;
 
     uint64_t x[N][2][I];  // x-slopes by sublattice
     uint64_t y[N][2][I];  // y-slopes; row 0 only within a half-step
     uint64_t tail[TAIL && !TAIL_LDS ? N : 1][I];
-    uint64_t* kept;       // of row 0, blockDim.x words apart (TAIL_LDS)
+    uint64_t* kept;       // word k of row i at (i * I + k) * blockDim.x (TAIL_LDS)
     uint32_t g0;          // canonical index of row 0's word 0 (the rows lie W apart)
     uint32_t W;
     RowLanes rl;
@@ -341,10 +340,10 @@ struct TileThread {
                 // With many rows per thread the products of the word index that
                 // every Philox call starts with are formed anew each time: kept
                 // across the half-steps they take four registers per row.
-                if constexpr (N >= 4) asm volatile("" : "+v"(gg[m]));
+                if constexpr (N * I >= 4) asm volatile("" : "+v"(gg[m]));
                 t[m] = 0;
                 if constexpr (TAIL_LDS) {
-                    if (a.parity == 1) t[m] = kept[row(m0 + m) * (int)blockDim.x];
+                    if (a.parity == 1) t[m] = kept[(row(m0 + m / I) * I + m % I) * (int)blockDim.x];
                 } else if constexpr (TAIL) {
                     t[m] = tail[row(m0 + m / I)][m % I];
                 }
@@ -353,7 +352,7 @@ struct TileThread {
 #pragma unroll
             for (int m = 0; m < NX * I; ++m) {
                 if constexpr (TAIL_LDS) {
-                    if (a.parity == 0) kept[row(m0 + m) * (int)blockDim.x] = t[m];
+                    if (a.parity == 0) kept[(row(m0 + m / I) * I + m % I) * (int)blockDim.x] = t[m];
                 } else if constexpr (TAIL) {
                     tail[row(m0 + m / I)][m % I] = t[m];
                 }
