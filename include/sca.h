@@ -380,6 +380,16 @@ int sca_batch_slot(const sca_batch* b, int32_t slot, sca_slot_info* out);
  * (as sca_roughness).  Synchronizes. */
 int sca_batch_roughness(sca_batch* b, int32_t slot, int64_t out3[3], double* w2);
 
+/* What sca_batch_roughness gives for each of n slots, and their h(0,0), with one
+ * wait for up to 256 of them.  status: SCA_OK or SCA_EOVERFLOW of that slot. */
+typedef struct sca_collected {
+    int64_t moments[3];
+    double w2;
+    int64_t h0;
+    int64_t status;
+} sca_collected;
+int sca_batch_collect(sca_batch* b, const int32_t* slots, int32_t n, sca_collected* out);
+
 /* Frees a slot and its arena space (after the enqueued work that uses it). */
 int sca_batch_release(sca_batch* b, int32_t slot);
 

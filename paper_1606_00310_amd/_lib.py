@@ -63,6 +63,12 @@ class SlotInfo(ctypes.Structure):
                 ("seed", ctypes.c_uint64), ("slopes_dev", ctypes.c_void_p), ("h0_dev", ctypes.c_void_p)]
 
 
+class Collected(ctypes.Structure):
+    """sca_collected: moments and origin height of a slot."""
+    _fields_ = [("moments", ctypes.c_int64 * 3), ("w2", ctypes.c_double), ("h0", ctypes.c_int64),
+                ("status", ctypes.c_int64)]
+
+
 _lib = None
 _vp, _i64, _u64, _u32, _int, _dbl = (ctypes.c_void_p, ctypes.c_int64, ctypes.c_uint64, ctypes.c_uint32,
                                       ctypes.c_int, ctypes.c_double)
@@ -101,6 +107,7 @@ _SIGNATURES = {
     "sca_batch_run_work": ([_vp, _i64, ctypes.POINTER(ctypes.c_int32)], _int),
     "sca_batch_slot": ([_vp, ctypes.c_int32, ctypes.POINTER(SlotInfo)], _int),
     "sca_batch_roughness": ([_vp, ctypes.c_int32, _i64p, _dblp], _int),
+    "sca_batch_collect": ([_vp, ctypes.POINTER(ctypes.c_int32), ctypes.c_int32, ctypes.POINTER(Collected)], _int),
     "sca_batch_release": ([_vp, ctypes.c_int32], _int),
     "sca_batch_destroy": ([_vp], None),
 }

@@ -124,6 +124,20 @@ class Batch:
         L.check(L.lib().sca_batch_roughness(self._b, int(slot), out, ctypes.byref(w2)), "sca_batch_roughness")
         return int(out[0]), int(out[1]), int(out[2]), float(w2.value)
 
+    def collect(self, slots):
+        """Per slot (roughness(slot), h0), with one wait for all; lazily, so
+        that an error of one slot shows when its turn comes."""
+        n = len(slots)
+        out = (L.Collected * max(n, 1))()
+        L.check(L.lib().sca_batch_collect(self._b, (ctypes.c_int32 * max(n, 1))(*slots), n, out), "sca_batch_collect")
+
+        def each():
+            for c in out[:n]:
+                L.check(int(c.status), "sca_batch_collect")
+                yield (c.moments[0], c.moments[1], c.moments[2], c.w2), c.h0
+
+        return each()
+
     def release(self, slot: int):
         L.check(L.lib().sca_batch_release(self._b, int(slot)), "sca_batch_release")
 

@@ -222,6 +222,19 @@ __int128 join128(int64_t lo, int64_t hi) { return (__int128)(((unsigned __int128
 
 bool fits64(__int128 v) { return v >= (__int128)INT64_MIN && v <= (__int128)INT64_MAX; }
 
+// Moments from the sums r; SCA_OK or SCA_EOVERFLOW.
+int moments_from(const int64_t r[7], int64_t X, int64_t Y, int64_t out3[3], double* w2)
+{
+    const __int128 s1 = join128(r[0], r[1]), s2 = join128(r[2], r[3]);
+    if (!fits64(s1) || !fits64(s2)) return SCA_EOVERFLOW;
+    const __int128 N = (__int128)X * Y;
+    out3[0] = (int64_t)N;
+    out3[1] = (int64_t)s1;
+    out3[2] = (int64_t)s2;
+    if (w2) *w2 = (double)(N * s2 - s1 * s1) / ((double)N * (double)N);
+    return SCA_OK;
+}
+
 // Exact moments of a state at S with origin height *h0, using ws (partial
 // sums [3Y], col[Y], res[8]) and, if not nullptr, the result slot `pinned`.
 // *flag, a device word, returns in *flag_out with the result.  Returns SCA_OK,
@@ -236,14 +249,7 @@ int moments_of(const uint64_t* S, const int64_t* h0, int64_t X, int64_t Y, int32
         fetch(stream, res, pinned != nullptr, r, 7) != hipSuccess)
         return SCA_EDEVICE;
     if (flag_out) *flag_out = r[6];
-    const __int128 s1 = join128(r[0], r[1]), s2 = join128(r[2], r[3]);
-    if (!fits64(s1) || !fits64(s2)) return SCA_EOVERFLOW;
-    const __int128 N = (__int128)X * Y;
-    out3[0] = (int64_t)N;
-    out3[1] = (int64_t)s1;
-    out3[2] = (int64_t)s2;
-    if (w2) *w2 = (double)(N * s2 - s1 * s1) / ((double)N * (double)N);
-    return SCA_OK;
+    return moments_from(r, X, Y, out3, w2);
 }
 
 // Runs `enqueue` on a private capture stream into a hipGraph, then launches
@@ -1143,7 +1149,9 @@ struct sca_batch {
     int32_t* d_order = nullptr;
     int32_t* d_counters = nullptr;  // kCounters words, see below
     int64_t* d_ws = nullptr;        // moments workspace for Y up to 131072
-    int64_t* pinned = nullptr;      // result slot of sca_batch_roughness, or nullptr
+    // sca_batch_collect: kCollect result slots of 8 words (the first one is also
+    // sca_batch_roughness's), and behind them as many items; pinned
+    int64_t* results = nullptr;
     // pinned staging
     sca::BatchDesc* h_desc = nullptr;
     int32_t* h_order = nullptr;
@@ -1166,13 +1174,13 @@ namespace {
 // and queues (the copy zeroes the queues).
 enum { kItems = 0, kQueue = 1, kOnChipCount = 4, kOnChipQueue = 8, kCounters = 12 };
 
+constexpr int32_t kCollect = 256;  // realizations per launch and wait of sca_batch_collect
+
 int bfail(sca_batch* b)
 {
     if (b) b->failed = true;
     return SCA_EDEVICE;
 }
-
-
 
 void batch_free(sca_batch* b)
 {
@@ -1195,7 +1203,7 @@ void batch_free(sca_batch* b)
     (void)hipHostFree(b->h_desc);
     (void)hipHostFree(b->h_order);
     (void)hipHostFree(b->h_count);
-    g_slots.give(b->pinned);
+    (void)hipHostFree(b->results);
     delete b;
 }
 
@@ -1300,6 +1308,8 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
         hipMalloc(&b->d_sync, sizeof(int32_t) * (size_t)b->num_cus * 8) != hipSuccess ||
         hipMalloc(&b->d_err, sizeof(int32_t)) != hipSuccess ||
         hipHostMalloc(&b->h_err, sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(&b->results, kCollect * (8 * sizeof(int64_t) + sizeof(sca::MomentsItem)), hipHostMallocDefault) !=
+            hipSuccess ||
         hipEventCreateWithFlags(&b->err_copied, hipEventDisableTiming) != hipSuccess ||
         hipMemsetAsync(b->d_err, 0, sizeof(int32_t), b->stream) != hipSuccess) {
         (void)hipGetLastError();
@@ -1308,7 +1318,6 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     }
     std::memset(b->h_desc, 0, nd);
     *b->h_err = 0;
-    b->pinned = g_slots.take();
     b->cu_grid = sca::onchip_occupancy() > 0 ? b->num_cus : 0;
     *out = b;
     return SCA_OK;
@@ -1665,10 +1674,47 @@ int sca_batch_roughness(sca_batch* b, int32_t slot, int64_t out3[3], double* w2)
     const SlotHost& s = b->slots[(size_t)slot];
     // d_err comes with the sums: a barrier that gave up in an earlier launch shows there
     int64_t err = 0;
-    const int rc = moments_of(s.desc.S, s.desc.h0, s.req.X, s.req.Y, s.W, s.nb, b->d_ws, b->pinned, b->stream, out3, w2,
+    const int rc = moments_of(s.desc.S, s.desc.h0, s.req.X, s.req.Y, s.W, s.nb, b->d_ws, b->results, b->stream, out3, w2,
                               b->d_err, &err);
     if (rc == SCA_EDEVICE || err) return bfail(b);
     return rc;
+}
+
+int sca_batch_collect(sca_batch* b, const int32_t* slots, int32_t n, sca_collected* out)
+{
+    if (!b || n < 0 || (n > 0 && (!slots || !out))) return SCA_EINVAL;
+    for (int32_t i = 0; i < n; ++i)
+        if (slots[i] < 0 || slots[i] >= b->max_slots || !b->slots[(size_t)slots[i]].used) return SCA_EINVAL;
+    if (b->failed) return SCA_ESTATE;
+    DeviceGuard dg(b->device);
+    if (!dg.ok) return bfail(b);
+    auto* const items = reinterpret_cast<sca::MomentsItem*>(b->results + 8 * kCollect);
+    for (int32_t i0 = 0; i0 < n; i0 += kCollect) {
+        const int32_t m = std::min(n - i0, kCollect);
+        int32_t n_items = 0;
+        for (int32_t i = 0; i < m; ++i) {
+            const SlotHost& s = b->slots[(size_t)slots[i0 + i]];
+            int64_t* const res = b->results + 8 * i;
+            if (sca::moments_in_one_block(s.req.Y, s.W))
+                items[n_items++] = sca::MomentsItem{s.desc.S, s.desc.h0, res, (int32_t)s.req.Y, s.W, s.nb};
+            else if (sca::launch_moments(s.desc.S, s.desc.h0, nullptr, nullptr, s.req.X, s.req.Y, s.W, s.nb, b->d_ws, res,
+                                         b->d_err, b->stream) != hipSuccess)
+                return bfail(b);
+        }
+        if (sca::launch_moments_many(items, n_items, b->d_err, b->stream) != hipSuccess ||
+            hipStreamSynchronize(b->stream) != hipSuccess)
+            return bfail(b);
+        for (int32_t i = 0; i < m; ++i) {
+            const SlotHost& s = b->slots[(size_t)slots[i0 + i]];
+            int64_t r[7];
+            for (int k = 0; k < 7; ++k) r[k] = reinterpret_cast<const volatile int64_t*>(b->results)[8 * i + k];
+            if (r[6]) return bfail(b);
+            sca_collected& o = out[i0 + i];
+            o.status = moments_from(r, s.req.X, s.req.Y, o.moments, &o.w2);
+            o.h0 = r[4];
+        }
+    }
+    return SCA_OK;
 }
 
 int sca_batch_release(sca_batch* b, int32_t slot)

@@ -57,12 +57,23 @@ hipError_t launch_flat_init_many(const FlatItem* items_dev, int32_t n, hipStream
 
 // Exact sums of the height field into res[7] (device memory or pinned host
 // memory): {S1 lo,hi, S2 lo,hi, S3 lo,hi, *flag or 0}, 128 bits each, with
-// S = {sum h, sum h^2, 0} or, with a snapshot, {sum h_t, sum h_t h_s, sum h_s}.
+// S = {sum h, sum h^2, h(0,0)} or, with a snapshot, {sum h_t, sum h_t h_s, sum h_s}.
 // partials: kMomentsPartial int64 per block of rows, at most 3 Y in all.
 constexpr int kMomentsPartial = 5;
 hipError_t launch_moments(const uint64_t* S, const int64_t* h0, const uint64_t* snap, const int64_t* snap_h0,
                           int64_t X, int64_t Y, int32_t W, int32_t nb, int64_t* partials, int64_t* res,
                           const int32_t* flag, hipStream_t stream);
+
+// The sums of n lattices whose moments take one block each (res[7] of each as
+// above); items in device memory or pinned host memory.
+struct MomentsItem {
+    const uint64_t* S;
+    const int64_t* h0;
+    int64_t* res;
+    int32_t Y, W, nb;
+};
+bool moments_in_one_block(int64_t Y, int32_t W);
+hipError_t launch_moments_many(const MomentsItem* items, int32_t n, const int32_t* flag, hipStream_t stream);
 
 // Heights h(0,y) of column 0 into col[Y], h(0,0) into *h0_out.
 hipError_t launch_column(const uint64_t* S, const int64_t* h0, int64_t Y, int32_t W, int64_t* col, int64_t* h0_out,

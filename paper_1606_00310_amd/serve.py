@@ -74,6 +74,22 @@ class BatchBackend:
             out["slopes"] = S.clone()
         return out
 
+    def collect_many(self, slots):
+        """collect for each of the slots, with one wait for all their moments."""
+        if type(self).collect is not BatchBackend.collect:  # a subclass collects otherwise
+            yield from map(self.collect, slots)
+            return
+        import torch
+
+        stream = torch.cuda.current_stream(self.batch.device)
+        for slot, (moments, h0) in zip(slots, self.batch.collect(slots)):
+            out = {"moments": moments, "h0": h0}
+            if self.keep_states:
+                out["slopes"] = self.batch.state(slot)[0].clone()
+                if stream != self.batch.stream:  # the slot's memory may be given away from here on
+                    self.batch.stream.wait_stream(stream)
+            yield out
+
     def release(self, slot):
         self.batch.release(slot)
 
@@ -117,16 +133,21 @@ class Server:
                 self.slot_owner[s] = (req.rid, i)
 
     def _retire(self):
-        for slot in list(self.slot_owner):
-            if self.backend.finished(slot):
-                rid, i = self.slot_owner.pop(slot)
-                req = self.running[rid]
-                req.results[i] = self.backend.collect(slot)
-                self.backend.release(slot)
-                if all(r is not None for r in req.results):
-                    req.done = self.now()
-                    self.completed.append(req)
-                    del self.running[rid]
+        finished = [slot for slot in self.slot_owner if self.backend.finished(slot)]
+        if not finished:
+            return
+        # a backend may collect many at once
+        many = getattr(self.backend, "collect_many", None)
+        results = many(finished) if many else map(self.backend.collect, finished)
+        for slot, result in zip(finished, results):
+            rid, i = self.slot_owner.pop(slot)
+            req = self.running[rid]
+            req.results[i] = result
+            self.backend.release(slot)
+            if all(r is not None for r in req.results):
+                req.done = self.now()
+                self.completed.append(req)
+                del self.running[rid]
 
     def step(self) -> int:
         """Admit, run one epoch, retire.  Returns the realizations advanced."""

@@ -106,3 +106,25 @@ def test_many_contexts(sca):
         lat.close()
     lat = sca.Lattice(8, 8, seed=5)
     assert lat.roughness()[0] == 64
+
+
+def test_collect_many(sca):
+    """Moments and origin heights of more realizations than one launch takes,
+    of one block and of several: as from one at a time."""
+    from paper_1606_00310_amd import batch
+
+    sizes = [(4, 4), (8, 64), (64, 32), (128, 128), (256, 512), (1024, 64), (4096, 4), (8192, 8), (8192, 4),
+             (512, 2048), (8192, 64), (4, 8192)]
+    reals = [batch.Realization(*sizes[i % len(sizes)], 0.75, 0.25 * (i % 2), 5 + i % 7, 1000 + i) for i in range(300)]
+    b = batch.Batch(max_slots=len(reals), arena_bytes=sum(batch.state_bytes(r.X, r.Y) for r in reals))
+    slots = b.admit(reals)
+    while b.run(100):
+        pass
+    got = list(b.collect(slots[::-1]))[::-1]
+    for s, (moments, h0) in zip(slots, got):
+        assert moments == b.roughness(s) and h0 == int(b.state(s)[1][0])
+    assert list(b.collect([])) == []
+    b.release(slots[3])
+    with pytest.raises(Exception):
+        b.collect(slots[:5])
+    assert next(b.collect(slots[:3])) == got[0]
