@@ -1158,7 +1158,7 @@ struct sca_batch {
     int32_t* h_count = nullptr;
     hipEvent_t staged = nullptr;
     bool staged_pending = false;
-    // flat initialisation of admitted realizations: one launch per admission
+    // flat initialisation of many admitted realizations
     sca::FlatItem* h_flat = nullptr;  // pinned staging
     sca::FlatItem* d_flat = nullptr;
     hipEvent_t flat_staged = nullptr;
@@ -1373,9 +1373,15 @@ int sca_batch_admit(sca_batch* b, const sca_req* reqs, int32_t n, int32_t* slots
     }
     DeviceGuard dg(b->device);
     if (!dg.ok) return bfail(b);
-    // the flat-init staging is free once the previous admission's copy has run
-    if (b->flat_pending && hipEventSynchronize(b->flat_staged) != hipSuccess) return bfail(b);
-    b->flat_pending = false;
+    // few states go as an argument of their launch, many through a staged table,
+    // which is free once the previous table's copy has run
+    sca::FlatItem few[sca::kFlatFew];
+    sca::FlatItem* flat = few;
+    if (n > sca::kFlatFew) {
+        if (b->flat_pending && hipEventSynchronize(b->flat_staged) != hipSuccess) return bfail(b);
+        b->flat_pending = false;
+        flat = b->h_flat;
+    }
     int32_t n_flat = 0;
     for (int32_t i = 0; i < n; ++i) {
         const sca_req& r = reqs[i];
@@ -1413,16 +1419,17 @@ int sca_batch_admit(sca_batch* b, const sca_req* reqs, int32_t n, int32_t* slots
             d.dig_q = Q.digits;
             d.ndraw = P.n > Q.n ? P.n : Q.n;
         }
-        // states of up to 2^20 words share one launch (one workgroup per
-        // state); larger ones get a launch of their own
+        // states of up to 2^20 words share one launch; larger ones get a launch of their own
         if (4 * d.plane <= ((int64_t)1 << 20)) {
-            b->h_flat[n_flat++] = sca::flat_item(d.S, r.Y, s.W, s.nb, d.h0);
+            flat[n_flat++] = sca::flat_item(d.S, r.Y, s.W, s.nb, d.h0);
         } else if (sca::launch_flat_init(d.S, r.Y, s.W, s.nb, d.h0, b->stream) != hipSuccess) {
             return bfail(b);
         }
         slots_out[i] = slot;
     }
-    if (n_flat > 0) {
+    if (flat == few) {
+        if (sca::launch_flat_init_few(few, n_flat, b->stream) != hipSuccess) return bfail(b);
+    } else if (n_flat > 0) {
         if (hipMemcpyAsync(b->d_flat, b->h_flat, sizeof(sca::FlatItem) * (size_t)n_flat, hipMemcpyHostToDevice,
                            b->stream) != hipSuccess ||
             hipEventRecord(b->flat_staged, b->stream) != hipSuccess ||

@@ -39,18 +39,27 @@ __global__ void flat_init_kernel(uint64_t* S, int64_t plane, uint64_t valid, int
 // of an ensemble issues one launch instead of one per realization).  With one
 // workgroup per item the largest, 1 MiB, set the time: 61 us for 512 of 2^6 to
 // 2^11 squared, 30 us with eight.
+__device__ __forceinline__ void flat_item_init(const FlatItem& f)
+{
+    const int64_t words = 4 * f.plane;
+    for (int64_t i = (int64_t)blockIdx.y * kBlock + threadIdx.x; i < words; i += (int64_t)gridDim.y * kBlock) {
+        const int parity = (int)((i / f.plane) & 1);  // arrays ordered S[d][parity]
+        f.S[i] = parity ? f.valid : 0ull;
+    }
+    if (blockIdx.y == 0 && threadIdx.x == 0) *f.h0 = 0;
+}
+
 __global__ __launch_bounds__(kBlock) void flat_init_many_kernel(const FlatItem* items, int32_t n)
 {
-    for (int32_t it = blockIdx.x; it < n; it += gridDim.x) {
-        const FlatItem f = items[it];
-        const int64_t words = 4 * f.plane;
-        for (int64_t i = (int64_t)blockIdx.y * kBlock + threadIdx.x; i < words; i += (int64_t)gridDim.y * kBlock) {
-            const int parity = (int)((i / f.plane) & 1);  // arrays ordered S[d][parity]
-            f.S[i] = parity ? f.valid : 0ull;
-        }
-        if (blockIdx.y == 0 && threadIdx.x == 0) *f.h0 = 0;
-    }
+    for (int32_t it = blockIdx.x; it < n; it += gridDim.x) flat_item_init(items[it]);
 }
+
+// Up to 32 items as an argument: no table to copy first, which takes a small
+// admission 4 us of 12.
+struct FlatFew {
+    FlatItem items[kFlatFew];
+};
+__global__ __launch_bounds__(kBlock) void flat_init_few_kernel(FlatFew f) { flat_item_init(f.items[blockIdx.x]); }
 
 // ---------------------------------------------------------------- sums of one word pair
 // Eight nibbles 1 and the nibbles 1..8.
@@ -412,7 +421,7 @@ __global__ __launch_bounds__(kSumBlock) void moments_kernel(const uint64_t* S, c
 
 // The moments of many small lattices, one block each: a launch and a wait for
 // each of them is what retiring an ensemble's realizations spends its time on
-// (96 of 64 to 512 sites wide, served and collected: 5.4 ms, 2.6 ms with these).
+// (96 of 64 to 512 sites wide, served and collected: 5.4 to 2.6 ms).
 __global__ __launch_bounds__(kSumBlock) void moments_many_kernel(const MomentsItem* items, const int32_t* flag)
 {
     __shared__ MomentsShared<false> sh;
@@ -610,6 +619,16 @@ hipError_t launch_flat_init_many(const FlatItem* items_dev, int32_t n, hipStream
     if (n <= 0) return hipSuccess;
     const int32_t grid = n < 4096 ? n : 4096;
     hipLaunchKernelGGL(flat_init_many_kernel, dim3((unsigned)grid, 8), dim3(kBlock), 0, stream, items_dev, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_flat_init_few(const FlatItem* items_host, int32_t n, hipStream_t stream)
+{
+    if (n <= 0) return hipSuccess;
+    if (n > kFlatFew) return hipErrorInvalidValue;
+    FlatFew f{};
+    for (int32_t i = 0; i < n; ++i) f.items[i] = items_host[i];
+    hipLaunchKernelGGL(flat_init_few_kernel, dim3((unsigned)n, 8), dim3(kBlock), 0, stream, f);
     return hipGetLastError();
 }
 

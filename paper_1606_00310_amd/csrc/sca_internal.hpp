@@ -54,6 +54,8 @@ struct FlatItem {
 };
 FlatItem flat_item(uint64_t* S, int64_t Y, int32_t W, int32_t nb, int64_t* h0);
 hipError_t launch_flat_init_many(const FlatItem* items_dev, int32_t n, hipStream_t stream);
+constexpr int32_t kFlatFew = 32;  // at most 1 KiB of arguments
+hipError_t launch_flat_init_few(const FlatItem* items_host, int32_t n, hipStream_t stream);
 
 // Exact sums of the height field into res[7] (device memory or pinned host
 // memory): {S1 lo,hi, S2 lo,hi, S3 lo,hi, *flag or 0}, 128 bits each, with

@@ -137,3 +137,20 @@ def test_two_batches_on_two_streams(sca):
     torch.cuda.synchronize()
     for (b, slots), reals in zip(batches, sets):
         check_solo(sca, b, slots, reals)
+
+
+@pytest.mark.parametrize("n", [1, 32, 33])
+def test_admission_initialises(sca, n):
+    """Few states (launch argument) and many (staged table) start flat, whatever
+    the arena held, one above 2^20 words among them."""
+    from paper_1606_00310_amd import batch
+
+    sizes = [(4, 4), (64, 64), (1024, 256), (8, 2048), (2048, 32768)]
+    reals = [batch.Realization(*sizes[(i + 3 * (n == 1)) % len(sizes)], 0.5, 0.0, 3, i) for i in range(n)]
+    b = batch.Batch(max_slots=n, arena_bytes=sum(batch.state_bytes(r.X, r.Y) for r in reals))
+    b.arena.fill_(-1)
+    for r, slot in zip(reals, b.admit(reals)):
+        S, h0 = b.state(slot)
+        W, nb = max(1, r.X // 128), min(64, r.X // 2)
+        assert S.shape == (2, 2, r.Y, W) and int(h0[0]) == 0
+        assert not S[:, 0].any() and bool((S[:, 1] == ((1 << nb) - 1 if nb < 64 else -1)).all())
