@@ -288,6 +288,8 @@ constexpr int64_t kWholeMcs = 1 << 14;
 //    takes V N/2 (4.7 + 0.44 w) ns, from one wave (p = 1: 0.13 us, p = 1/2:
 //    0.24 us, p = 3/4, q = 1/4: 0.40 us, all latency) to sixteen (0.28, 0.58 and
 //    1.0 us, all vector issue); a launch adds 2.6 us and 0.2 us per MB moved;
+//  - with its words formed ahead, V (2.5 + 0.58 w) ns, and the first ones take
+//    0.4 us and 5 V ns per launch;
 //  - a half-step of a per-site tile takes 0.5 us and 5.8 ns (6.6 ns with
 //    removals) for every word a CU draws for; unfused it takes 3.7 us, or the
 //    vector issue of the chip, 24 us per 2^20 words;
@@ -316,6 +318,15 @@ struct CostModel {
           mb(32e-6 * (double)c->Y * c->W), Y(c->Y), W(c->W), has_q(pl.has_q), draw_free(pl.draw_free), persite(pl.persite)
     {
     }
+    // Whether `tiles` tiles of `rows` rows, two per thread, form the words of n
+    // MCS ahead: with up to five waves of rows on a CU (with four a half-step gets
+    // shorter by a sixth, with eight by nothing), and from three MCS on (the
+    // first one's words are not ahead).
+    bool ahead(int32_t tiles, int32_t rows, int32_t n) const
+    {
+        const int64_t waves = ((int64_t)rows / 2 * W + 63) / 64 * ((tiles + 255) / 256);
+        return !persite && !draw_free && n > 2 && waves <= 5 && sca::tile_ahead(W, sca::TileShape{2, rows, 0, 0});
+    }
     double team(int64_t n, int32_t words) const
     {
         return 6 + 0.4 * mb + 2.0 * (double)n * std::max(1.27, 0.00825 * V * words + 0.12);
@@ -331,8 +342,11 @@ struct CostModel {
     double whole(int64_t n) const
     {
         if (persite) return 2.6 + 2.0 * (double)n * (0.5 + draw((double)Y * W));
-        return 2.6 + 10 * mb + 2.0 * (double)n * half((double)((Y / 2 * W + 63) / 64), 2);
+        const double waves = (double)((Y / 2 * W + 63) / 64);
+        return 2.6 + 10 * mb + 2.0 * (double)n * (ahead(1, (int32_t)Y, (int32_t)n) ? half_ahead(waves) : half(waves, 2));
     }
+    // The same with the words formed ahead (tile.hpp).
+    double half_ahead(double waves) const { return V * (0.0025 + 0.00058 * waves); }
     double tile(int32_t N, int32_t b, int32_t d) const
     {
         const int I = W > 64 ? W / 64 : 1;
@@ -342,6 +356,9 @@ struct CostModel {
             return 2.6 + 2 * d * (0.5 * (double)((per_cu + 1) / 2) + draw((double)per_cu * (b + 2 * d) * W)) +
                    0.2 * mb * (2 + 4.0 * d / b);
         // workgroups a CU holds: of the two-row kernels by threads, of the others by registers
+        if (N == 2 && ahead((int32_t)(Y / b), b + 4 * d, d))
+            return 3.0 + 0.005 * V + 2 * d * half_ahead(threads / 64 * (double)(b + 2 * d) / (b + 4 * d) * (double)per_cu) +
+                   0.2 * mb * (2 + 4.0 * d / b);
         const int64_t fit = std::max<int64_t>(1, (N == 2 ? 2048 : 1024) / threads);
         const int64_t rounds = (per_cu + fit - 1) / fit;
         const double busy = threads / 64 * (double)(b + 2 * d) / (b + 4 * d) * (double)std::min(per_cu, fit);
@@ -386,12 +403,19 @@ bool tile_fits(int32_t W, int64_t Y, int32_t N, int32_t b, int32_t d, bool persi
            (b + 2 * tile_halo(N, d)) / N * (W / I) <= (I == 1 ? 1024 : 768);
 }
 
-// The tile of a pass of d MCS.
+// The tile of a pass of d MCS, and the mode of its acceptance words.
 sca::TileShape tile_shape(const sca_ctx* c, const StepPlan& pl, int32_t d)
 {
     if (pl.whole) return sca::TileShape{pl.tile_rows, (int32_t)c->Y, (int32_t)c->Y, 0};
     const int32_t halo = tile_halo(pl.tile_rows, d);
     return sca::TileShape{pl.tile_rows, pl.band + 2 * halo, pl.band, halo};
+}
+
+sca::XiMode tile_mode(const sca_ctx* c, const StepPlan& pl, const sca::TileShape& s, int64_t n_mcs)
+{
+    const bool ahead = s.rows_per_thread == 2 && CostModel(c, pl).ahead((int32_t)(c->Y / s.band), s.rows,
+                                                                        (int32_t)std::min<int64_t>(n_mcs, 3));
+    return ahead ? sca::XiMode::Ahead : pl.mode;
 }
 
 // The passes of n MCS at depth d: an even number of whole ones, and two for
@@ -701,8 +725,9 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
         if (pl.whole) {
             for (int64_t i = 0; i < n_mcs; i += kWholeMcs) {
                 a.t = (uint32_t)(t0 + i);
-                const hipError_t e = sca::launch_tile(a, pl.mode, pl.has_q, c->S, c->S, tile_shape(c, pl, 0),
-                                                      (int32_t)std::min(kWholeMcs, n_mcs - i), st);
+                const sca::TileShape s = tile_shape(c, pl, 0);
+                const int64_t n = std::min(kWholeMcs, n_mcs - i);
+                const hipError_t e = sca::launch_tile(a, tile_mode(c, pl, s, n), pl.has_q, c->S, c->S, s, (int32_t)n, st);
                 if (e != hipSuccess) return e;
             }
             return hipSuccess;
@@ -722,9 +747,13 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
             const bool fwd = (i & 1) == 0;
             const uint64_t* src = fwd ? c->S : c->alt;
             uint64_t* dst = fwd ? c->alt : c->S;
-            const hipError_t e =
-                pl.tile_rows > 0 ? sca::launch_tile(a, pl.mode, pl.has_q, src, dst, tile_shape(c, pl, d), d, st)
-                                 : sca::launch_mcs_fused(a, pl.mode, pl.has_q, src, dst, pl.band, d, st);
+            hipError_t e;
+            if (pl.tile_rows > 0) {
+                const sca::TileShape s = tile_shape(c, pl, d);
+                e = sca::launch_tile(a, tile_mode(c, pl, s, d), pl.has_q, src, dst, s, d, st);
+            } else {
+                e = sca::launch_mcs_fused(a, pl.mode, pl.has_q, src, dst, pl.band, d, st);
+            }
             if (e != hipSuccess) return e;
         }
         for (int64_t i = n_fused; i < n_mcs; ++i) {
@@ -760,11 +789,13 @@ int sca_plan_step(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned 
     const sca::SweepArgs a = sweep_args(c, pl);
     if (pl.team_rows > 0) sca::team_kernel_name(a, pl.has_q, pl.team_rows, out->kernel, sizeof out->kernel);
     else if (pl.whole || (pl.n_pass > 0 && pl.tile_rows > 0))
-        sca::tile_kernel_name(a, pl.mode, pl.has_q, pl.tile_rows, out->kernel, sizeof out->kernel);
+        sca::tile_kernel_name(a, tile_mode(c, pl, tile_shape(c, pl, pl.depth), pl.whole ? n_mcs : pl.depth), pl.has_q,
+                              pl.tile_rows, out->kernel, sizeof out->kernel);
     else if (pl.n_pass > 0) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.depth, out->kernel, sizeof out->kernel);
     else std::snprintf(out->kernel, sizeof out->kernel, "none");
     if (pl.tail1 && pl.tile_rows > 0)
-        sca::tile_kernel_name(a, pl.mode, pl.has_q, pl.tile_rows, out->tail_kernel, sizeof out->tail_kernel);
+        sca::tile_kernel_name(a, tile_mode(c, pl, tile_shape(c, pl, pl.tail1), pl.tail1), pl.has_q, pl.tile_rows,
+                              out->tail_kernel, sizeof out->tail_kernel);
     else if (pl.tail1) sca::fused_kernel_name(a, pl.mode, pl.has_q, pl.tail1, out->tail_kernel, sizeof out->tail_kernel);
     else std::snprintf(out->tail_kernel, sizeof out->tail_kernel, "none");
     sca::halfstep_kernel_name(c->W, pl.mode, pl.has_q, out->halfstep_kernel, sizeof out->halfstep_kernel);

@@ -30,13 +30,19 @@ void halfstep_kernel_name(int32_t W, XiMode mode, bool has_q, char* out, size_t 
 // the `band` rows behind the first `halo` are written; halo = 0: the tile is
 // the whole lattice (rows = band = Y), in place and for any number of MCS.
 // Otherwise halo >= 2 n_mcs, src and dst are different states and the bands
-// partition Y.
+// partition Y.  In mode Ahead, for tiles that tile_ahead allows, waves of their
+// own form the words of mode Mask.
 struct TileShape {
     int32_t rows_per_thread = 0;  // 0: no tile serves the lattice
     int32_t rows = 0, band = 0, halo = 0;
 };
 hipError_t launch_tile(const SweepArgs& a, XiMode mode, bool has_q, const uint64_t* src, uint64_t* dst,
                        const TileShape& s, int32_t n_mcs, hipStream_t stream);
+
+inline bool tile_ahead(int32_t W, const TileShape& s)
+{
+    return s.rows_per_thread == 2 && W <= 64 && (s.rows / 2 * W + 63) / 64 * 64 + (s.rows * W + 63) / 64 * 64 <= 1024;
+}
 
 void tile_kernel_name(const SweepArgs& a, XiMode mode, bool has_q, int32_t rows_per_thread, char* out, size_t n);
 

@@ -11,6 +11,7 @@ enum class XiMode : int {
     PerSite = 1,  // one 32-bit uniform per site against floor(r*2^32) (Sec. II-B)
     Inject = 2,   // read from caller arrays (test hook)
     Fixed = 3,    // p, q in {0, 1}: xi is all ones or zero, no draws
+    Ahead = 4,    // Mask, by waves of their own one MCS ahead (tile.hpp)
 };
 
 // Everything a half-step launch needs; passed by value as the kernel argument.

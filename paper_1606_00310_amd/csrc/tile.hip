@@ -17,6 +17,7 @@ struct TileLaunch {
     int32_t band;         // of these, the rows written: tile rows halo .. halo+band-1
     int32_t halo;         // 0: the tile is the whole lattice
     int32_t n;            // MCS
+    int32_t threads;      // ahead mode: threads that hold rows, whole waves
 };
 
 // Threads of a workgroup at most: with two words per lane the rows take more
@@ -29,7 +30,8 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
 {
     extern __shared__ uint64_t ly[];  // [sublattice][word i][thread]
     const SweepArgs& a = L.a;
-    const int T = (int)blockDim.x;  // rows / N groups of G lanes, rounded up to whole waves
+    // rows / N groups of G lanes, rounded up to whole waves
+    const int T = MODE == XiMode::Ahead ? L.threads : (int)blockDim.x;
     constexpr int L2G = G == 0 ? 0 : __builtin_ctz(G == 0 ? 1u : (unsigned)G);  // log2 of the lanes per row
     constexpr int GL = 1 << L2G;
     const int groups = L.rows / N;
@@ -69,10 +71,20 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
         th.ps = PerSiteTile{ly + 2 * T, L.rows << L2G, L2G, used, (int)blockIdx.x * L.band - L.halo, ymask, HASQ};
         th.xrow = active ? (r0 << L2G) + gl : 0;
     }
+    if constexpr (MODE == XiMode::Ahead) {
+        th.ahead = AheadTile{ly + 2 * T, L.rows << L2G, L2G, (int)blockIdx.x * L.band - L.halo, ymask, HASQ ? 1 : 0};
+        th.xrow = active ? (r0 << L2G) + gl : 0;
+        for (int w = tid; w < th.ahead.words; w += (int)blockDim.x) {
+            uint64_t tail = 0;
+            th.ahead.template generate<0, HASQ, DR>(a, w, tail);
+            th.ahead.template generate<1, HASQ, DR>(a, w, tail);
+        }
+    }
+    if (MODE != XiMode::Ahead || tid < T)
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int k = 0; k < I; ++k) ly[(p * I + k) * T + tid] = th.y[0][p][k];
+            for (int k = 0; k < I; ++k) ly[(p * I + k) * T + tid] = th.y[0][p][k];
 
     // tile rows of this wave, and the rows that half-step h has to get right
     const int w0 = __builtin_amdgcn_readfirstlane(tid);
@@ -82,11 +94,37 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
     const int shrink = L.halo > 0 ? 1 : 0;
     SweepArgs ah = a;
     NoEdge edge;
+    // one wave of rows orders its half-steps by itself and meets the others once
+    // per MCS
+    const bool alone = MODE == XiMode::Ahead && T == 64;
+    if (MODE == XiMode::Ahead && w0 >= T) {
+        if constexpr (MODE == XiMode::Ahead) {
+            // a thread forms a word for both half-steps, or the second set of
+            // waves those of the odd ones
+            const int per_set = (th.ahead.words + 63) / 64 * 64;
+            const bool split = T + per_set < (int)blockDim.x, second = w0 - T >= per_set;
+            const int w = tid - T - (second ? per_set : 0);
+            for (int m = 0; m < L.n; ++m) {
+                ++ah.t;
+                lo += 2 * shrink;
+                hi -= 2 * shrink;
+                const bool mine = w >= lo << L2G && w < (hi + 1) << L2G && m + 1 < L.n;
+                uint64_t tail = 0;
+                __syncthreads();
+                if (mine && !second) th.ahead.template generate<0, HASQ, DR>(ah, w, tail);
+                if (!alone) __syncthreads();
+                if (mine && !split) th.ahead.template generate<1, HASQ, DR>(ah, w, tail);
+                if (mine && second) th.ahead.template generate<1, HASQ, Draws::Any>(ah, w, tail);
+            }
+        }
+        __syncthreads();
+        return;
+    }
     for (int m = 0; m < L.n; ++m) {
         th.template halfstep<0>(ah, ly, lo, hi, whi < lo || wlo > hi, edge);
         lo += shrink;
         hi -= shrink;
-        th.template halfstep<1>(ah, ly, lo, hi, whi < lo || wlo > hi, edge);
+        th.template halfstep<1>(ah, ly, lo, hi, whi < lo || wlo > hi, edge, alone);
         lo += shrink;
         hi -= shrink;
         ++ah.t;
@@ -113,17 +151,27 @@ __global__ __launch_bounds__(kTileThreads<I>) void tile_kernel(TileLaunch L)
 }
 
 template <int G, int N, int I, XiMode MODE, bool HASQ, Draws DR>
-hipError_t launch(const TileLaunch& L, hipStream_t stream)
+hipError_t launch(const TileLaunch& L0, hipStream_t stream)
 {
-    int threads = (L.rows / N * (G == 0 ? 1 : G) + 63) / 64 * 64;
+    int threads = (L0.rows / N * (G == 0 ? 1 : G) + 63) / 64 * 64;
     size_t lds = 0;
     if (MODE == XiMode::PerSite) {
         // helpers for the acceptance words: a thread for each byte of the rows a
         // half-step needs on average
-        const int words = L.rows * (G == 0 ? 1 : G);
-        const int bytes = (L.rows - L.halo) * (G == 0 ? 1 : G) * 8;
+        const int words = L0.rows * (G == 0 ? 1 : G);
+        const int bytes = (L0.rows - L0.halo) * (G == 0 ? 1 : G) * 8;
         threads = std::max(threads, std::min(1024, (bytes + 63) / 64 * 64));
         lds = (size_t)(HASQ ? 4 : 2) * words * sizeof(uint64_t);
+    }
+    TileLaunch L = L0;
+    if (MODE == XiMode::Ahead) {
+        // A thread for each word; two for rows of one wave, which do not hold up
+        // the second set within an MCS, unless p and q have a single digit, whose
+        // one draw serves both half-steps.
+        const int words = L.rows * (G == 0 ? 1 : G);
+        L.threads = threads;
+        lds = (size_t)(HASQ ? 8 : 4) * words * sizeof(uint64_t);
+        threads += (words + 63) / 64 * 64 * (threads == 64 && L.a.ndraw > 1 ? 2 : 1);
     }
     const int grid = L.a.Y / L.band;
     if (threads > kTileThreads<I> || L.rows % N != 0 || L.a.Y % L.band != 0 || L.rows < L.band + 2 * L.halo ||
@@ -143,6 +191,16 @@ hipError_t launch_mode(const TileLaunch& L, XiMode mode, bool has_q, hipStream_t
         if constexpr (N == 2 && G < 64)
             return has_q ? launch<G, N, I, XiMode::PerSite, true, Draws::Any>(L, stream)
                          : launch<G, N, I, XiMode::PerSite, false, Draws::Any>(L, stream);
+    }
+    if (mode == XiMode::Ahead) {
+        if constexpr (N == 2) {
+            if (L.a.ndraw & 1)
+                return has_q ? launch<G, N, I, XiMode::Ahead, true, Draws::OddTail>(L, stream)
+                             : launch<G, N, I, XiMode::Ahead, false, Draws::OddTail>(L, stream);
+            if (L.a.ndraw > 0)
+                return has_q ? launch<G, N, I, XiMode::Ahead, true, Draws::Even>(L, stream)
+                             : launch<G, N, I, XiMode::Ahead, false, Draws::Even>(L, stream);
+        }
     }
     if (mode != XiMode::Mask) return hipErrorInvalidValue;
     if (L.a.ndraw == 0)
@@ -177,7 +235,7 @@ hipError_t launch_tile(const SweepArgs& a, XiMode mode, bool has_q, const uint64
                        const TileShape& s, int32_t n_mcs, hipStream_t stream)
 {
     if (n_mcs <= 0) return hipSuccess;
-    const TileLaunch L{a, src, dst, s.rows, s.band, s.halo, n_mcs};
+    const TileLaunch L{a, src, dst, s.rows, s.band, s.halo, n_mcs, 0};
     switch (s.rows_per_thread) {
     case 2: return launch_width<2>(L, mode, has_q, stream);
     case 4: return launch_width<4>(L, mode, has_q, stream);
@@ -189,8 +247,14 @@ hipError_t launch_tile(const SweepArgs& a, XiMode mode, bool has_q, const uint64
 void tile_kernel_name(const SweepArgs& a, XiMode mode, bool has_q, int32_t rows_per_thread, char* out, size_t n)
 {
     const int G = a.W == 1 && a.nb < 64 ? 0 : (a.W < 64 ? a.W : 64);
-    std::snprintf(out, n, "tile_kernel<%d,%d,%d,%s,%s>", G, rows_per_thread, a.W > 64 ? a.W / 64 : 1,
-                  mode == XiMode::PerSite ? "PerSite" : a.ndraw == 0 ? "Fixed" : ((a.ndraw & 1) ? "Mask,OddTail" : "Mask,Even"), has_q ? "true" : "false");
+    const char* const odd = a.ndraw & 1 ? "OddTail" : "Even";
+    char words[24];
+    if (mode == XiMode::PerSite || a.ndraw == 0)
+        std::snprintf(words, sizeof words, mode == XiMode::PerSite ? "PerSite" : "Fixed");
+    else
+        std::snprintf(words, sizeof words, "%s,%s", mode == XiMode::Ahead ? "Ahead" : "Mask", odd);
+    std::snprintf(out, n, "tile_kernel<%d,%d,%d,%s,%s>", G, rows_per_thread, a.W > 64 ? a.W / 64 : 1, words,
+                  has_q ? "true" : "false");
 }
 
 }  // namespace sca

@@ -25,10 +25,10 @@
 // periodic neighbour in the first form and outside that cone in the second.
 //
 // What bounds it: with a wave or two per CU the chain of one half-step (LDS
-// write, barrier, LDS read, the row's masks: 0.13 us at p = 1, 0.24 us at p =
+// write, barrier, LDS read, the row's masks: 0.13 us at p = 1, 0.16 us at p =
 // 1/2), with eight and more waves the vector issue.  Against two launches per
 // MCS (2.8 us each, 1.6 us of it in the kernel): 128 x 128 at p = 1/2, 1000 MCS,
-// 5.80 to 0.45 ms; 2^12 x 2^12 at p = 3/4, q = 1/4, 6.1 to 2.4 us per MCS, of
+// 5.80 to 0.32 ms; 2^12 x 2^12 at p = 3/4, q = 1/4, 6.1 to 2.4 us per MCS, of
 // which half is the recomputed halo (16-row bands, 12 MCS per pass).
 #pragma once
 
@@ -274,6 +274,43 @@ struct PerSiteTile {
     }
 };
 
+// Acceptance words of a tile of few waves (one word per lane, mask mode),
+// formed by further waves of the workgroup one MCS ahead.  They depend on
+// counters alone, so that the rows' waves keep only the chain through the slopes
+// while the other SIMDs of the CU, idle otherwise, run the Philox calls.  Two
+// buffers in LDS, one per MCS in turn; the barrier that starts an MCS orders them.
+// Bound by that chain with one wave of rows (0.13 us without words), by the
+// producers' chain with more draws, by vector issue from four waves on.  us per
+// half-step before and after, p = 1/2; p = 3/4, q = 1/4; p = 15/16:
+//   one wave   (128 x 128)  0.225 to 0.159, 0.39 to 0.23, 0.50 to 0.33
+//   two waves  (512 x 64)   0.273 to 0.211, 0.45 to 0.32, 0.57 to 0.40
+//   four waves (256 x 256)  0.306 to 0.247, 0.51 to 0.42, 0.64 to 0.53
+struct AheadTile {
+    uint64_t* xi;   // [MCS mod 2][sublattice][p, q][tile row][word]
+    int words;      // words of the tile
+    int lw;         // log2 of the words per row
+    int y0, ymask;  // lattice row of tile row 0
+    int q;          // 1 with removals
+
+    __device__ __forceinline__ uint64_t* buffer(uint32_t t, int parity) const
+    {
+        return xi + ((int)(2 * (t & 1u)) + parity) * (words << q);
+    }
+
+    // Word w of the tile for sublattice PI at MCS a.t; tail as in mask_words.
+    template <int PI, bool HASQ, Draws DR>
+    __device__ __forceinline__ void generate(SweepArgs a, int w, uint64_t& tail) const
+    {
+        const uint32_t row = (uint32_t)((y0 + (w >> lw)) & ymask);
+        a.parity = PI;
+        uint64_t xp, xq;
+        mask_words<DR>(a, (row << lw) + (uint32_t)(w & ((1 << lw) - 1)), HASQ, xp, xq, &tail);
+        uint64_t* const out = buffer(a.t, PI) + w;
+        out[0] = xp;
+        if (HASQ) out[words] = xq;
+    }
+};
+
 // What a half-step does at the tile's first and last row beyond the tile:
 // nothing, where the tile wraps or its halo runs out.
 struct NoEdge {
@@ -299,9 +336,9 @@ struct TileThread {
     static_assert(I == 1 || G == 64, "a row of several words per lane fills a wave");
     // Rows whose random words are formed together: two words' worth.  With two
     // words per thread those are all of a half-step, formed before the barrier
-    // it starts with and so off the path from write to read.  Per-site words
-    // come from LDS behind the barrier.
-    static constexpr bool PRE = N * I <= 2 && MODE != XiMode::PerSite;
+    // it starts with and so off the path from write to read.  Words that others
+    // form come from LDS behind the barrier.
+    static constexpr bool PRE = N * I <= 2 && MODE != XiMode::PerSite && MODE != XiMode::Ahead;
     static constexpr int NX = N >= 8 ? 1 : 2 / I;
     // The shared last draw of an odd number of draws waits for the odd half-step.
     static constexpr bool TAIL = DR == Draws::OddTail && MODE == XiMode::Mask;
@@ -319,6 +356,7 @@ struct TileThread {
     uint32_t org[N / 2];  // 1 in the lane and even row that hold site (0,0) (never in a halo row)
     int32_t lifts;        // (lifts - drops) of site (0,0)
     PerSiteTile ps;       // per-site mode
+    AheadTile ahead;      // ahead mode
     int xrow;             // index of the first row's word in a buffer of acceptance words
 
     // The rows of a half-step are independent; they go first, last, then the
@@ -364,7 +402,11 @@ struct TileThread {
             for (int m = 0; m < NX * I; ++m) {
                 xp[m / I][m % I] = a.all_p;
                 xq[m / I][m % I] = a.all_q;
-                if constexpr (MODE == XiMode::PerSite) {
+                if constexpr (MODE == XiMode::Ahead) {
+                    const uint64_t* w = ahead.buffer(a.t, a.parity) + xrow + (row(m0 + m) << ahead.lw);
+                    xp[m][0] = w[0];
+                    if (HASQ) xq[m][0] = w[ahead.words];
+                } else if constexpr (MODE == XiMode::PerSite) {
                     const uint64_t* w = ps.buffer(a.parity) + xrow + (row(m0 + m) << ps.lw);
                     xp[m][0] |= w[0];
                     if (HASQ) xq[m][0] |= w[ps.words];
@@ -375,8 +417,11 @@ struct TileThread {
 
     // Half-step of sublattice PI at MCS a.t; tile rows lo .. hi have to be
     // right, and `skip` (scalar): none of the wave's rows are among them.
+    // `alone` (scalar): the wave holds all rows, and nothing else waits for it
+    // at this half-step.
     template <int PI, class Edge>
-    __device__ __forceinline__ void halfstep(SweepArgs a, uint64_t* ly, int lo, int hi, bool skip, Edge& edge)
+    __device__ __forceinline__ void halfstep(SweepArgs a, uint64_t* ly, int lo, int hi, bool skip, Edge& edge,
+                                             bool alone = false)
     {
         a.parity = PI;
         uint64_t xp[NX][I], xq[NX][I];
@@ -384,7 +429,12 @@ struct TileThread {
         if constexpr (PRE) {
             if (!skip) words(a, 0, xp, xq);
         }
-        __syncthreads();
+        if (alone) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            __syncthreads();
+        }
         if (skip) return;
         uint64_t* const lB = ly + PI * I * stride;        // y- slopes of the first row
         uint64_t* const lC = ly + (1 - PI) * I * stride;  // y+ slopes behind the last row
@@ -411,7 +461,7 @@ struct TileThread {
                                                     mp0, mq0);
             // Pin the new slopes here, or the compiler interleaves the rows and
             // keeps the masks of all of them live.
-            if constexpr (!PRE) {
+            if constexpr (!PRE && MODE != XiMode::Ahead) {
 #pragma unroll
                 for (int k = 0; k < I; ++k)
                     asm volatile("" : "+v"(x[i][0][k]), "+v"(x[i][1][k]), "+v"(y[i][PI][k]), "+v"(C[k]));

@@ -157,3 +157,30 @@ def test_graph_replays_of_tiles(sca):
             a.step(3, 0.5, 0.0)
             b.step(3, 0.5, 0.0)
             assert torch.equal(a.slopes, b.slopes)
+
+
+# words formed ahead: less than a wave of rows, one wave (two sets of producers
+# with more than one draw), two to five waves; bands with idle lanes and with
+# words outside the cone; up to 32 draws
+AHEAD = [(4, 4, 0, 0), (32, 16, 0, 0), (128, 128, 0, 0), (256, 64, 0, 0), (64, 256, 0, 0), (1024, 64, 0, 0),
+         (128, 512, 3, 4), (512, 128, 5, 8), (1024, 256, 6, 4), (2048, 64, 4, 4), (4096, 64, 3, 4), (4096, 32, 4, 4)]
+
+
+@pytest.mark.parametrize("X,Y,depth,band", AHEAD)
+@pytest.mark.parametrize("p,q", [(0.5, 0.0), (0.75, 0.25), (0.625, 0.0), (1.0, 0.5), (0.5 + 2.0**-11, 0.125),
+                                 (1.0 - 2.0**-32, 2.0**-31)])
+def test_words_ahead(orc, sca, X, Y, depth, band, p, q):
+    _say(f"[ahead] {X}x{Y} depth={depth} band={band} p={p} q={q}")
+    st, lat = rough_pair(orc, sca, X, Y, seed=31 + X + Y)
+    if depth:
+        lat.set_blocking(depth, band)
+    else:
+        detach_pass_buffer(lat)
+    for n in (2 * max(depth, 3), 2 * depth + 7):  # from an even and an odd number of MCS
+        # (with 32 draws, four waves of rows are slower than half-step launches)
+        assert "Ahead" in lat.plan(n, p, q)["kernel"] or (depth == 0 and p > 0.99)
+        lat.step(n, p, q)
+        orc.run(st, n, p, q, seed=31 + X + Y)
+        lat.step(1, p, q)
+        orc.run(st, 1, p, q, seed=31 + X + Y)
+        assert_same(orc, lat, st)
