@@ -538,8 +538,11 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
     }
     const bool may_fuse = !(flags & SCA_NO_FUSE) && (c->W < 64 ? c->depth != 0 : depth > 0) && n_mcs >= 1;
     // Lattices too small for full-height bands (and, from X = 8192 on, with the
-    // pass buffer that all their passes need) go by cost.
-    if (automatic && may_fuse && c->W <= 512 && band < tall && (c->W < 64 || (c->alt && !pl.persite))) {
+    // pass buffer that all their passes need) go by cost, with draws also those
+    // whose full-height bands make fewer than four waves per SIMD: 2^15 x 2^16 at
+    // p = 15/16 takes 143 us per MCS at 4 MCS and 128 rows, 127 us at 3 and 64.
+    const bool few_waves = !pl.draw_free && c->Y / band * nw < 4096;
+    if (automatic && may_fuse && c->W <= 512 && (band < tall || few_waves) && (c->W < 64 || (c->alt && !pl.persite))) {
         pl.depth = depth;
         const bool fuse = plan_by_cost(c, n_mcs, team, pl);
         set_passes(pl, n_mcs, fuse);

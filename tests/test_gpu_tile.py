@@ -184,3 +184,17 @@ def test_words_ahead(orc, sca, X, Y, depth, band, p, q):
         lat.step(1, p, q)
         orc.run(st, 1, p, q, seed=31 + X + Y)
         assert_same(orc, lat, st)
+
+
+@pytest.mark.parametrize("X,Y", [(32768, 65536), (65536, 32768), (16384, 131072)])
+@pytest.mark.parametrize("p,q", [(0.75, 0.25), (0.9375, 0.0)])
+def test_full_height_bands_of_few_waves(sca, X, Y, p, q):
+    """With fewer than four waves per SIMD at 128 rows the cost decides: 64 rows
+    for these; the two-launch form's bits."""
+    a, b = sca.Lattice(X, Y, seed=5), sca.Lattice(X, Y, seed=5)
+    assert a.plan(24, p, q)["band"] == 64
+    for n in (5, 24):
+        _say(f"[few waves] {X}x{Y} p={p} q={q} n={n}: {a.plan(n, p, q)}")
+        a.step(n, p, q)
+        b.step(n, p, q, fuse=False)
+        assert torch.equal(a.slopes, b.slopes) and a.meta() == b.meta()
