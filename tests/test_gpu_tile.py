@@ -192,8 +192,8 @@ def test_full_height_bands_of_few_waves(sca, X, Y, p, q):
     """With fewer than four waves per SIMD at 128 rows the cost decides: 64 rows
     for these; the two-launch form's bits."""
     a, b = sca.Lattice(X, Y, seed=5), sca.Lattice(X, Y, seed=5)
-    assert a.plan(24, p, q)["band"] == 64
-    for n in (5, 24):
+    assert a.plan(33, p, q)["band"] == 64
+    for n in (5, 33):
         _say(f"[few waves] {X}x{Y} p={p} q={q} n={n}: {a.plan(n, p, q)}")
         a.step(n, p, q)
         b.step(n, p, q, fuse=False)
