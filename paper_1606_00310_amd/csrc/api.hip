@@ -1172,7 +1172,7 @@ struct sca_batch {
     int64_t save_words = 0;         // per workgroup (and per part) in the captured graph
     int32_t resident = 0;           // workgroups of the captured launch that run at once
     int32_t* d_sync = nullptr;      // barrier counters of split realizations (one per part slot of the grid)
-    uint64_t* d_team = nullptr;     // posts and messages of on-chip teams (allocated on first use)
+    uint64_t* d_team = nullptr;     // formation, posts and messages of on-chip teams (allocated on first use)
     int32_t cu_grid = 0;            // workgroups of the on-chip launch: one per compute unit, 0 if it does not fit
     int32_t* d_err = nullptr;       // set by a barrier wait that gave up
     int32_t* h_err = nullptr;       // pinned copy of d_err, written after each launch
@@ -1184,7 +1184,8 @@ struct sca_batch {
     int32_t* d_counters = nullptr;  // kCounters words, see below
     int64_t* d_ws = nullptr;        // moments workspace for Y up to 131072
     // sca_batch_collect: kCollect result slots of 8 words (the first one is also
-    // sca_batch_roughness's), and behind them as many items; pinned
+    // sca_batch_roughness's), behind them as many items, and a word that an
+    // on-chip launch sets whose teams could not form; pinned
     int64_t* results = nullptr;
     // pinned staging
     sca::BatchDesc* h_desc = nullptr;
@@ -1209,6 +1210,13 @@ namespace {
 enum { kItems = 0, kQueue = 1, kOnChipCount = 4, kOnChipQueue = 8, kCounters = 12 };
 
 constexpr int32_t kCollect = 256;  // realizations per launch and wait of sca_batch_collect
+
+sca::MomentsItem* collect_items(const sca_batch* b)
+{
+    return reinterpret_cast<sca::MomentsItem*>(b->results + 8 * kCollect);
+}
+
+int32_t* batch_apart(const sca_batch* b) { return reinterpret_cast<int32_t*>(collect_items(b) + kCollect); }
 
 int bfail(sca_batch* b)
 {
@@ -1342,8 +1350,8 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
         hipMalloc(&b->d_sync, sizeof(int32_t) * (size_t)b->num_cus * 8) != hipSuccess ||
         hipMalloc(&b->d_err, sizeof(int32_t)) != hipSuccess ||
         hipHostMalloc(&b->h_err, sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&b->results, kCollect * (8 * sizeof(int64_t) + sizeof(sca::MomentsItem)), hipHostMallocDefault) !=
-            hipSuccess ||
+        hipHostMalloc(&b->results, kCollect * (8 * sizeof(int64_t) + sizeof(sca::MomentsItem)) + sizeof(int64_t),
+                      hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&b->err_copied, hipEventDisableTiming) != hipSuccess ||
         hipMemsetAsync(b->d_err, 0, sizeof(int32_t), b->stream) != hipSuccess) {
         (void)hipGetLastError();
@@ -1352,6 +1360,7 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     }
     std::memset(b->h_desc, 0, nd);
     *b->h_err = 0;
+    *batch_apart(b) = 0;
     b->cu_grid = sca::onchip_occupancy() > 0 ? b->num_cus : 0;
     *out = b;
     return SCA_OK;
@@ -1522,14 +1531,16 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
             ++active;
         }
     }
+    // teams that could not form once are not tried again
+    const bool apart = *const_cast<const volatile int32_t*>(batch_apart(b)) != 0;
+    const int max_parts = std::min(apart ? 1 : sca::kOnChipMaxParts, b->cu_grid);
     const int64_t chip_share = b->cu_grid > 0 ? total / (2 * b->cu_grid) : 0;
     auto chip_parts = [&](const SlotHost& s, int64_t w, int32_t* rows) {
         const int Y = (int)s.req.Y;
-        for (int32_t P = 1; P <= sca::kOnChipMaxParts && P <= b->cu_grid; P *= 2) {
+        for (int32_t P = 1; P <= max_parts; P *= 2) {
             const int N = sca::team_rows(s.W, Y, P);
             if (N == 0) continue;
-            const bool more = b->cfg.order == 0 && w / P > chip_share && N > 2 && 2 * P <= sca::kOnChipMaxParts &&
-                              2 * P <= b->cu_grid;
+            const bool more = b->cfg.order == 0 && w / P > chip_share && N > 2 && 2 * P <= max_parts;
             if (more && sca::team_rows(s.W, Y, 2 * P) > 0) continue;
             *rows = N;
             return P;
@@ -1636,8 +1647,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     if (active_out) *active_out = active;
     if (count == 0) return SCA_OK;
     if (teams && !b->d_team &&
-        hipMalloc(&b->d_team, sizeof(uint64_t) * (size_t)(sca::onchip_mail_words(b->cu_grid) +
-                                                          sca::onchip_message_words(b->cu_grid))) != hipSuccess)
+        hipMalloc(&b->d_team, sizeof(uint64_t) * (size_t)sca::onchip_team_words(b->cu_grid)) != hipSuccess)
         return bfail(b);
     if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1), hipMemcpyHostToDevice,
                        b->stream) != hipSuccess ||
@@ -1653,9 +1663,9 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
                                   b->d_order + items,
                                   b->d_counters + kOnChipCount,
                                   b->d_counters + kOnChipQueue,
-                                  b->d_team,
-                                  b->d_team + (teams ? sca::onchip_mail_words(b->cu_grid) : 0),
-                                  b->d_err};
+                                  teams ? b->d_team : nullptr,
+                                  b->d_err,
+                                  batch_apart(b)};
         if (sca::launch_onchip(L, b->cu_grid, teams, b->stream) != hipSuccess) return bfail(b);
     }
     if (items > 0 && hipGraphLaunch(b->exec, b->stream) != hipSuccess) return bfail(b);
@@ -1729,7 +1739,7 @@ int sca_batch_collect(sca_batch* b, const int32_t* slots, int32_t n, sca_collect
     if (b->failed) return SCA_ESTATE;
     DeviceGuard dg(b->device);
     if (!dg.ok) return bfail(b);
-    auto* const items = reinterpret_cast<sca::MomentsItem*>(b->results + 8 * kCollect);
+    sca::MomentsItem* const items = collect_items(b);
     for (int32_t i0 = 0; i0 < n; i0 += kCollect) {
         const int32_t m = std::min(n - i0, kCollect);
         int32_t n_items = 0;

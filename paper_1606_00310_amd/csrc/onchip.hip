@@ -10,9 +10,10 @@
 // workgroups, longest first, then each half of them goes on with the list for
 // four, and so on.  The first workgroup of a team takes the next realization
 // and posts it to the others.  A wait is therefore for workgroups in the same
-// list of the same team, in lockstep through their messages; only a launch that
-// shares the device with others waits longer, for its own workgroups to be
-// started.
+// list of the same team, in lockstep through their messages.  Where the launch's
+// workgroups do not get to run at the same time, the realizations for teams go
+// half-step by half-step in memory, one workgroup each, in a kernel behind this
+// one; the host learns of it and makes no more teams for that ensemble.
 //
 // Bound by vector issue: p = 1/2, 3/4 and 15/16 take some 50, 70 and 110
 // instructions per word and half-step and run at 3.7e13, 2.6e13 and 1.8e13 site
@@ -43,10 +44,9 @@ __device__ __forceinline__ BatchDesc load_desc(const BatchDesc* table, int32_t s
     return d;
 }
 
-// The epoch of one realization, N rows per thread.
-template <int N>
-__device__ __forceinline__ void run_rows(const BatchDesc& d, uint64_t* xch, uint64_t* ly, int parts, int member,
-                                         uint32_t tag, Patience& patience)
+__device__ __host__ constexpr int64_t mail_words(int grid) { return (int64_t)kLevels * grid * kMailSlots; }
+
+__device__ __forceinline__ SweepArgs sweep_args(const BatchDesc& d)
 {
     SweepArgs a{};
     a.plane = d.plane;
@@ -62,6 +62,15 @@ __device__ __forceinline__ void run_rows(const BatchDesc& d, uint64_t* xch, uint
     a.all_p = d.all_p;
     a.all_q = d.all_q;
     a.h0 = d.h0;
+    return a;
+}
+
+// The epoch of one realization, N rows per thread.
+template <int N>
+__device__ __forceinline__ void run_rows(const BatchDesc& d, uint64_t* xch, uint64_t* ly, int parts, int member,
+                                         uint32_t tag, Patience& patience)
+{
+    const SweepArgs a = sweep_args(d);
     const bool odd = (d.ndraw & 1) != 0;
     const auto ready = [] { return true; };
     if (d.has_q) {
@@ -78,15 +87,26 @@ __global__ __launch_bounds__(kThreads) void onchip_kernel(OnChipLaunch L)
     __shared__ uint64_t ly[kTeamLds<8, 1>];
     __shared__ int32_t s_item;
     Patience patience{L.err};
+    uint64_t* const mails = L.team + kFormationWords;
+    uint64_t* const messages = mails + mail_words((int)gridDim.x);
+    bool teams = false;
+    if (L.team) {
+        if (threadIdx.x == 0) {
+            arrive(L.team, 1, gridDim.x);
+            s_item = formed(L.team, 1) ? 1 : 0;
+        }
+        __syncthreads();
+        teams = __builtin_amdgcn_readfirstlane(s_item) != 0;
+    }
     uint32_t tag = 0;
     int32_t first = 0;
     for (int level = 0; level < kLevels; ++level) {
         const int parts = 8 >> level;
-        const int32_t count = L.count[level];
+        const int32_t count = parts == 1 || teams ? L.count[level] : 0;
         const int team = (int)blockIdx.x / parts, member = (int)blockIdx.x % parts;
         const bool whole_team = (team + 1) * parts <= (int)gridDim.x;
-        uint64_t* const xch = L.xch + (int64_t)level * gridDim.x * kSlots<1>;
-        uint64_t* const mail = L.mail + ((int64_t)level * gridDim.x + team) * kMailSlots;
+        uint64_t* const xch = messages + (int64_t)level * gridDim.x * kSlots<1>;
+        uint64_t* const mail = mails + ((int64_t)level * gridDim.x + team) * kMailSlots;
         for (uint32_t seq = 1; count > 0 && whole_team; ++seq) {
             __syncthreads();  // the last realization is finished with LDS
             if (threadIdx.x == 0) {
@@ -117,11 +137,61 @@ __global__ __launch_bounds__(kThreads) void onchip_kernel(OnChipLaunch L)
             }
             tag += 2u * d.n_run;
         }
+        first += L.count[level];
+    }
+}
+
+// Half-steps in memory, one workgroup per realization (its n_run MCS).
+template <int G, bool HASQ>
+__device__ __forceinline__ void memory_run(const BatchDesc& d)
+{
+    SweepArgs a = sweep_args(d);
+    for (uint32_t m = 0; m < d.n_run; ++m, ++a.t)
+        for (a.parity = 0; a.parity < 2; ++a.parity) {
+            for (int r0 = 0; r0 < a.Y; r0 += kThreads / G)
+                halfstep_rows<G, 1, XiMode::Mask, HASQ>(a, d.S, r0 + (int64_t)threadIdx.x / G, (int)threadIdx.x & 63);
+            __syncthreads();
+        }
+}
+
+template <int G>
+__device__ __forceinline__ void memory_run(const BatchDesc& d)
+{
+    if (d.has_q) memory_run<G, true>(d);
+    else memory_run<G, false>(d);
+}
+
+// The realizations meant for teams, if the teams could not form.
+__global__ __launch_bounds__(kThreads) void onchip_apart_kernel(OnChipLaunch L)
+{
+    __shared__ int32_t s_item;
+    if (peek(L.team + kDecision) != 3) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    int32_t first = 0;
+    for (int level = 0; level < kLevels - 1; ++level) {
+        const int32_t count = L.count[level];
+        for (;;) {
+            __syncthreads();
+            if (threadIdx.x == 0) s_item = atomicAdd(L.queue + level, 1);
+            __syncthreads();
+            const int32_t item = __builtin_amdgcn_readfirstlane(s_item);
+            if (item >= count) break;
+            const BatchDesc d = load_desc(L.desc, __builtin_amdgcn_readfirstlane(L.order[first + item]));
+            switch (d.W) {
+            case 1: memory_run<1>(d); break;
+            case 2: memory_run<2>(d); break;
+            case 4: memory_run<4>(d); break;
+            case 8: memory_run<8>(d); break;
+            case 16: memory_run<16>(d); break;
+            case 32: memory_run<32>(d); break;
+            default: memory_run<64>(d); break;
+            }
+        }
         first += count;
     }
 }
 
-// Zeroes the posts and messages of the last launch.
+// Zeroes the formation, posts and messages of the last launch.
 __global__ __launch_bounds__(256) void onchip_reset_kernel(uint64_t* p, int64_t n)
 {
     for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) p[k] = 0;
@@ -129,18 +199,23 @@ __global__ __launch_bounds__(256) void onchip_reset_kernel(uint64_t* p, int64_t 
 
 }  // namespace
 
-int64_t onchip_mail_words(int grid) { return (int64_t)kLevels * grid * kMailSlots; }
-int64_t onchip_message_words(int grid) { return (int64_t)(kLevels - 1) * grid * kSlots<1>; }
+int64_t onchip_team_words(int grid)
+{
+    return kFormationWords + mail_words(grid) + (int64_t)(kLevels - 1) * grid * kSlots<1>;
+}
 
 hipError_t launch_onchip(const OnChipLaunch& L, int grid, bool teams, hipStream_t stream)
 {
-    if (teams) {  // L.xch follows L.mail
-        hipLaunchKernelGGL(onchip_reset_kernel, dim3(256), dim3(256), 0, stream, L.mail,
-                           onchip_mail_words(grid) + onchip_message_words(grid));
+    if (teams != (L.team != nullptr)) return hipErrorInvalidValue;
+    if (teams) {
+        hipLaunchKernelGGL(onchip_reset_kernel, dim3(256), dim3(256), 0, stream, L.team, onchip_team_words(grid));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(onchip_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, L);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !teams) return e;
+    hipLaunchKernelGGL(onchip_apart_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, L);
     return hipGetLastError();
 }
 

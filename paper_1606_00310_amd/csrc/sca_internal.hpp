@@ -233,12 +233,11 @@ struct OnChipLaunch {
     const int32_t* order;  // slots: the lists for teams of 8, 4, 2 and 1 workgroups, one after another
     const int32_t* count;  // [4] entries of each list
     int32_t* queue;        // [4] entries taken, 0 before the launch
-    uint64_t* mail;        // onchip_mail_words(grid), and behind them
-    uint64_t* xch;         // onchip_message_words(grid); neither without teams
+    uint64_t* team;        // onchip_team_words(grid), nullptr without teams
     int32_t* err;          // set if a wait ran out of patience
+    int32_t* apart;        // (host memory) set if the teams could not form
 };
-int64_t onchip_mail_words(int grid);
-int64_t onchip_message_words(int grid);
+int64_t onchip_team_words(int grid);
 // grid: workgroups, at most as many as run at once; teams: a list other than
 // the last has entries.
 hipError_t launch_onchip(const OnChipLaunch& L, int grid, bool teams, hipStream_t stream);

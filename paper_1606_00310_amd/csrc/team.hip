@@ -15,14 +15,11 @@
 // A launch without MCS would take about 33 us at 2^28 sites: 27 us for the state's
 // way in and out, the rest until the team has formed.
 //
-// All workgroups have to run at the same time for that, which another stream's
-// kernels can prevent.  So the team forms first, while its rows are loaded: the
-// last workgroup to arrive decides to go on, or, after a millisecond, one that
-// waits decides that they work apart.  Apart, they take half-steps of bands of
-// rows in memory from a common list, in an order in which each depends on
-// earlier entries only: any number of workgroups, one after another if need be,
-// completes them.  The host learns of it and launches no more teams for that
-// lattice.
+// All workgroups have to run at the same time for that (team.hpp).  Apart, they
+// take half-steps of bands of rows in memory from a common list, in an order in
+// which each depends on earlier entries only: any number of workgroups, one after
+// another if need be, completes them.  The host learns of it and launches no more
+// teams for that lattice.
 #include <cstdio>
 
 #include "sca_internal.hpp"
@@ -31,34 +28,8 @@
 namespace sca {
 namespace {
 
-constexpr uint64_t kFormation = 100000;  // ticks of the 100 MHz clock: 1 ms
-
 // Control words ahead of the messages, each on a line of its own.
-enum Control { kArrivals = 0, kDecision = 16, kTicket = 32, kDone = 64, kControl = kDone + kTeamMaxParts };
-
-// Thread 0: the decision of launch L.epoch, 2 epoch (go) or 2 epoch + 1 (apart),
-// if need be the one wanted.
-__device__ __forceinline__ uint64_t decide(const TeamLaunch& L, uint64_t want)
-{
-    uint64_t v = peek(L.ctl + kDecision);
-    while (v < 2 * L.epoch)
-        if (__hip_atomic_compare_exchange_strong(L.ctl + kDecision, &v, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT))
-            return want;
-    return v;
-}
-
-// Thread 0: whether all workgroups run at the same time.
-__device__ __forceinline__ bool formed(const TeamLaunch& L)
-{
-    const uint64_t since = __builtin_amdgcn_s_memrealtime();
-    uint64_t v;
-    while ((v = peek(L.ctl + kDecision)) < 2 * L.epoch) {
-        __builtin_amdgcn_s_sleep(1);
-        if (__builtin_amdgcn_s_memrealtime() - since > kFormation) v = decide(L, 2 * L.epoch + 1);
-    }
-    return v == 2 * L.epoch;
-}
+enum Control { kTicket = kFormationWords, kDone = kTicket + 32, kControl = kDone + kTeamMaxParts };
 
 // Thread 0: the next entry of the list.
 __device__ __forceinline__ uint32_t take_ticket(const TeamLaunch& L)
@@ -116,14 +87,11 @@ __global__ __launch_bounds__(kThreads) void team_kernel(TeamLaunch L)
     __shared__ uint64_t ly[kTeamLds<N, I>];
     __shared__ uint32_t s_word;
     const int parts = (int)gridDim.x;
-    if (threadIdx.x == 0) {
-        const uint64_t before = __hip_atomic_fetch_add(L.ctl + kArrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (before + 1 == L.epoch * (uint64_t)parts) decide(L, 2 * L.epoch);
-    }
+    if (threadIdx.x == 0) arrive(L.ctl, L.epoch, (uint64_t)parts);
     Patience patience{L.err};
     const bool done = team_run<G, N, I, HASQ, DR>(
         L.a, L.a.S, (uint32_t)L.n, L.ctl + kControl, ly, parts, (int)blockIdx.x, L.tag, patience, [&] {
-            if (threadIdx.x == 0) s_word = formed(L) ? 1u : 0u;
+            if (threadIdx.x == 0) s_word = formed(L.ctl, L.epoch) ? 1u : 0u;
             __syncthreads();
             return __builtin_amdgcn_readfirstlane(s_word) != 0u;
         });

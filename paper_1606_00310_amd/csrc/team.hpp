@@ -20,6 +20,13 @@
 // thread without random words.
 //
 // Every wait gives up after two minutes, or when another has, and waits no more.
+//
+// The workgroups of a team have to run at the same time, which kernels on other
+// streams can prevent for good: each XCD dispatches its share of a grid by
+// itself, so two launches that start together can each hold some XCDs, and no
+// team of either has all its workgroups.  So a launch forms first: the last of
+// its workgroups to arrive decides to go on, or, after a millisecond, one that
+// waits decides that there will be no teams.
 #pragma once
 
 #include "sca_internal.hpp"
@@ -40,6 +47,42 @@ __device__ __forceinline__ void post(uint64_t* p, uint64_t v)
 __device__ __forceinline__ uint64_t peek(const uint64_t* p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Words of a launch's formation, each on a line of its own; `epoch` numbers the
+// launches since they were zero, from 1.
+enum Formation { kArrivals = 0, kDecision = 16, kFormationWords = 32 };
+constexpr uint64_t kFormationTime = 100000;  // ticks of the 100 MHz clock: 1 ms
+
+// One thread: the launch's decision, 2 epoch (go on) or 2 epoch + 1 (apart), if
+// there is none yet the one wanted.
+__device__ __forceinline__ uint64_t decide(uint64_t* ctl, uint64_t epoch, uint64_t want)
+{
+    uint64_t v = peek(ctl + kDecision);
+    while (v < 2 * epoch)
+        if (__hip_atomic_compare_exchange_strong(ctl + kDecision, &v, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return want;
+    return v;
+}
+
+// One thread of each of the launch's `parts` workgroups.
+__device__ __forceinline__ void arrive(uint64_t* ctl, uint64_t epoch, uint64_t parts)
+{
+    const uint64_t before = __hip_atomic_fetch_add(ctl + kArrivals, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + 1 == epoch * parts) decide(ctl, epoch, 2 * epoch);
+}
+
+// The same thread: whether all of them run at the same time.
+__device__ __forceinline__ bool formed(uint64_t* ctl, uint64_t epoch)
+{
+    const uint64_t since = __builtin_amdgcn_s_memrealtime();
+    uint64_t v;
+    while ((v = peek(ctl + kDecision)) < 2 * epoch) {
+        __builtin_amdgcn_s_sleep(1);
+        if (__builtin_amdgcn_s_memrealtime() - since > kFormationTime) v = decide(ctl, epoch, 2 * epoch + 1);
+    }
+    return v == 2 * epoch;
 }
 
 // Whether a wait should go on: false once it has lasted too long or another

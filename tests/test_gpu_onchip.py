@@ -154,3 +154,19 @@ def test_admission_initialises(sca, n):
         W, nb = max(1, r.X // 128), min(64, r.X // 2)
         assert S.shape == (2, 2, r.Y, W) and int(h0[0]) == 0
         assert not S[:, 0].any() and bool((S[:, 1] == ((1 << nb) - 1 if nb < 64 else -1)).all())
+
+
+@pytest.mark.parametrize("X,Y,p,q", [(2048, 2048, 0.75, 0.25), (4096, 1024, 0.5, 0.0), (64, 65536, 0.9375, 0.0),
+                                     (8192, 512, 0.5, 0.5), (512, 8192, 0.5, 0.0)])
+def test_teams_that_cannot_form(sca, X, Y, p, q):
+    """A kernel on another stream keeps a compute unit from the launch: the
+    realizations for teams run in memory, and later epochs make no teams."""
+    from paper_1606_00310_amd.batch import Realization as R
+
+    reals = [R(X, Y, p, q, 22, 5), R(128, 128, p, q, 22, 6), R(X, Y, 1.0, 0.0, 9, 7)]
+    for _ in range(6):  # a stream may share the ensemble's hardware queue, and then delays it only
+        torch.cuda.synchronize()
+        with torch.cuda.stream(torch.cuda.Stream()):
+            torch.cuda._sleep(20_000_000)
+        b, slots = run_batch(reals, epochs=(9, 5, 8))
+        check_solo(sca, b, slots, reals)
