@@ -118,3 +118,36 @@ def test_not_in_graphs(sca):
         a.step(n, 0.5, 0.0)
         b.step(n, 0.5, 0.0)
         assert torch.equal(a.slopes, b.slopes) and a.meta() == b.meta()
+
+
+def test_beside_an_ensemble(sca):
+    """A lattice and an ensemble, both with teams, started together on two
+    streams again and again: both end with the bits of the two-launch form."""
+    from paper_1606_00310_amd.batch import Batch, Realization, state_bytes
+
+    X, Y = 8192, 32768
+    reals = [Realization(2048, 2048, 0.75, 0.25, 60, 10 + k) for k in range(6)] + [Realization(512, 512, 0.5, 0.0, 60, 3)]
+    ref = sca.Lattice(X, Y, seed=9)
+    ref.step(120, 0.5, 0.0, fuse=False)
+    torch.cuda.synchronize()
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    for rep in range(3):
+        _say(f"[beside] {rep}")
+        with torch.cuda.stream(one):
+            lat = sca.Lattice(X, Y, seed=9)
+        with torch.cuda.stream(two):
+            b = Batch(max_slots=len(reals), arena_bytes=sum(state_bytes(r.X, r.Y) for r in reals), stream=two)
+            slots = b.admit(reals)
+        torch.cuda.synchronize()
+        for _ in range(6):
+            with torch.cuda.stream(two):
+                b.run(10)
+            with torch.cuda.stream(one):
+                lat.step(20, 0.5, 0.0)
+        torch.cuda.synchronize()
+        assert torch.equal(lat.slopes, ref.slopes) and lat.meta() == ref.meta()
+        for r, s in zip(reals, slots):
+            solo = sca.Lattice(r.X, r.Y, seed=r.seed)
+            solo.step(r.n_mcs, r.p, r.q, fuse=False)
+            assert torch.equal(b.state(s)[0], solo.slopes) and b.roughness(s) == solo.roughness()
+        b.close()
