@@ -1205,9 +1205,15 @@ struct sca_batch {
 namespace {
 
 // The launch counters, staged and copied with the order: the persistent
-// kernel's item count and queue, then the on-chip kernel's four list lengths
+// kernel's item count and queue, then the on-chip kernel's list lengths
 // and queues (the copy zeroes the queues).
-enum { kItems = 0, kQueue = 1, kOnChipCount = 4, kOnChipQueue = 8, kCounters = 12 };
+enum {
+    kItems = 0,
+    kQueue = 1,
+    kOnChipCount = 4,
+    kOnChipQueue = kOnChipCount + sca::kOnChipLevels,
+    kCounters = kOnChipQueue + sca::kOnChipLevels
+};
 
 constexpr int32_t kCollect = 256;  // realizations per launch and wait of sca_batch_collect
 
@@ -1502,17 +1508,17 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     if (b->staged_pending && hipEventSynchronize(b->staged) != hipSuccess) return bfail(b);
     b->staged_pending = false;
     int32_t count = 0, hi = -1;
-    std::vector<std::pair<int64_t, int32_t>> work, chip[4];
+    std::vector<std::pair<int64_t, int32_t>> work, chip[sca::kOnChipLevels];
     std::vector<int64_t> runs((size_t)b->max_slots, 0);
     int64_t total = 0, rest_total = 0;
     // On chip (unless the configuration keeps states in the arena) go the
-    // bit-mask realizations that up to eight workgroups hold, with as few
+    // bit-mask realizations that up to sixteen workgroups hold, with as few
     // workgroups as do, or more where each would have more than half of the
     // average work per compute unit and its rows per thread can still be halved.
     // Work is counted in vector instructions (p = 15/16 takes more than twice
-    // those of p = 1/2 per site).  512 realizations of 2^6 to 2^11 squared: 3.7 ms;
-    // with sites for work and a whole average as the line 5.2 ms, the longest
-    // realization with eight workgroups alone 3.6 ms.
+    // those of p = 1/2 per site).  512 realizations of 2^6 to 2^11 squared: 3.6 ms;
+    // with a whole average as the line 4.4 ms, with a third or a sixth of it 1.5
+    // and 5 % more, with sites for work and a whole average 5.2 ms.
     auto cost = [](const SlotHost& s, int64_t run) {
         const int64_t nd = s.desc.mode == 0 ? s.desc.ndraw : 32, q = s.desc.has_q;
         return run * s.req.Y * s.W * (30 + 10 * q + 18 * nd + 2 * nd * (1 + q));
@@ -1565,7 +1571,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
             if (P > 0) {
                 d.parts = P;
                 d.bands = rows;
-                chip[P == 8 ? 0 : P == 4 ? 1 : P == 2 ? 2 : 3].emplace_back(cost(s, run), slot);
+                chip[sca::kOnChipLevels - 1 - __builtin_ctz((unsigned)P)].emplace_back(cost(s, run), slot);
             } else {
                 work.emplace_back(w, slot);
                 rest_total += w;
@@ -1639,11 +1645,12 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     const int32_t items = count;
     std::memset(b->h_count, 0, kCounters * sizeof(int32_t));
     b->h_count[kItems] = items;
-    for (int i = 0; i < 4; ++i) {
+    bool teams = false;
+    for (int i = 0; i < sca::kOnChipLevels; ++i) {
+        teams = teams || (i < sca::kOnChipLevels - 1 && !chip[i].empty());
         b->h_count[kOnChipCount + i] = (int32_t)chip[i].size();
         for (const auto& w : chip[i]) b->h_order[count++] = w.second;
     }
-    const bool teams = !chip[0].empty() || !chip[1].empty() || !chip[2].empty();
     if (active_out) *active_out = active;
     if (count == 0) return SCA_OK;
     if (teams && !b->d_team &&

@@ -2,13 +2,13 @@
 // or a few compute units for a whole epoch.
 //
 // A workgroup holds a lattice of up to 1024 x 1024, larger ones spread over a
-// team of 2, 4 or 8 workgroups (team.hpp).  Each size of team has message slots
+// team of 2 to 16 workgroups (team.hpp).  Each size of team has message slots
 // of its own, since its neighbours are others.
 //
-// Teams are fixed groups of workgroups, eight, then four, two and one:
-// all teams of eight work through the list of realizations for eight
+// Teams are fixed groups of workgroups, sixteen, then eight, four, two and one:
+// all teams of sixteen work through the list of realizations for sixteen
 // workgroups, longest first, then each half of them goes on with the list for
-// four, and so on.  The first workgroup of a team takes the next realization
+// eight, and so on.  The first workgroup of a team takes the next realization
 // and posts it to the others.  A wait is therefore for workgroups in the same
 // list of the same team, in lockstep through their messages.  Where the launch's
 // workgroups do not get to run at the same time, the realizations for teams go
@@ -19,8 +19,9 @@
 // instructions per word and half-step and run at 3.7e13, 2.6e13 and 1.8e13 site
 // updates/s with 256 lattices of 1024^2 or 64 of 2048^2.  The 4096 realizations
 // of 2^6 to 2^11 squared, 100 to 10^4 MCS, took 0.62 s in blocked passes
-// through memory and take 0.36 s; a 2048^2 lattice alone at p = 1/2 takes 3.7 us
-// per MCS on a team of eight, whose half-steps wait for messages.  A workgroup
+// through memory and take 0.36 s; a 2048^2 lattice alone at p = 1/2 takes 2.4 us
+// per MCS on a team of sixteen, whose half-steps wait for messages (3.8 us on
+// eight; p = 15/16: 4.0 and 7.1 us).  A workgroup
 // per CU: eight rows per thread fill the 128 registers that 1024 threads leave.
 #include "sca_internal.hpp"
 #include "team.hpp"
@@ -28,8 +29,8 @@
 namespace sca {
 namespace {
 
-constexpr int kLevels = 4;     // teams of 8, 4, 2 and 1 workgroups
-constexpr int kMailSlots = 8;  // posts of a team; a member lags at most half a team behind the first
+constexpr int kLevels = kOnChipLevels;
+constexpr int kMailSlots = 16;  // posts of a team; a member lags at most half a team behind the first
 
 // A descriptor in scalar registers: it is the same for the whole workgroup.
 __device__ __forceinline__ BatchDesc load_desc(const BatchDesc* table, int32_t slot)
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void onchip_kernel(OnChipLaunch L)
     uint32_t tag = 0;
     int32_t first = 0;
     for (int level = 0; level < kLevels; ++level) {
-        const int parts = 8 >> level;
+        const int parts = kOnChipMaxParts >> level;
         const int32_t count = parts == 1 || teams ? L.count[level] : 0;
         const int team = (int)blockIdx.x / parts, member = (int)blockIdx.x % parts;
         const bool whole_team = (team + 1) * parts <= (int)gridDim.x;

@@ -227,12 +227,13 @@ void team_kernel_name(const SweepArgs& a, bool has_q, int rows, char* out, size_
 
 // Realizations that stay on chip for an epoch (onchip.hip): bit-mask mode, in
 // a team of d.parts workgroups with d.bands = team_rows rows per thread.
-constexpr int kOnChipMaxParts = 8;
+constexpr int kOnChipLevels = 5;  // teams of 16, 8, 4, 2 and 1 workgroups
+constexpr int kOnChipMaxParts = 1 << (kOnChipLevels - 1);
 struct OnChipLaunch {
     const BatchDesc* desc;
-    const int32_t* order;  // slots: the lists for teams of 8, 4, 2 and 1 workgroups, one after another
-    const int32_t* count;  // [4] entries of each list
-    int32_t* queue;        // [4] entries taken, 0 before the launch
+    const int32_t* order;  // slots: the lists for teams of 16 to 1 workgroups, one after another
+    const int32_t* count;  // [kOnChipLevels] entries of each list
+    int32_t* queue;        // [kOnChipLevels] entries taken, 0 before the launch
     uint64_t* team;        // onchip_team_words(grid), nullptr without teams
     int32_t* err;          // set if a wait ran out of patience
     int32_t* apart;        // (host memory) set if the teams could not form

@@ -170,3 +170,18 @@ def test_teams_that_cannot_form(sca, X, Y, p, q):
             torch.cuda._sleep(20_000_000)
         b, slots = run_batch(reals, epochs=(9, 5, 8))
         check_solo(sca, b, slots, reals)
+
+
+@pytest.mark.parametrize("p,q", [(0.5, 0.0), (0.75, 0.25), (0.9375, 0.0), (1.0, 0.0)])
+def test_teams_of_sixteen(sca, p, q):
+    """Lattices that only sixteen workgroups hold, and ones that are split as far
+    because little else runs."""
+    from paper_1606_00310_amd.batch import Realization as R
+
+    sizes = [(4096, 4096), (8192, 2048), (64, 131072), (2048, 8192), (2048, 2048), (512, 4096)]
+    reals = [R(X, Y, p, q, 7 + 5 * (k % 3), 50 + k) for k, (X, Y) in enumerate(sizes)]
+    b, slots = run_batch(reals, epochs=(1, 2, 8))
+    check_solo(sca, b, slots, reals)
+    reals = [R(2048, 2048, p, q, 33, 70)]
+    b, slots = run_batch(reals)
+    check_solo(sca, b, slots, reals)
