@@ -276,15 +276,17 @@ void sca_destroy(sca_ctx* ctx);
 /* ------------------------------------------------------------------------ */
 /* A batch advances thousands of independent lattices of uneven size in one
  * persistent kernel launch per epoch: realizations with dyadic p, q that the
- * registers of up to eight compute units hold (up to 2^23 sites) stay on chip
+ * registers of up to sixteen compute units hold (up to 2^24 sites) stay on chip
  * for the epoch, the others go through a second, hipGraph-captured persistent
- * kernel.  Each realization
+ * kernel.  If other streams' kernels keep the launch's workgroups from running at
+ * the same time for a millisecond, realizations that need several compute units
+ * run in memory in that epoch and in the second kernel later.  Each realization
  * draws from its own seed with the same counters as the single-lattice path,
  * so its state after any number of MCS is bit-identical to a solo run of the
  * same (X, Y, p, q, seed) -- independent of the schedule and configuration.
  * States live in a caller-owned device arena; the library keeps a small
  * table of per-slot descriptors on the device (and, once a realization needs
- * several compute units, 3 MiB for the messages between them). */
+ * several compute units, 4.2 MB for the messages between them). */
 
 typedef struct sca_batch sca_batch;
 
