@@ -211,6 +211,19 @@ inline int team_rows(int W, int64_t Y, int parts)
 // captured: each is given its number.
 constexpr int kTeamMaxParts = 256;
 constexpr int64_t kTeamMaxMcs = 1 << 14;
+
+// Words of `ctl` that count within one launch hold the launch's number (mod
+// 2^40) above the count, so that whatever earlier launches left in them counts
+// nothing in this one: only launches whose team did not form write these words,
+// and any number of others may lie between two of those.
+constexpr int kTeamCountBits = 24;
+static_assert((2 * kTeamMaxMcs + 1) * kTeamMaxParts < 1 << kTeamCountBits, "every half-step of every band has a number");
+__host__ __device__ inline uint64_t team_count(uint64_t epoch, uint32_t n) { return (epoch << kTeamCountBits) | n; }
+__host__ __device__ inline uint32_t team_counted(uint64_t word, uint64_t epoch)
+{
+    return (word ^ (epoch << kTeamCountBits)) >> kTeamCountBits == 0 ? (uint32_t)word & ((1u << kTeamCountBits) - 1u) : 0u;
+}
+
 struct TeamLaunch {
     SweepArgs a;     // a.S, a.t: the state and its MCS
     int64_t n;

@@ -35,10 +35,9 @@ enum Control { kTicket = kFormationWords, kDone = kTicket + 32, kControl = kDone
 __device__ __forceinline__ uint32_t take_ticket(const TeamLaunch& L)
 {
     uint64_t v = peek(L.ctl + kTicket);
-    const uint32_t e = (uint32_t)L.epoch;
     for (;;) {
-        const uint32_t k = (uint32_t)(v >> 32) == e ? (uint32_t)v : 0u;
-        if (__hip_atomic_compare_exchange_strong(L.ctl + kTicket, &v, ((uint64_t)e << 32) | (k + 1u), __ATOMIC_RELAXED,
+        const uint32_t k = team_counted(v, L.epoch);
+        if (__hip_atomic_compare_exchange_strong(L.ctl + kTicket, &v, team_count(L.epoch, k + 1u), __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             return k;
     }
@@ -64,7 +63,7 @@ __device__ void run_apart(const TeamLaunch& L, int parts, uint32_t* s_entry, Pat
         if (tid == 0 && h > 0)
             for (int d = parts - 1; d <= parts + 1; ++d) {
                 patience.begin();
-                while ((int32_t)((uint32_t)peek(L.ctl + kDone + (c + d) % parts) - (L.tag + h)) < 0 && patience.wait()) {
+                while (team_counted(peek(L.ctl + kDone + (c + d) % parts), L.epoch) < h && patience.wait()) {
                 }
             }
         __syncthreads();
@@ -77,7 +76,7 @@ __device__ void run_apart(const TeamLaunch& L, int parts, uint32_t* s_entry, Pat
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
-        if (tid == 0) post(L.ctl + kDone + c, (uint64_t)(L.tag + h + 1u));
+        if (tid == 0) post(L.ctl + kDone + c, team_count(L.epoch, h + 1u));
     }
 }
 

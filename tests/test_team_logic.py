@@ -1,0 +1,23 @@
+"""Host logic of the teams of workgroups (no GPU): the counts by which a launch
+whose team did not form orders its bands."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_1606_00310_amd", "csrc")
+
+
+def test_counts_are_relative_to_the_launch(tmp_path):
+    """A band's progress word holds whatever an earlier launch left, or zero:
+    neither may count as progress, however many half-steps the context has run
+    (a sign test on 32-bit half-step numbers failed past 2^31 of them)."""
+    if shutil.which("g++") is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("g++ or the HIP headers not available")
+    exe = tmp_path / "team_count"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", CSRC,
+                           os.path.join(HERE, "helpers", "team_count.cpp"), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
