@@ -138,11 +138,13 @@ class Server:
             return
         # a backend may collect many at once
         many = getattr(self.backend, "collect_many", None)
-        results = many(finished) if many else map(self.backend.collect, finished)
-        for slot, result in zip(finished, results):
+        results = iter(many(finished) if many else map(self.backend.collect, finished))
+        for slot in finished:
+            # the slot goes first, so that a collection that fails is not tried
+            # again at every step ahead of the slots behind it
             rid, i = self.slot_owner.pop(slot)
             req = self.running[rid]
-            req.results[i] = result
+            req.results[i] = next(results)
             self.backend.release(slot)
             if all(r is not None for r in req.results):
                 req.done = self.now()
