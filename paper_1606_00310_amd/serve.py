@@ -76,7 +76,8 @@ class BatchBackend:
 
     def collect_many(self, slots):
         """collect for each of the slots, with one wait for all their moments."""
-        if type(self).collect is not BatchBackend.collect:  # a subclass collects otherwise
+        # a subclass may collect otherwise, a batch have no collection of many
+        if type(self).collect is not BatchBackend.collect or not hasattr(self.batch, "collect"):
             yield from map(self.collect, slots)
             return
         import torch

@@ -45,3 +45,24 @@ def test_a_failing_collection_fails_once(backend):
         srv.step()
     assert [r.rid for r in srv.completed] == [0, 2, 3, 4, 5]
     assert set(srv.running) == {1}
+
+
+class PlainBatch:
+    """A batch with the calls that one collection at a time takes, and no other."""
+
+    device = "cpu"
+
+    def state(self, slot):
+        import torch
+
+        return torch.full((2, 2, 4, 1), slot), torch.tensor([7 * slot])
+
+    def roughness(self, slot):
+        return 16, slot, slot * slot, 0.5
+
+
+@pytest.mark.parametrize("keep", [True, False])
+def test_collects_from_a_batch_without_collect(keep):
+    got = list(BatchBackend(PlainBatch(), keep_states=keep).collect_many([3, 5]))
+    assert [(r["moments"], r["h0"]) for r in got] == [((16, 3, 9, 0.5), 21), ((16, 5, 25, 0.5), 35)]
+    assert all(("slopes" in r) == keep for r in got)
