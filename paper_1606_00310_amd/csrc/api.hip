@@ -139,6 +139,16 @@ bool may_team(const sca_ctx* c, unsigned flags)
     return c->team_ctl && !team_flag(c, 1) && !(flags & SCA_STEP_GRAPH);
 }
 
+// Whether work enqueued on the stream now becomes part of a graph (or the stream
+// cannot tell).
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 int64_t* ws_col(sca_ctx* c) { return c->ws + 3 * c->Y; }
 int64_t* ws_res(sca_ctx* c) { return c->ws + 4 * c->Y; }
 
@@ -698,15 +708,7 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
     if (c->t + n_mcs > (int64_t)UINT32_MAX) return SCA_EINVAL;
     if (n_mcs == 0) return SCA_OK;
     if (team_flag(c, 0)) return fail(c);
-    bool team = may_team(c, flags);
-    if (team) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
-            (void)hipGetLastError();
-            team = false;
-        }
-        team = team && capture == hipStreamCaptureStatusNone;
-    }
+    const bool team = may_team(c, flags) && !capturing(c->stream);
     if (n_mcs != c->plan_n || p != c->plan_p || q != c->plan_q || flags != c->plan_flags || team != c->plan_team) {
         c->plan = make_plan(c, n_mcs, p, q, flags, team);
         c->plan_n = n_mcs;
@@ -1537,6 +1539,8 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
             ++active;
         }
     }
+    // A graph of an epoch would replay whatever the staging buffers hold by then.
+    if (active > 0 && capturing(b->stream)) return bfail(b);
     // teams that could not form once are not tried again
     const bool apart = *const_cast<const volatile int32_t*>(batch_apart(b)) != 0;
     const int max_parts = std::min(apart ? 1 : sca::kOnChipMaxParts, b->cu_grid);
