@@ -578,11 +578,13 @@ StepPlan make_plan(const sca_ctx* c, int64_t n_mcs, double p, double q, unsigned
 }
 
 // Memory for teams, from 2^25 sites on (below, tiles are faster) up to what the
-// compute units hold.  A context that gets none goes without.
+// compute units hold.  A context that gets none goes without, and so does one
+// whose initialisation is being captured: a graph would clear the words at its
+// launches instead of now.
 void init_team(sca_ctx* c)
 {
     int cus = 0;
-    if (!c->pinned || c->W < 16 || c->X * c->Y < (1ll << 25) ||
+    if (!c->pinned || c->W < 16 || c->X * c->Y < (1ll << 25) || capturing(c->stream) ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess)
         return;
     int parts = sca::kTeamMaxParts;

@@ -21,3 +21,17 @@ for sizes in ([(64, 64)], [(2048, 2048)], [(8192, 8192)], [(64, 64), (2048, 2048
     fake.fake_capturing(0)
 """)
 
+
+def test_a_context_made_under_capture_has_no_teams(host):
+    """The words of its teams would be cleared by the graph's launch, not before
+    the next step."""
+    host("""
+fake.fake_capturing(1)
+c = lattice(8192, 32768)
+assert not launches("team_clear")
+fake.fake_capturing(0)
+assert lib.sca_step(c, 64, 0.5, 0.0) == 0 and not launches("team_kernel")
+c = lattice(8192, 32768)
+assert launches("team_clear")
+assert lib.sca_step(c, 64, 0.5, 0.0) == 0 and launches("team_kernel")
+""")
