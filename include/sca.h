@@ -286,7 +286,8 @@ void sca_destroy(sca_ctx* ctx);
  * same (X, Y, p, q, seed) -- independent of the schedule and configuration.
  * States live in a caller-owned device arena; the library keeps a small
  * table of per-slot descriptors on the device (and, once a realization needs
- * several compute units, 4.2 MB for the messages between them). */
+ * several compute units, 4.4 MB for the messages between them; where there is
+ * no room for those, such realizations go through the second kernel). */
 
 typedef struct sca_batch sca_batch;
 

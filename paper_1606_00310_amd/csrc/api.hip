@@ -1177,6 +1177,7 @@ struct sca_batch {
     int32_t resident = 0;           // workgroups of the captured launch that run at once
     int32_t* d_sync = nullptr;      // barrier counters of split realizations (one per part slot of the grid)
     uint64_t* d_team = nullptr;     // formation, posts and messages of on-chip teams (allocated on first use)
+    bool no_teams = false;          // there was no memory for them
     int32_t cu_grid = 0;            // workgroups of the on-chip launch: one per compute unit, 0 if it does not fit
     int32_t* d_err = nullptr;       // set by a barrier wait that gave up
     int32_t* h_err = nullptr;       // pinned copy of d_err, written after each launch
@@ -1545,9 +1546,8 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     if (active > 0 && capturing(b->stream)) return bfail(b);
     // teams that could not form once are not tried again
     const bool apart = *const_cast<const volatile int32_t*>(batch_apart(b)) != 0;
-    const int max_parts = std::min(apart ? 1 : sca::kOnChipMaxParts, b->cu_grid);
     const int64_t chip_share = b->cu_grid > 0 ? total / (2 * b->cu_grid) : 0;
-    auto chip_parts = [&](const SlotHost& s, int64_t w, int32_t* rows) {
+    auto chip_parts = [&](const SlotHost& s, int64_t w, int max_parts, int32_t* rows) {
         const int Y = (int)s.req.Y;
         for (int32_t P = 1; P <= max_parts; P *= 2) {
             const int N = sca::team_rows(s.W, Y, P);
@@ -1559,32 +1559,52 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         }
         return 0;
     };
-    for (int32_t slot = 0; slot < b->max_slots; ++slot) {
-        SlotHost& s = b->slots[(size_t)slot];
-        if (!s.used) continue;
-        const int64_t run = runs[(size_t)slot], w = run * s.req.X * s.req.Y;
-        sca::BatchDesc d = s.desc;
-        d.t = (uint32_t)s.t;
-        d.n_run = (uint32_t)run;
-        d.depth = 0;
-        d.bands = 0;
-        d.parts = 1;
-        d.sync_idx = 0;
-        d.save = nullptr;
-        if (run > 0) {
-            int32_t rows = 0;
-            const int32_t P = (b->cfg.lds_bytes > 0 && d.mode == 0) ? chip_parts(s, cost(s, run), &rows) : 0;
-            if (P > 0) {
-                d.parts = P;
-                d.bands = rows;
-                chip[sca::kOnChipLevels - 1 - __builtin_ctz((unsigned)P)].emplace_back(cost(s, run), slot);
-            } else {
-                work.emplace_back(w, slot);
-                rest_total += w;
+    // Fills the descriptors and both kinds of lists, with teams of up to max_parts
+    // workgroups; whether there are any.
+    auto place = [&](int max_parts) {
+        bool teams = false;
+        rest_total = 0;
+        hi = -1;
+        work.clear();
+        for (auto& list : chip) list.clear();
+        for (int32_t slot = 0; slot < b->max_slots; ++slot) {
+            SlotHost& s = b->slots[(size_t)slot];
+            if (!s.used) continue;
+            const int64_t run = runs[(size_t)slot], w = run * s.req.X * s.req.Y;
+            sca::BatchDesc d = s.desc;
+            d.t = (uint32_t)s.t;
+            d.n_run = (uint32_t)run;
+            d.depth = 0;
+            d.bands = 0;
+            d.parts = 1;
+            d.sync_idx = 0;
+            d.save = nullptr;
+            if (run > 0) {
+                int32_t rows = 0;
+                const int32_t P =
+                    (b->cfg.lds_bytes > 0 && d.mode == 0) ? chip_parts(s, cost(s, run), max_parts, &rows) : 0;
+                if (P > 0) {
+                    d.parts = P;
+                    d.bands = rows;
+                    chip[sca::kOnChipLevels - 1 - __builtin_ctz((unsigned)P)].emplace_back(cost(s, run), slot);
+                    teams = teams || P > 1;
+                } else {
+                    work.emplace_back(w, slot);
+                    rest_total += w;
+                }
             }
+            b->h_desc[slot] = d;
+            hi = slot;
         }
-        b->h_desc[slot] = d;
-        hi = slot;
+        return teams;
+    };
+    bool teams = place(std::min(apart || b->no_teams ? 1 : sca::kOnChipMaxParts, b->cu_grid));
+    if (teams && !b->d_team &&
+        hipMalloc(&b->d_team, sizeof(uint64_t) * (size_t)sca::onchip_team_words(b->cu_grid)) != hipSuccess) {
+        (void)hipGetLastError();
+        b->d_team = nullptr;
+        b->no_teams = true;
+        teams = place(1);
     }
     const auto longer = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
         return x.first > y.first;
@@ -1651,17 +1671,12 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     const int32_t items = count;
     std::memset(b->h_count, 0, kCounters * sizeof(int32_t));
     b->h_count[kItems] = items;
-    bool teams = false;
     for (int i = 0; i < sca::kOnChipLevels; ++i) {
-        teams = teams || (i < sca::kOnChipLevels - 1 && !chip[i].empty());
         b->h_count[kOnChipCount + i] = (int32_t)chip[i].size();
         for (const auto& w : chip[i]) b->h_order[count++] = w.second;
     }
     if (active_out) *active_out = active;
     if (count == 0) return SCA_OK;
-    if (teams && !b->d_team &&
-        hipMalloc(&b->d_team, sizeof(uint64_t) * (size_t)sca::onchip_team_words(b->cu_grid)) != hipSuccess)
-        return bfail(b);
     if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1), hipMemcpyHostToDevice,
                        b->stream) != hipSuccess ||
         hipMemcpyAsync(b->d_order, b->h_order, sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, b->stream) !=
