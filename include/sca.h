@@ -280,9 +280,8 @@ void sca_destroy(sca_ctx* ctx);
  * for the epoch, the others go through a second, hipGraph-captured persistent
  * kernel.  If other streams' kernels keep the launch's workgroups from running at
  * the same time for a millisecond, realizations that need several compute units
- * run in memory in that epoch and in the second kernel later.  Each realization
- * draws from its own seed with the same counters as the single-lattice path,
- * so its state after any number of MCS is bit-identical to a solo run of the
+ * go through the second kernel, in that epoch and later.  Each realization draws
+ * from its own seed with the same counters as the single-lattice path, so its state after any number of MCS is bit-identical to a solo run of the
  * same (X, Y, p, q, seed) -- independent of the schedule and configuration.
  * States live in a caller-owned device arena; the library keeps a small
  * table of per-slot descriptors on the device (and, once a realization needs

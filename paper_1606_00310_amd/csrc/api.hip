@@ -1173,8 +1173,10 @@ struct sca_batch {
     uint64_t* d_save = nullptr;     // save areas of the blocked passes: grid x save words per workgroup,
                                     // then grid x save words for the parts of split realizations
     size_t save_bytes = 0;
-    int64_t save_words = 0;         // per workgroup (and per part) in the captured graph
-    int32_t resident = 0;           // workgroups of the captured launch that run at once
+    bool prepared = false;          // the next three are up to date with the configuration
+    sca::BatchLaunch launch{};      // the persistent kernel's arguments
+    int64_t save_words = 0;         // per workgroup (and per part)
+    int32_t resident = 0;           // workgroups of that launch that run at once
     int32_t* d_sync = nullptr;      // barrier counters of split realizations (one per part slot of the grid)
     uint64_t* d_team = nullptr;     // formation, posts and messages of on-chip teams (allocated on first use)
     bool no_teams = false;          // there was no memory for them
@@ -1260,23 +1262,18 @@ void batch_free(sca_batch* b)
     delete b;
 }
 
-// (Re)captures the epoch graph: reset the work counter, then the persistent
-// kernel.  The table, order and count are read from device memory, so the
-// graph is reused for every epoch until the configuration changes.
-hipError_t capture_epoch_graph(sca_batch* b)
+// The persistent kernel's arguments in the current configuration, with the save
+// areas that they name (no launch of another configuration is in flight: callers
+// synchronize first).
+void prepare_launch(sca_batch* b)
 {
-    if (b->exec) {
-        (void)hipGraphExecDestroy(b->exec);
-        b->exec = nullptr;
-    }
-    if (!b->capture && hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking) != hipSuccess)
-        return hipErrorUnknown;
+    if (b->prepared) return;
     const int grid = b->num_cus * b->cfg.blocks_per_cu;
     int32_t depth = b->cfg.depth;
     int64_t save_words = sca::blocked_save_words(depth, b->cfg.block_threads);
     // per-workgroup save areas, then as many again for the parts of split realizations
     const size_t need = sizeof(uint64_t) * (size_t)save_words * (size_t)grid * 2;
-    if (need > b->save_bytes) {  // no launch of the old graph is in flight (callers synchronize first)
+    if (need > b->save_bytes) {
         (void)hipFree(b->d_save);
         b->d_save = nullptr;
         b->save_bytes = 0;
@@ -1291,13 +1288,34 @@ hipError_t capture_epoch_graph(sca_batch* b)
     b->save_words = depth > 0 ? save_words : 0;
     const int occ = sca::ensemble_occupancy(b->cfg.block_threads, b->cfg.words_per_lane, b->cfg.lds_bytes, depth);
     b->resident = std::min(grid, occ * b->num_cus);
-    sca::BatchLaunch L{b->d_desc, b->d_order, b->d_counters + kItems, b->d_counters + kQueue, b->cfg.lds_bytes,
-                       depth,     b->d_save,  save_words,    b->d_sync,         grid,
-                       b->d_err};
+    sca::BatchLaunch L{};
+    L.desc = b->d_desc;
+    L.order = b->d_order;
+    L.n_items = b->d_counters + kItems;
+    L.queue = b->d_counters + kQueue;
+    L.lds_bytes = b->cfg.lds_bytes;
+    L.depth = depth;
+    L.save = b->d_save;
+    L.save_words = save_words;
+    L.sync = b->d_sync;
+    L.n_sync = grid;
+    L.err = b->d_err;
+    b->launch = L;
+    b->prepared = true;
+}
+
+// Captures the epoch graph: reset the work counter, then the persistent kernel.
+// The table, order and count are read from device memory, so the graph is reused
+// for every epoch until the configuration changes.
+hipError_t capture_epoch_graph(sca_batch* b)
+{
+    const int grid = b->num_cus * b->cfg.blocks_per_cu;
+    if (!b->capture && hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking) != hipSuccess)
+        return hipErrorUnknown;
     if (hipStreamBeginCapture(b->capture, hipStreamCaptureModeRelaxed) != hipSuccess) return hipErrorUnknown;
     hipError_t e1 = sca::launch_counter_reset(b->d_counters + kQueue, b->d_sync, grid, b->capture);
     if (e1 == hipSuccess)
-        e1 = sca::launch_ensemble(L, b->cfg.block_threads, b->cfg.words_per_lane, grid, b->capture);
+        e1 = sca::launch_ensemble(b->launch, b->cfg.block_threads, b->cfg.words_per_lane, grid, b->capture);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(b->capture, &graph);
     if (e1 != hipSuccess || e2 != hipSuccess || !graph) {
@@ -1345,9 +1363,10 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     }
     // the work queue holds one item per realization, plus one more per extra
     // part of a split realization (at most one part per persistent workgroup
-    // in all, and at most 8 of those per compute unit)
-    const size_t nd = sizeof(sca::BatchDesc) * (size_t)max_slots,
-                 no = sizeof(int32_t) * ((size_t)max_slots + (size_t)b->num_cus * 8);
+    // in all, and at most 8 of those per compute unit); the table and the order
+    // twice, with teams and for when they do not form
+    const size_t nd = 2 * sizeof(sca::BatchDesc) * (size_t)max_slots,
+                 no = 2 * sizeof(int32_t) * ((size_t)max_slots + (size_t)b->num_cus * 8);
     if (hipMalloc(&b->d_desc, nd) != hipSuccess || hipMalloc(&b->d_order, no) != hipSuccess ||
         hipMalloc(&b->d_counters, kCounters * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(&b->d_ws, sizeof(int64_t) * (size_t)(4 * 131072 + 8)) != hipSuccess ||
@@ -1393,6 +1412,7 @@ int sca_batch_set_config(sca_batch* b, const sca_batch_config* cfg)
     // the old graph may still be in flight on the stream
     if (hipStreamSynchronize(b->stream) != hipSuccess) return bfail(b);
     b->cfg = *cfg;
+    b->prepared = false;
     if (b->exec) {
         (void)hipGraphExecDestroy(b->exec);
         b->exec = nullptr;
@@ -1609,76 +1629,102 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     const auto longer = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
         return x.first > y.first;
     };
-    // The save areas and the depth of the captured graph decide which
-    // realizations can run blocked, so the graph is made first.
-    if (!work.empty() && !b->exec && capture_epoch_graph(b) != hipSuccess) return bfail(b);
+    // The save areas and their depth decide which realizations can run blocked.
+    if (!work.empty() || teams) prepare_launch(b);
     const int32_t grid = b->num_cus * b->cfg.blocks_per_cu;
     const int32_t max_depth = b->save_words > 0 ? b->cfg.depth : 0;
-    for (const auto& w : work) {
-        sca::BatchDesc& d = b->h_desc[w.second];
-        const SlotHost& s = b->slots[(size_t)w.second];
-        if (d.mode == 0)
-            (void)sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, 1, &d.depth, &d.bands);
-    }
-    if (b->cfg.order == 0) {
-        std::stable_sort(work.begin(), work.end(), longer);
+    if (b->cfg.order == 0)
         for (auto& list : chip) std::stable_sort(list.begin(), list.end(), longer);
-    }
-    // Realizations that run as temporally blocked passes go first (the
-    // persistent kernel takes them in a phase of their own), and among them
-    // the split ones: a blocked realization with more work than the average
-    // per persistent workgroup runs on parts = the smallest power of two that
+    // The persistent kernel's list of `work` (site updates in all: sum), from
+    // entry `count` of the order on, with its descriptors in `desc`; returns its
+    // length.  Realizations that run as temporally blocked passes go first (the
+    // kernel takes them in a phase of their own), and among them the split
+    // ones: a blocked realization with more work than the average per
+    // persistent workgroup runs on parts = the smallest power of two that
     // brings its share under that average (at most max_parts, as the band
-    // geometry allows), while the parts in all stay within the number of
+    // geometry allows), while the parts in all stay within `room`, a number of
     // persistent workgroups that the device runs at once, so that every part
     // is taken by a running workgroup's first pop.
-    std::stable_partition(work.begin(), work.end(), [b](const std::pair<int64_t, int32_t>& w) {
-        return b->h_desc[w.second].depth > 0;
-    });
-    const int64_t avg = rest_total / grid;
-    int32_t parts_used = 0, n_split = 0;
-    std::vector<std::pair<int64_t, int32_t>> split, rest;
-    for (const auto& w : work) {
-        sca::BatchDesc& d = b->h_desc[w.second];
-        const SlotHost& s = b->slots[(size_t)w.second];
-        int32_t P = 1, K = d.depth, nb = d.bands;
-        if (d.depth > 0 && b->cfg.order == 0)
-            for (int32_t p2 = 2; p2 <= b->cfg.max_parts && w.first / (p2 / 2) > avg; p2 *= 2) {
-                int32_t K2 = 0, nb2 = 0;
-                if (parts_used + p2 > b->resident ||
-                    !sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, p2, &K2, &nb2))
-                    break;
-                P = p2;
-                K = K2;
-                nb = nb2;
-            }
-        if (P > 1) {
-            d.parts = P;
-            d.depth = K;
-            d.bands = nb;
-            d.sync_idx = n_split++;
-            d.save = b->d_save + (size_t)b->save_words * (size_t)(grid + parts_used);
-            parts_used += P;
-            split.push_back(w);
-        } else {
-            rest.push_back(w);
+    int32_t n_split = 0;
+    auto list_work = [&](std::vector<std::pair<int64_t, int32_t>>& work, int64_t sum, int32_t room,
+                         sca::BatchDesc* desc) {
+        for (const auto& w : work) {
+            sca::BatchDesc& d = desc[w.second];
+            const SlotHost& s = b->slots[(size_t)w.second];
+            if (d.mode == 0)
+                (void)sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, 1, &d.depth, &d.bands);
         }
+        if (b->cfg.order == 0) std::stable_sort(work.begin(), work.end(), longer);
+        std::stable_partition(work.begin(), work.end(),
+                              [desc](const std::pair<int64_t, int32_t>& w) { return desc[w.second].depth > 0; });
+        const int64_t avg = sum / grid;
+        int32_t parts_used = 0, split = 0;
+        std::vector<int32_t> rest;
+        const int32_t first = count;
+        for (const auto& w : work) {
+            sca::BatchDesc& d = desc[w.second];
+            const SlotHost& s = b->slots[(size_t)w.second];
+            int32_t P = 1, K = d.depth, nb = d.bands;
+            if (d.depth > 0 && b->cfg.order == 0)
+                for (int32_t p2 = 2; p2 <= b->cfg.max_parts && w.first / (p2 / 2) > avg; p2 *= 2) {
+                    int32_t K2 = 0, nb2 = 0;
+                    if (parts_used + p2 > room ||
+                        !sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, p2, &K2, &nb2))
+                        break;
+                    P = p2;
+                    K = K2;
+                    nb = nb2;
+                }
+            if (P > 1) {
+                d.parts = P;
+                d.depth = K;
+                d.bands = nb;
+                d.sync_idx = split++;
+                d.save = b->d_save + (size_t)b->save_words * (size_t)(grid + parts_used);
+                parts_used += P;
+                for (int32_t m = 0; m < P; ++m) b->h_order[count++] = w.second | (m << sca::kItemSlotBits);
+            } else {
+                rest.push_back(w.second);
+            }
+        }
+        for (const int32_t slot : rest) b->h_order[count++] = slot;
+        n_split += split;
+        return count - first;
+    };
+    // Should the teams not form, everything but the single workgroups' realizations
+    // goes through the persistent kernel: a second table and a second list, split
+    // over half of the workgroups at most, as something else holds others.
+    sca::BatchDesc* const apart_desc = b->h_desc + (hi + 1);
+    std::vector<std::pair<int64_t, int32_t>> apart_work;
+    int64_t apart_total = rest_total;
+    if (teams) {
+        apart_work = work;
+        std::copy(b->h_desc, apart_desc, apart_desc);
+        for (int i = 0; i < sca::kOnChipLevels - 1; ++i)
+            for (const auto& c : chip[i]) {
+                const int32_t slot = c.second;
+                const SlotHost& s = b->slots[(size_t)slot];
+                const int64_t w = runs[(size_t)slot] * s.req.X * s.req.Y;
+                apart_desc[slot].parts = 1;
+                apart_desc[slot].bands = 0;
+                apart_work.emplace_back(w, slot);
+                apart_total += w;
+            }
     }
-    for (const auto& w : split)
-        for (int32_t m = 0; m < b->h_desc[w.second].parts; ++m)
-            b->h_order[count++] = w.second | (m << sca::kItemSlotBits);
-    for (const auto& w : rest) b->h_order[count++] = w.second;
-    const int32_t items = count;
+    const int32_t items = list_work(work, rest_total, b->resident, b->h_desc);
     std::memset(b->h_count, 0, kCounters * sizeof(int32_t));
     b->h_count[kItems] = items;
     for (int i = 0; i < sca::kOnChipLevels; ++i) {
         b->h_count[kOnChipCount + i] = (int32_t)chip[i].size();
         for (const auto& w : chip[i]) b->h_order[count++] = w.second;
     }
+    const bool on_chip = count > items;
+    const int32_t apart_order = count;
+    const int32_t apart_items = teams ? list_work(apart_work, apart_total, b->resident / 2, apart_desc) : 0;
     if (active_out) *active_out = active;
     if (count == 0) return SCA_OK;
-    if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1), hipMemcpyHostToDevice,
-                       b->stream) != hipSuccess ||
+    if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1) * (teams ? 2 : 1),
+                       hipMemcpyHostToDevice, b->stream) != hipSuccess ||
         hipMemcpyAsync(b->d_order, b->h_order, sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, b->stream) !=
             hipSuccess ||
         hipMemcpyAsync(b->d_counters, b->h_count, kCounters * sizeof(int32_t), hipMemcpyHostToDevice, b->stream) !=
@@ -1686,17 +1732,32 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         hipEventRecord(b->staged, b->stream) != hipSuccess)
         return bfail(b);
     b->staged_pending = true;
-    if (count > items) {
+    if (on_chip) {
         const sca::OnChipLaunch L{b->d_desc,
                                   b->d_order + items,
                                   b->d_counters + kOnChipCount,
                                   b->d_counters + kOnChipQueue,
                                   teams ? b->d_team : nullptr,
                                   b->d_err,
-                                  batch_apart(b)};
+                                  b->d_sync,
+                                  teams ? grid : 0};
         if (sca::launch_onchip(L, b->cu_grid, teams, b->stream) != hipSuccess) return bfail(b);
     }
-    if (items > 0 && hipGraphLaunch(b->exec, b->stream) != hipSuccess) return bfail(b);
+    if (teams) {
+        // behind teams, in one launch of this epoch's own: nothing to reset, and the
+        // list is chosen by what became of them
+        sca::BatchLaunch L = b->launch;
+        L.decision = sca::onchip_decision(b->d_team);
+        L.apart_order = apart_order;
+        L.apart_desc = hi + 1;
+        L.apart_items = apart_items;
+        L.apart = batch_apart(b);
+        if (sca::launch_ensemble(L, b->cfg.block_threads, b->cfg.words_per_lane, grid, b->stream) != hipSuccess)
+            return bfail(b);
+    } else if (items > 0) {
+        if (!b->exec && capture_epoch_graph(b) != hipSuccess) return bfail(b);
+        if (hipGraphLaunch(b->exec, b->stream) != hipSuccess) return bfail(b);
+    }
     if ((n_split > 0 || teams) && !b->err_pending) {
         if (hipMemcpyAsync(b->h_err, b->d_err, sizeof(int32_t), hipMemcpyDeviceToHost, b->stream) != hipSuccess ||
             hipEventRecord(b->err_copied, b->stream) != hipSuccess)

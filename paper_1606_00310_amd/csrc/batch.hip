@@ -443,12 +443,12 @@ __device__ __forceinline__ SweepArgs args_of(const BatchDesc& d)
 // The descriptor of an item, moved into scalar registers: it is the same for
 // the whole workgroup, and buffer descriptors built from it must be uniform.
 // *part receives the item's part of a split realization.
-__device__ __forceinline__ BatchDesc load_desc(const BatchLaunch& L, int32_t item, int32_t* part)
+__device__ __forceinline__ BatchDesc load_desc(const BatchDesc* table, const int32_t* order, int32_t item, int32_t* part)
 {
     static_assert(sizeof(BatchDesc) % 4 == 0, "descriptor of whole dwords");
-    const int32_t code = __builtin_amdgcn_readfirstlane(L.order[item]);
+    const int32_t code = __builtin_amdgcn_readfirstlane(order[item]);
     *part = code >> kItemSlotBits;
-    const BatchDesc d = L.desc[code & ((1 << kItemSlotBits) - 1)];
+    const BatchDesc d = table[code & ((1 << kItemSlotBits) - 1)];
     uint32_t w[sizeof(BatchDesc) / 4];
     __builtin_memcpy(w, &d, sizeof(BatchDesc));
 #pragma unroll
@@ -479,7 +479,16 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
     __shared__ int32_t s_item;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int32_t n_items = *L.n_items;
+    int32_t n_items = *L.n_items;
+    const int32_t* order = L.order;
+    const BatchDesc* desc = L.desc;
+    if (L.decision && *L.decision == kOnChipApart) {
+        n_items = L.apart_items;
+        order += L.apart_order;
+        desc += L.apart_desc;
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 
     // Phase 1: realizations that run as temporally blocked passes (the host
     // orders them first, split realizations at the head): passes of d.depth
@@ -489,7 +498,7 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
     int32_t item = next_item(L.queue, &s_item);
     while (item < n_items) {
         int32_t part = 0;
-        const BatchDesc d = load_desc(L, item, &part);
+        const BatchDesc d = load_desc(desc, order, item, &part);
         if (d.depth <= 0) break;
         if (d.n_run > 0) {
             const SweepArgs a = args_of(d);
@@ -511,7 +520,7 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
     // the arena.
     for (; item < n_items; item = next_item(L.queue, &s_item)) {
         int32_t part = 0;
-        const BatchDesc d = load_desc(L, item, &part);
+        const BatchDesc d = load_desc(desc, order, item, &part);
         if (d.n_run == 0) continue;
         SweepArgs a = args_of(d);
         const bool has_q = d.has_q != 0;

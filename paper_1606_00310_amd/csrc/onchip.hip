@@ -12,8 +12,9 @@
 // and posts it to the others.  A wait is therefore for workgroups in the same
 // list of the same team, in lockstep through their messages.  Where the launch's
 // workgroups do not get to run at the same time, the realizations for teams go
-// half-step by half-step in memory, one workgroup each, in a kernel behind this
-// one; the host learns of it and makes no more teams for that ensemble.
+// through the persistent kernel (batch.hip), which is launched behind this one with
+// a second list for that case; the host learns of it and makes no more teams for
+// that ensemble.
 //
 // Bound by vector issue: p = 1/2, 3/4 and 15/16 take some 50, 70 and 110
 // instructions per word and half-step and run at 3.7e13, 2.6e13 and 1.8e13 site
@@ -142,59 +143,11 @@ __global__ __launch_bounds__(kThreads) void onchip_kernel(OnChipLaunch L)
     }
 }
 
-// Half-steps in memory, one workgroup per realization (its n_run MCS).
-template <int G, bool HASQ>
-__device__ __forceinline__ void memory_run(const BatchDesc& d)
+// Zeroes the formation, posts and messages of the last launch, and the barrier
+// counters of the kernel behind this one.
+__global__ __launch_bounds__(256) void onchip_reset_kernel(uint64_t* p, int64_t n, int32_t* sync, int32_t n_sync)
 {
-    SweepArgs a = sweep_args(d);
-    for (uint32_t m = 0; m < d.n_run; ++m, ++a.t)
-        for (a.parity = 0; a.parity < 2; ++a.parity) {
-            for (int r0 = 0; r0 < a.Y; r0 += kThreads / G)
-                halfstep_rows<G, 1, XiMode::Mask, HASQ>(a, d.S, r0 + (int64_t)threadIdx.x / G, (int)threadIdx.x & 63);
-            __syncthreads();
-        }
-}
-
-template <int G>
-__device__ __forceinline__ void memory_run(const BatchDesc& d)
-{
-    if (d.has_q) memory_run<G, true>(d);
-    else memory_run<G, false>(d);
-}
-
-// The realizations meant for teams, if the teams could not form.
-__global__ __launch_bounds__(kThreads) void onchip_apart_kernel(OnChipLaunch L)
-{
-    __shared__ int32_t s_item;
-    if (peek(L.team + kDecision) != 3) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    int32_t first = 0;
-    for (int level = 0; level < kLevels - 1; ++level) {
-        const int32_t count = L.count[level];
-        for (;;) {
-            __syncthreads();
-            if (threadIdx.x == 0) s_item = atomicAdd(L.queue + level, 1);
-            __syncthreads();
-            const int32_t item = __builtin_amdgcn_readfirstlane(s_item);
-            if (item >= count) break;
-            const BatchDesc d = load_desc(L.desc, __builtin_amdgcn_readfirstlane(L.order[first + item]));
-            switch (d.W) {
-            case 1: memory_run<1>(d); break;
-            case 2: memory_run<2>(d); break;
-            case 4: memory_run<4>(d); break;
-            case 8: memory_run<8>(d); break;
-            case 16: memory_run<16>(d); break;
-            case 32: memory_run<32>(d); break;
-            default: memory_run<64>(d); break;
-            }
-        }
-        first += count;
-    }
-}
-
-// Zeroes the formation, posts and messages of the last launch.
-__global__ __launch_bounds__(256) void onchip_reset_kernel(uint64_t* p, int64_t n)
-{
+    for (int32_t k = (int32_t)(blockIdx.x * 256 + threadIdx.x); k < n_sync; k += (int32_t)(gridDim.x * 256)) sync[k] = 0;
     for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) p[k] = 0;
 }
 
@@ -205,18 +158,18 @@ int64_t onchip_team_words(int grid)
     return kFormationWords + mail_words(grid) + (int64_t)(kLevels - 1) * grid * kSlots<1>;
 }
 
+const uint64_t* onchip_decision(const uint64_t* team) { return team + kDecision; }
+
 hipError_t launch_onchip(const OnChipLaunch& L, int grid, bool teams, hipStream_t stream)
 {
     if (teams != (L.team != nullptr)) return hipErrorInvalidValue;
     if (teams) {
-        hipLaunchKernelGGL(onchip_reset_kernel, dim3(256), dim3(256), 0, stream, L.team, onchip_team_words(grid));
+        hipLaunchKernelGGL(onchip_reset_kernel, dim3(256), dim3(256), 0, stream, L.team, onchip_team_words(grid),
+                           L.sync, L.n_sync);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(onchip_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, L);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !teams) return e;
-    hipLaunchKernelGGL(onchip_apart_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, L);
     return hipGetLastError();
 }
 

@@ -135,7 +135,14 @@ struct BatchLaunch {
     int32_t* sync;           // arrival counters of split realizations, zeroed before each launch
     int32_t n_sync;          // number of counters
     int32_t* err;            // set if a barrier wait of a split realization ran out of patience
+    // Behind an on-chip launch with teams: its decision, and the list, which has
+    // the teams' realizations as well, that takes the other's place where it is
+    // kOnChipApart (entries of order and desc to start from, and their number).
+    const uint64_t* decision;  // nullptr: there is one list
+    int32_t apart_order, apart_desc, apart_items;
+    int32_t* apart;            // (host memory) set in that case
 };
+constexpr uint64_t kOnChipApart = 3;
 
 // Save-area words per persistent workgroup (and per part of a split
 // realization) for blocked passes of up to `depth` MCS: each band (one group
@@ -249,9 +256,12 @@ struct OnChipLaunch {
     int32_t* queue;        // [kOnChipLevels] entries taken, 0 before the launch
     uint64_t* team;        // onchip_team_words(grid), nullptr without teams
     int32_t* err;          // set if a wait ran out of patience
-    int32_t* apart;        // (host memory) set if the teams could not form
+    int32_t* sync;         // the barrier counters (n_sync) of the kernel behind a launch with teams, which zeroes them
+    int32_t n_sync;
 };
 int64_t onchip_team_words(int grid);
+// Where a launch with teams leaves whether they formed.
+const uint64_t* onchip_decision(const uint64_t* team);
 // grid: workgroups, at most as many as run at once; teams: a list other than
 // the last has entries.
 hipError_t launch_onchip(const OnChipLaunch& L, int grid, bool teams, hipStream_t stream);

@@ -20,6 +20,7 @@ size_t g_fail_from = 0;    // device allocations of this size or more fail, 0: n
 bool g_capturing = false;  // every stream is being captured
 bool g_apart = false;      // teams do not form
 int g_cus = 256;
+sca::BatchLaunch g_batch{};  // the last one
 
 struct Call {
     dim3 grid, block;
@@ -46,6 +47,15 @@ const char* fake_log() { return g_log.c_str(); }
 void fake_fail_malloc(size_t from) { g_fail_from = from; }
 void fake_capturing(int on) { g_capturing = on != 0; }
 void fake_apart(int on) { g_apart = on != 0; }
+
+// The last launch of the persistent kernel, and what its tables hold.
+int fake_items() { return *g_batch.n_items; }
+int fake_apart_items() { return g_batch.apart_items; }
+int fake_apart_order() { return g_batch.apart_order; }
+int fake_apart_desc() { return g_batch.apart_desc; }
+int fake_order(int k) { return g_batch.order[k]; }
+int fake_parts(int k) { return g_batch.desc[k].parts; }
+int fake_depth(int k) { return g_batch.desc[k].depth; }
 
 void** __hipRegisterFatBinary(const void*) { return reinterpret_cast<void**>(handle()); }
 void __hipUnregisterFatBinary(void**) {}
@@ -79,7 +89,10 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
     } else if (has(name, "onchip_kernel")) {
         const auto* L = static_cast<const sca::OnChipLaunch*>(args[0]);
         more = L->team ? " teams" : " alone";
-        if (L->team && g_apart) *L->apart = 1;
+    } else if (has(name, "ensemble_kernel")) {
+        g_batch = *static_cast<const sca::BatchLaunch*>(args[0]);
+        if (g_batch.decision && g_apart) *g_batch.apart = 1;
+        more = g_batch.decision ? " behind teams" : "";
     }
     say("launch " + name + " grid=" + std::to_string(grid.x) + " block=" + std::to_string(block.x) + more);
     return hipSuccess;
