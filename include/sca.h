@@ -109,12 +109,13 @@ int sca_init(sca_ctx** out, int64_t X, int64_t Y, uint64_t seed, void* slopes_de
  * with or without a buffer.  With a buffer attached, lattices of 2^25 to 2^28
  * sites may run all MCS in one launch and in place, on chip in a team of
  * workgroups, one per compute unit; a team that other streams' kernels keep from
- * forming for a millisecond runs the same half-steps in memory, and the context
- * launches no more of them.  (Not under stream capture.)  The passes come in an even number so that S holds
- * the state when the enqueued work has run: whole passes of `depth` MCS, then
+ * forming for a millisecond runs blocked passes into the pass buffer and back in
+ * that launch, and the context launches no more of them.  (Not under stream
+ * capture.)  The passes come in an even number so that S holds the state when the
+ * enqueued work has run: whole passes of `depth` MCS, then
  * the remainder r as two passes of ceil(r/2) and floor(r/2) MCS, or two
- * half-step launches when r = 1 (sca_plan_step reports the plan).  The results are bit-identical
- * to the two-launch form.  SCA_ENOBUF (nothing enqueued, t unchanged) if X >=
+ * half-step launches when r = 1 (sca_plan_step reports the plan).  The results are
+ * bit-identical to the two-launch form.  SCA_ENOBUF (nothing enqueued, t unchanged) if X >=
  * 8192, a blocked pass is planned and no pass buffer is attached; sca_set_blocking
  * with depth 0 selects the two-launch form, which needs none. */
 int sca_step(sca_ctx* ctx, int64_t n_mcs, double p, double q);
@@ -281,8 +282,9 @@ void sca_destroy(sca_ctx* ctx);
  * kernel.  If other streams' kernels keep the launch's workgroups from running at
  * the same time for a millisecond, realizations that need several compute units
  * go through the second kernel, in that epoch and later.  Each realization draws
- * from its own seed with the same counters as the single-lattice path, so its state after any number of MCS is bit-identical to a solo run of the
- * same (X, Y, p, q, seed) -- independent of the schedule and configuration.
+ * from its own seed with the same counters as the single-lattice path, so its
+ * state after any number of MCS is bit-identical to a solo run of the same
+ * (X, Y, p, q, seed) -- independent of the schedule and configuration.
  * States live in a caller-owned device arena; the library keeps a small
  * table of per-slot descriptors on the device (and, once a realization needs
  * several compute units, 4.4 MB for the messages between them; where there is

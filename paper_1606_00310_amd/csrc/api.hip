@@ -608,6 +608,7 @@ hipError_t launch_team_step(sca_ctx* c, const sca::SweepArgs& a, const StepPlan&
 {
     sca::TeamLaunch L{};
     L.a = a;
+    L.alt = c->alt;
     L.n = n;
     L.ctl = c->team_ctl;
     L.epoch = ++c->team_epoch;

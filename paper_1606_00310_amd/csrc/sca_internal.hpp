@@ -224,15 +224,20 @@ constexpr int64_t kTeamMaxMcs = 1 << 14;
 // nothing in this one: only launches whose team did not form write these words,
 // and any number of others may lie between two of those.
 constexpr int kTeamCountBits = 24;
-static_assert((2 * kTeamMaxMcs + 1) * kTeamMaxParts < 1 << kTeamCountBits, "every half-step of every band has a number");
+static_assert((kTeamMaxMcs + 2) * 2 * kTeamMaxParts < 1 << kTeamCountBits, "every pass of every band has a number");
 __host__ __device__ inline uint64_t team_count(uint64_t epoch, uint32_t n) { return (epoch << kTeamCountBits) | n; }
+__host__ __device__ inline bool team_counts(uint64_t word, uint64_t epoch)
+{
+    return (word ^ (epoch << kTeamCountBits)) >> kTeamCountBits == 0;
+}
 __host__ __device__ inline uint32_t team_counted(uint64_t word, uint64_t epoch)
 {
-    return (word ^ (epoch << kTeamCountBits)) >> kTeamCountBits == 0 ? (uint32_t)word & ((1u << kTeamCountBits) - 1u) : 0u;
+    return team_counts(word, epoch) ? (uint32_t)word & ((1u << kTeamCountBits) - 1u) : 0u;
 }
 
 struct TeamLaunch {
     SweepArgs a;     // a.S, a.t: the state and its MCS
+    uint64_t* alt;   // the pass buffer
     int64_t n;
     uint64_t* ctl;   // team_words(W, parts), zero before the first launch
     uint64_t epoch;  // 1 for the first launch on ctl, 2 for the next, ...

@@ -16,10 +16,10 @@
 // way in and out, the rest until the team has formed.
 //
 // All workgroups have to run at the same time for that (team.hpp).  Apart, they
-// take half-steps of bands of rows in memory from a common list, in an order in
-// which each depends on earlier entries only: any number of workgroups, one after
-// another if need be, completes them.  The host learns of it and launches no more
-// teams for that lattice.
+// take passes over bands of rows from a common list, in an order in which each
+// depends on earlier entries only: any number of workgroups, one after another if
+// need be, completes them.  The host learns of it and launches no more teams for
+// that lattice.
 #include <cstdio>
 
 #include "sca_internal.hpp"
@@ -29,54 +29,128 @@ namespace sca {
 namespace {
 
 // Control words ahead of the messages, each on a line of its own.
-enum Control { kTicket = kFormationWords, kDone = kTicket + 32, kControl = kDone + kTeamMaxParts };
+enum Control { kTicket = kFormationWords, kDone = kTicket + 32, kControl = kDone + 2 * kTeamMaxParts };
 
-// Thread 0: the next entry of the list.
-__device__ __forceinline__ uint32_t take_ticket(const TeamLaunch& L)
+// Thread 0, once: the count of entries taken starts from none.
+__device__ __forceinline__ void begin_tickets(const TeamLaunch& L)
 {
     uint64_t v = peek(L.ctl + kTicket);
-    for (;;) {
-        const uint32_t k = team_counted(v, L.epoch);
-        if (__hip_atomic_compare_exchange_strong(L.ctl + kTicket, &v, team_count(L.epoch, k + 1u), __ATOMIC_RELAXED,
+    while (!team_counts(v, L.epoch))
+        if (__hip_atomic_compare_exchange_strong(L.ctl + kTicket, &v, team_count(L.epoch, 0), __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return k;
-    }
+            break;
 }
 
-// The launch's MCS by half-steps in memory.  Entry k is half-step k / parts of
-// band k % parts; band c needs half-step h-1 of the bands c-1, c and c+1.
-template <int G, int I, bool HASQ>
-__device__ void run_apart(const TeamLaunch& L, int parts, uint32_t* s_entry, Patience& patience)
+// Thread 0: the next entry of the list.  (An addition: with a compare and exchange
+// 255 workgroups that ask at once wait 0.3 to 0.5 ms for each other.)
+__device__ __forceinline__ uint32_t take_ticket(const TeamLaunch& L)
+{
+    return team_counted(
+        __hip_atomic_fetch_add(L.ctl + kTicket, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), L.epoch);
+}
+
+// The launch's MCS as passes over bands of rows, out of place between the lattice
+// and the pass buffer: a tile of as many rows as the threads hold, half of them
+// the band and the rest its halo, which allows rows / 8 MCS per pass.  Entry k is
+// pass k / bands of band k % bands, and pass j of band c needs pass j - 1 of the
+// bands c-1, c and c+1: what it reads, and what still read the rows that it writes.
+// The passes are even in number, so that the last one writes the lattice.
+// One thread per workgroup makes its writes visible and sees the others'; in every
+// wave the fences, each of the XCD's whole L2, would wait for each other.  64 MCS
+// beside a kernel that holds a compute unit, without the wait for the team to form:
+// 2^14 x 2^14 sites at p = 1/2 0.95 ms, as in the row sweeps that the step takes
+// without teams (69 ms half-step by half-step in memory, with fences in every wave);
+// 2^12 x 2^16 1.1 ms (69 ms).
+template <int G, int N, int I, bool HASQ, Draws DR>
+__device__ __forceinline__ void run_apart(const TeamLaunch& L, uint64_t* ly, uint32_t* s_entry, Patience& patience)
 {
     SweepArgs a = L.a;
-    const int R = a.Y / parts;
-    const uint32_t total = 2u * (uint32_t)L.n * (uint32_t)parts;
-    const int tid = (int)threadIdx.x, lane = tid & 63, step = kThreads / G;
+    const int lanes = I > 1 ? 64 : a.W, lg = __builtin_ctz((unsigned)lanes);  // of a row
+    const int groups = kThreads >> lg, rows = groups * N, band = rows / 2, halo = rows / 4;
+    const uint32_t bands = (uint32_t)(a.Y / band), most = (uint32_t)halo / 2;
+    const uint32_t n = (uint32_t)L.n, passes = 2u * ((n + 2u * most - 1u) / (2u * most));
+    const int tid = (int)threadIdx.x, grp = tid >> lg, gl = tid & (lanes - 1), r0 = grp * N;
+    const int w0 = __builtin_amdgcn_readfirstlane(tid);
+    const int wlo = (w0 >> lg) * N, whi = ((w0 + 63) >> lg) * N + N - 1;  // the wave's rows
+    const int64_t P = a.plane;
+
+    TileThread<G, N, I, XiMode::Mask, HASQ, DR, (N * I >= 8)> th;
+    th.rl = RowLanes{lanes, a.nb, gl == 0, gl == lanes - 1, (tid & 32) != 0};
+    th.own = tid;
+    th.nxt = grp + 1 < groups ? tid + lanes : gl;
+    th.stride = kStride;
+    th.kept = ly + 2 * I * kStride + tid;
+    th.W = (uint32_t)a.W;
+    NoEdge edge;
+    if (tid == 0) begin_tickets(L);
     for (;;) {
         __syncthreads();
         if (tid == 0) *s_entry = take_ticket(L);
         __syncthreads();
         const uint32_t k = __builtin_amdgcn_readfirstlane(*s_entry);
-        if (k >= total) break;
-        const uint32_t h = k / (uint32_t)parts;
-        const int c = (int)(k % (uint32_t)parts);
-        if (tid == 0 && h > 0)
-            for (int d = parts - 1; d <= parts + 1; ++d) {
+        if (k >= passes * bands) break;
+        const uint32_t j = k / bands, c = k % bands;
+        if (tid == 0 && j > 0) {
+            for (uint32_t d = bands - 1; d <= bands + 1; ++d) {
                 patience.begin();
-                while (team_counted(peek(L.ctl + kDone + (c + d) % parts), L.epoch) < h && patience.wait()) {
+                while (team_counted(peek(L.ctl + kDone + (c + d) % bands), L.epoch) < j && patience.wait()) {
                 }
             }
-        __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        a.t = L.a.t + h / 2;
-        a.parity = (int)(h & 1u);
-        for (int r0 = 0; r0 < R; r0 += step) {
-            const int r = r0 + tid / G;
-            halfstep_rows<G, I, XiMode::Mask, HASQ>(a, a.S, r < R ? (int64_t)c * R + r : (int64_t)a.Y, lane);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
-        if (tid == 0) post(L.ctl + kDone + c, team_count(L.epoch, h + 1u));
+        const uint32_t m0 = n * j / passes, m1 = n * (j + 1) / passes;  // n passes < 2^27
+        const uint64_t* const src = (j & 1u) ? L.alt : a.S;
+        uint64_t* const dst = (j & 1u) ? a.S : L.alt;
+        const int y0 = ((int)c * band - halo + r0) & (a.Y - 1);
+        th.g0 = (uint32_t)y0 * th.W + (uint32_t)gl;
+        th.lifts = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (i % 2 == 0) th.org[i / 2] = y0 + i == 0 && gl == 0 && r0 + i >= halo && r0 + i < halo + band;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int q = 0; q < I; ++q) {
+                    const int64_t w = (int64_t)th.g(i) + 64 * q;
+                    th.x[i][p][q] = src[(int64_t)p * P + w];
+                    th.y[i][p][q] = src[(int64_t)(2 + p) * P + w];
+                }
+        }
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < I; ++q) ly[(p * I + q) * kStride + tid] = th.y[0][p][q];
+        a.t = L.a.t + m0;
+        int lo = halo - 2 * (int)(m1 - m0), hi = halo + band + 2 * (int)(m1 - m0) - 2;
+        for (uint32_t m = m0; m < m1; ++m, ++a.t) {
+            th.template halfstep<0>(a, ly, lo, hi, whi < lo || wlo > hi, edge);
+            ++lo;
+            --hi;
+            th.template halfstep<1>(a, ly, lo, hi, whi < lo || wlo > hi, edge);
+            ++lo;
+            --hi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < I; ++q) th.y[0][p][q] = ly[(p * I + q) * kStride + tid];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if (r0 + i < halo || r0 + i >= halo + band) continue;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int q = 0; q < I; ++q) {
+                    const int64_t w = (int64_t)th.g(i) + 64 * q;
+                    dst[(int64_t)p * P + w] = th.x[i][p][q];
+                    dst[(int64_t)(2 + p) * P + w] = th.y[i][p][q];
+                }
+        }
+        if (th.lifts != 0) atomicAdd((unsigned long long*)a.h0, (unsigned long long)(2 * (int64_t)th.lifts));
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(L.ctl + kDone + c, team_count(L.epoch, j + 1u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -96,10 +170,7 @@ __global__ __launch_bounds__(kThreads) void team_kernel(TeamLaunch L)
         });
     if (done) return;
     if (threadIdx.x == 0) __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if constexpr (I == 2) run_apart<64, 2, HASQ>(L, parts, &s_word, patience);
-    else if (L.a.W == 64) run_apart<64, 1, HASQ>(L, parts, &s_word, patience);
-    else if (L.a.W == 32) run_apart<32, 1, HASQ>(L, parts, &s_word, patience);
-    else run_apart<16, 1, HASQ>(L, parts, &s_word, patience);
+    run_apart<G, N, I, HASQ, DR>(L, ly, &s_word, patience);
 }
 
 __global__ __launch_bounds__(256) void team_clear_kernel(uint64_t* p, int64_t n)
