@@ -107,8 +107,9 @@ int sca_init(sca_ctx** out, int64_t X, int64_t Y, uint64_t seed, void* slopes_de
  * MCS by about 2*depth.  Lattices with X < 8192 do so only if a pass buffer is
  * attached; small ones may run all MCS in one workgroup instead, in place and
  * with or without a buffer.  With a buffer attached, lattices of 2^25 to 2^28
- * sites may run all MCS in one launch and in place, on chip in a team of
- * workgroups, one per compute unit; a team that other streams' kernels keep from
+ * sites may run up to 512 MCS per launch and in place, on chip in a team of
+ * workgroups, one per compute unit, which such a launch (some milliseconds)
+ * keeps from other streams' kernels; a team that other streams' kernels keep from
  * forming for a millisecond runs blocked passes into the pass buffer and back in
  * that launch, and the context launches no more of them.  (Not under stream
  * capture.)  The passes come in an even number so that S holds the state when the

@@ -216,8 +216,10 @@ inline int team_rows(int W, int64_t Y, int parts)
 // workgroups (4 <= parts <= kTeamMaxParts) of `rows` = team_rows rows per thread.
 // The launches that share `ctl` follow one another on one stream and are not
 // captured: each is given its number.
+// A launch holds every compute unit, so it lasts some milliseconds at most (1.3 ms
+// at 2^25 sites, 3 ms at 2^28, p = 1/2; the state's way in and out is a hundredth).
 constexpr int kTeamMaxParts = 256;
-constexpr int64_t kTeamMaxMcs = 1 << 14;
+constexpr int64_t kTeamMaxMcs = 512;
 
 // Words of `ctl` that count within one launch hold the launch's number (mod
 // 2^40) above the count, so that whatever earlier launches left in them counts

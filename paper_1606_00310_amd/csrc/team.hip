@@ -99,7 +99,7 @@ __device__ __forceinline__ void run_apart(const TeamLaunch& L, uint64_t* ly, uin
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
         __syncthreads();
-        const uint32_t m0 = n * j / passes, m1 = n * (j + 1) / passes;  // n passes < 2^27
+        const uint32_t m0 = n * j / passes, m1 = n * (j + 1) / passes;
         const uint64_t* const src = (j & 1u) ? L.alt : a.S;
         uint64_t* const dst = (j & 1u) ? a.S : L.alt;
         const int y0 = ((int)c * band - halo + r0) & (a.Y - 1);

@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from host_lib import host  # noqa: F401
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_1606_00310_amd", "csrc")
 
@@ -21,3 +23,17 @@ def test_counts_are_relative_to_the_launch(tmp_path):
                            os.path.join(HERE, "helpers", "team_count.cpp"), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+def test_a_launch_is_bounded(host):
+    """A team holds every compute unit for a launch: a long step comes in launches
+    of some milliseconds, between which other streams' kernels get in."""
+    host("""
+c = lattice(16384, 16384)
+log()
+assert lib.sca_step(c, 5000, 0.5, 0.0) == 0
+runs = [dict(w.split("=") for w in l.split() if "=" in w) for l in launches("team_kernel")]
+assert [int(r["t"]) for r in runs] == [sum(int(s["n"]) for s in runs[:i]) for i in range(len(runs))]
+assert sum(int(r["n"]) for r in runs) == 5000 and max(int(r["n"]) for r in runs) <= 512
+assert [int(r["epoch"]) for r in runs] == list(range(1, len(runs) + 1))
+""")
