@@ -110,9 +110,9 @@ int sca_init(sca_ctx** out, int64_t X, int64_t Y, uint64_t seed, void* slopes_de
  * sites may run up to 512 MCS per launch and in place, on chip in a team of
  * workgroups, one per compute unit, which such a launch (some milliseconds)
  * keeps from other streams' kernels; a team that other streams' kernels keep from
- * forming for a millisecond runs blocked passes into the pass buffer and back in
- * that launch, and the context launches no more of them.  (Not under stream
- * capture.)  The passes come in an even number so that S holds the state when the
+ * forming for a quarter of a millisecond runs blocked passes into the pass buffer
+ * and back in that launch, and the context's next 256 steps go without.  (Not
+ * under stream capture.)  The passes come in an even number so that S holds the state when the
  * enqueued work has run: whole passes of `depth` MCS, then
  * the remainder r as two passes of ceil(r/2) and floor(r/2) MCS, or two
  * half-step launches when r = 1 (sca_plan_step reports the plan).  The results are
@@ -281,8 +281,9 @@ void sca_destroy(sca_ctx* ctx);
  * registers of up to sixteen compute units hold (up to 2^24 sites) stay on chip
  * for the epoch, the others go through a second, hipGraph-captured persistent
  * kernel.  If other streams' kernels keep the launch's workgroups from running at
- * the same time for a millisecond, realizations that need several compute units
- * go through the second kernel, in that epoch and later.  Each realization draws
+ * the same time for a quarter of a millisecond, realizations that need several
+ * compute units go through the second kernel, in that epoch and the next 256.
+ * Each realization draws
  * from its own seed with the same counters as the single-lattice path, so its
  * state after any number of MCS is bit-identical to a solo run of the same
  * (X, Y, p, q, seed) -- independent of the schedule and configuration.

@@ -88,6 +88,7 @@ struct sca_ctx {
     int32_t team_parts = 0;
     uint64_t team_epoch = 0;
     uint32_t team_tag = 0;
+    int32_t team_pause = 0;  // steps to go without teams
 };
 
 namespace {
@@ -136,7 +137,19 @@ bool team_flag(const sca_ctx* c, int i)
 // every launch has its number.
 bool may_team(const sca_ctx* c, unsigned flags)
 {
-    return c->team_ctl && !team_flag(c, 1) && !(flags & SCA_STEP_GRAPH);
+    return c->team_ctl && c->team_pause == 0 && !team_flag(c, 1) && !(flags & SCA_STEP_GRAPH);
+}
+
+// A step is on its way: the pause after a team that did not form begins (a launch
+// still under way may set the flag once more) or gets shorter.
+void count_pause(sca_ctx* c)
+{
+    if (team_flag(c, 1)) {
+        reinterpret_cast<volatile int32_t*>(c->pinned + 7)[1] = 0;
+        c->team_pause = sca::kTeamPause;
+    } else if (c->team_pause > 0) {
+        --c->team_pause;
+    }
 }
 
 // Whether work enqueued on the stream now becomes part of a graph (or the stream
@@ -777,6 +790,7 @@ int sca_step_ex(sca_ctx* c, int64_t n_mcs, double p, double q, unsigned flags)
     const hipError_t e = (flags & SCA_STEP_GRAPH) ? run_as_graph(c->capture, c->stream, enqueue) : enqueue(c->stream);
     if (e != hipSuccess) return fail(c);
     c->t += n_mcs;
+    if (c->team_ctl) count_pause(c);
     return SCA_OK;
 }
 
@@ -1181,6 +1195,7 @@ struct sca_batch {
     int32_t* d_sync = nullptr;      // barrier counters of split realizations (one per part slot of the grid)
     uint64_t* d_team = nullptr;     // formation, posts and messages of on-chip teams (allocated on first use)
     bool no_teams = false;          // there was no memory for them
+    int32_t team_pause = 0;         // epochs to go without
     int32_t cu_grid = 0;            // workgroups of the on-chip launch: one per compute unit, 0 if it does not fit
     int32_t* d_err = nullptr;       // set by a barrier wait that gave up
     int32_t* h_err = nullptr;       // pinned copy of d_err, written after each launch
@@ -1565,8 +1580,13 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     }
     // A graph of an epoch would replay whatever the staging buffers hold by then.
     if (active > 0 && capturing(b->stream)) return bfail(b);
-    // teams that could not form once are not tried again
-    const bool apart = *const_cast<const volatile int32_t*>(batch_apart(b)) != 0;
+    // After teams that could not form come epochs without.
+    if (*const_cast<volatile int32_t*>(batch_apart(b)) != 0) {
+        *const_cast<volatile int32_t*>(batch_apart(b)) = 0;
+        b->team_pause = sca::kTeamPause;
+    }
+    const bool apart = b->team_pause > 0;
+    if (apart && active > 0) --b->team_pause;
     const int64_t chip_share = b->cu_grid > 0 ? total / (2 * b->cu_grid) : 0;
     auto chip_parts = [&](const SlotHost& s, int64_t w, int max_parts, int32_t* rows) {
         const int Y = (int)s.req.Y;

@@ -13,8 +13,8 @@
 // list of the same team, in lockstep through their messages.  Where the launch's
 // workgroups do not get to run at the same time, the realizations for teams go
 // through the persistent kernel (batch.hip), which is launched behind this one with
-// a second list for that case; the host learns of it and makes no more teams for
-// that ensemble.
+// a second list for that case; the host learns of it, and that ensemble's next 256
+// epochs go without teams.
 //
 // Bound by vector issue: p = 1/2, 3/4 and 15/16 take some 50, 70 and 110
 // instructions per word and half-step and run at 3.7e13, 2.6e13 and 1.8e13 site

@@ -252,6 +252,11 @@ hipError_t launch_team_clear(uint64_t* ctl, int32_t W, int parts, hipStream_t st
 hipError_t launch_team(const TeamLaunch& L, bool has_q, int parts, int rows, hipStream_t stream);
 void team_kernel_name(const SweepArgs& a, bool has_q, int rows, char* out, size_t n);
 
+// After a launch whose teams did not form, this many steps of the lattice, or
+// epochs of the ensemble, go without.  An attempt in vain costs a quarter of a
+// millisecond, a hundredth of what these take at the smallest sizes.
+constexpr int32_t kTeamPause = 256;
+
 // Realizations that stay on chip for an epoch (onchip.hip): bit-mask mode, in
 // a team of d.parts workgroups with d.bands = team_rows rows per thread.
 constexpr int kOnChipLevels = 5;  // teams of 16, 8, 4, 2 and 1 workgroups

@@ -18,8 +18,8 @@
 // All workgroups have to run at the same time for that (team.hpp).  Apart, they
 // take passes over bands of rows from a common list, in an order in which each
 // depends on earlier entries only: any number of workgroups, one after another if
-// need be, completes them.  The host learns of it and launches no more teams for
-// that lattice.
+// need be, completes them.  The host learns of it, and that lattice's next 256
+// steps go without a team.
 #include <cstdio>
 
 #include "sca_internal.hpp"

@@ -37,3 +37,40 @@ assert [int(r["t"]) for r in runs] == [sum(int(s["n"]) for s in runs[:i]) for i 
 assert sum(int(r["n"]) for r in runs) == 5000 and max(int(r["n"]) for r in runs) <= 512
 assert [int(r["epoch"]) for r in runs] == list(range(1, len(runs) + 1))
 """)
+
+
+def test_teams_are_tried_again(host):
+    """After a launch whose team did not form, 256 steps or epochs go without, and
+    then one tries again."""
+    host("""
+c = lattice(16384, 16384)
+fake.fake_apart(1)
+log()
+teams = []
+for i in range(600):
+    planned = team_planned(c, 64)
+    assert lib.sca_step(c, 64, 0.5, 0.0) == 0
+    ran = len(launches("team_kernel")) > 0
+    assert ran == planned
+    if ran:
+        teams.append(i)
+assert teams == [0, 257, 514]
+fake.fake_apart(0)
+for i in range(600):
+    assert lib.sca_step(c, 64, 0.5, 0.0) == 0
+assert 300 < len(launches("team_kernel")) < 600
+
+e = Ensemble([(2048, 2048), (64, 64)], n_mcs=10**6)
+fake.fake_apart(1)
+log()
+teams = []
+for i in range(600):
+    assert e.run(3) == 0
+    if launches("onchip_kernel")[0].endswith("teams"):
+        teams.append(i)
+assert teams == [0, 257, 514]
+fake.fake_apart(0)
+for i in range(300):
+    assert e.run(3) == 0
+assert e.t(0) == 2700 and [l for l in launches("onchip_kernel") if l.endswith("teams")]
+""")
