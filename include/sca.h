@@ -396,6 +396,12 @@ typedef struct sca_collected {
 } sca_collected;
 int sca_batch_collect(sca_batch* b, const int32_t* slots, int32_t n, sca_collected* out);
 
+/* Test hook: 1 if the next epoch may spread realizations over several compute
+ * units, 0 while it goes without since an earlier launch's workgroups did not
+ * get to run at the same time (known once that launch has run), or since there is
+ * no memory for their messages. */
+int sca_debug_batch_teams(const sca_batch* b);
+
 /* Frees a slot and its arena space (after the enqueued work that uses it). */
 int sca_batch_release(sca_batch* b, int32_t slot);
 

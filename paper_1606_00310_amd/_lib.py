@@ -108,6 +108,7 @@ _SIGNATURES = {
     "sca_batch_slot": ([_vp, ctypes.c_int32, ctypes.POINTER(SlotInfo)], _int),
     "sca_batch_roughness": ([_vp, ctypes.c_int32, _i64p, _dblp], _int),
     "sca_batch_collect": ([_vp, ctypes.POINTER(ctypes.c_int32), ctypes.c_int32, ctypes.POINTER(Collected)], _int),
+    "sca_debug_batch_teams": ([_vp], _int),
     "sca_batch_release": ([_vp, ctypes.c_int32], _int),
     "sca_batch_destroy": ([_vp], None),
 }

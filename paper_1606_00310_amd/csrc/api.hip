@@ -1878,6 +1878,13 @@ int sca_batch_collect(sca_batch* b, const int32_t* slots, int32_t n, sca_collect
     return SCA_OK;
 }
 
+int sca_debug_batch_teams(const sca_batch* b)
+{
+    if (!b) return SCA_EINVAL;
+    return b->cu_grid > 0 && !b->no_teams && b->team_pause == 0 &&
+           *const_cast<const volatile int32_t*>(batch_apart(b)) == 0;
+}
+
 int sca_batch_release(sca_batch* b, int32_t slot)
 {
     if (!b || slot < 0 || slot >= b->max_slots || !b->slots[(size_t)slot].used) return SCA_EINVAL;

@@ -80,3 +80,48 @@ def test_lattice(sca, X, Y, p, q):
                 break
         else:
             raise AssertionError("the team formed every time")
+
+
+# rows of 1 to 64 words, realizations of two to sixteen workgroups, blocked passes
+# for them (rows of 8 words and more) and none; a short one on chip beside them
+ENSEMBLE = [(64, 65536), (128, 32768), (256, 16384), (512, 8192), (1024, 4096), (2048, 2048), (4096, 1024), (8192, 512),
+            (4096, 4096), (8192, 2048)]
+
+
+@pytest.mark.parametrize("X,Y", ENSEMBLE)
+@pytest.mark.parametrize("config", [dict(), dict(block_threads=1024, blocks_per_cu=1, lds_bytes=65536, order=0,
+                                                 words_per_lane=1, depth=2, max_parts=4),
+                                    dict(block_threads=512, blocks_per_cu=1, depth=4, max_parts=2), dict(depth=0)],
+                         ids=["default", "split", "deep", "unblocked"])
+def test_ensemble(sca, X, Y, config):
+    """All is made and the teams have formed once before the unit is held; then an
+    epoch, whose teams cannot form, and one that goes without."""
+    from paper_1606_00310_amd import lib
+    from paper_1606_00310_amd.batch import Batch, Realization as R, state_bytes
+
+    reals = [R(X, Y, 0.5, 0.0, 22, 5), R(X, Y, 0.75, 0.25, 22, 6), R(128, 128, 0.5, 0.0, 22, 7), R(X, Y, 1.0, 0.0, 9, 8),
+             R(X, Y, 0.9375, 0.5, 22, 9)]
+    for tries in range(8):  # a stream may share the ensemble's hardware queue, and then delays it only
+        holder = Holder()
+        b = Batch(max_slots=len(reals), arena_bytes=sum(state_bytes(r.X, r.Y) for r in reals), config=config)
+        slots = b.admit(reals)
+        b.run(4)
+        torch.cuda.synchronize()
+        assert lib().sca_debug_batch_teams(b._b) == 1
+        _say(f"[apart] {X}x{Y} {config} try {tries}")
+        holder.hold()
+        b.run(9)
+        torch.cuda.synchronize()
+        apart = lib().sca_debug_batch_teams(b._b) == 0
+        while b.run(1 << 20):
+            pass
+        for r, s in zip(reals, slots):
+            lat = sca.Lattice(r.X, r.Y, seed=r.seed)
+            lat.step(r.n_mcs, r.p, r.q, fuse=False)
+            S, h0 = b.state(s)
+            assert torch.equal(S, lat.slopes) and (b.info(s).t, int(h0[0])) == lat.meta(), r
+            assert b.roughness(s) == lat.roughness(), r
+        b.close()
+        if apart:
+            return
+    raise AssertionError("the teams formed every time")
