@@ -1153,7 +1153,16 @@ struct SlotHost {
     size_t offset = 0, bytes = 0;
     int64_t t = 0;          // MCS reached once the enqueued epochs have run
     int32_t W = 0, nb = 0;
-    sca::BatchDesc desc{};  // static part; t and n_run are set per epoch
+    int32_t instructions = 0;  // vector instructions per word and half-step, about
+    sca::BatchDesc desc{};     // static part; the rest is set per epoch
+};
+
+// A realization with work in an epoch.
+struct EpochItem {
+    int64_t run, sites, cost;  // MCS, site updates, vector instructions of a lane
+    int32_t slot, W, Y;
+    int32_t parts, rows;       // on chip: workgroups (0: not there) and rows per thread
+    bool mask;
 };
 
 bool valid_req(const sca_req& r)
@@ -1223,6 +1232,10 @@ struct sca_batch {
     bool flat_pending = false;
     hipGraphExec_t exec = nullptr;
     bool failed = false;
+    // an epoch's lists, kept for their memory
+    std::vector<EpochItem> epoch_items;
+    std::vector<std::pair<int64_t, int32_t>> epoch_work, epoch_apart, epoch_chip[sca::kOnChipLevels];
+    std::vector<int32_t> epoch_whole, epoch_plain;
 };
 
 namespace {
@@ -1379,9 +1392,9 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     }
     // the work queue holds one item per realization, plus one more per extra
     // part of a split realization (at most one part per persistent workgroup
-    // in all, and at most 8 of those per compute unit); the table and the order
-    // twice, with teams and for when they do not form
-    const size_t nd = 2 * sizeof(sca::BatchDesc) * (size_t)max_slots,
+    // in all, and at most 8 of those per compute unit); the table has a second
+    // geometry and the order a second list, for teams that do not form
+    const size_t nd = (sizeof(sca::BatchDesc) + sizeof(sca::BlockedGeometry)) * (size_t)max_slots,
                  no = 2 * sizeof(int32_t) * ((size_t)max_slots + (size_t)b->num_cus * 8);
     if (hipMalloc(&b->d_desc, nd) != hipSuccess || hipMalloc(&b->d_order, no) != hipSuccess ||
         hipMalloc(&b->d_counters, kCounters * sizeof(int32_t)) != hipSuccess ||
@@ -1509,6 +1522,8 @@ int sca_batch_admit(sca_batch* b, const sca_req* reqs, int32_t n, int32_t* slots
             d.dig_q = Q.digits;
             d.ndraw = P.n > Q.n ? P.n : Q.n;
         }
+        const int32_t nd = persite ? 32 : d.ndraw;
+        s.instructions = 30 + 10 * d.has_q + 18 * nd + 2 * nd * (1 + d.has_q);
         // states of up to 2^20 words share one launch; larger ones get a launch of their own
         if (4 * d.plane <= ((int64_t)1 << 20)) {
             flat[n_flat++] = sca::flat_item(d.S, r.Y, s.W, s.nb, d.h0);
@@ -1548,10 +1563,39 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     // the staging buffers are free once the previous epoch's copies have run
     if (b->staged_pending && hipEventSynchronize(b->staged) != hipSuccess) return bfail(b);
     b->staged_pending = false;
-    int32_t count = 0, hi = -1;
-    std::vector<std::pair<int64_t, int32_t>> work, chip[sca::kOnChipLevels];
-    std::vector<int64_t> runs((size_t)b->max_slots, 0);
-    int64_t total = 0, rest_total = 0;
+    // The slots with work, in a table of their own: the slots themselves lie far apart.
+    auto& items = b->epoch_items;
+    items.clear();
+    int32_t hi = -1;
+    int64_t total = 0;
+    for (int32_t slot = 0; slot < b->max_slots; ++slot) {
+        const SlotHost& s = b->slots[(size_t)slot];
+        if (!s.used) continue;
+        const int64_t run = std::min(mcs_of(s), s.req.n_mcs - s.t);
+        if (run <= 0) continue;
+        EpochItem it;
+        it.slot = hi = slot;
+        it.W = s.W;
+        it.Y = (int32_t)s.req.Y;
+        it.mask = s.desc.mode == 0;
+        it.run = run;
+        it.sites = run * s.req.X * s.req.Y;
+        it.cost = run * s.req.Y * s.W * s.instructions;
+        total += it.cost;
+        items.push_back(it);
+    }
+    if (active_out) *active_out = (int32_t)items.size();
+    if (items.empty()) return SCA_OK;
+    // A graph of an epoch would replay whatever the staging buffers hold by then.
+    if (capturing(b->stream)) return bfail(b);
+    // After teams that could not form come epochs without.
+    volatile int32_t* const apart = batch_apart(b);
+    if (*apart != 0) {
+        *apart = 0;
+        b->team_pause = sca::kTeamPause;
+    }
+    const bool paused = b->team_pause > 0;
+    if (paused) --b->team_pause;
     // On chip (unless the configuration keeps states in the arena) go the
     // bit-mask realizations that up to sixteen workgroups hold, with as few
     // workgroups as do, or more where each would have more than half of the
@@ -1560,92 +1604,59 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     // those of p = 1/2 per site).  512 realizations of 2^6 to 2^11 squared: 3.6 ms;
     // with a whole average as the line 4.4 ms, with a third or a sixth of it 1.5
     // and 5 % more, with sites for work and a whole average 5.2 ms.
-    auto cost = [](const SlotHost& s, int64_t run) {
-        const int64_t nd = s.desc.mode == 0 ? s.desc.ndraw : 32, q = s.desc.has_q;
-        return run * s.req.Y * s.W * (30 + 10 * q + 18 * nd + 2 * nd * (1 + q));
-    };
-    int32_t active = 0;
-    for (int32_t slot = 0; slot < b->max_slots; ++slot) {
-        SlotHost& s = b->slots[(size_t)slot];
-        if (!s.used) continue;
-        const int64_t left = s.req.n_mcs - s.t;
-        int64_t run = mcs_of(s);
-        if (run > left) run = left;
-        if (run < 0) run = 0;
-        runs[(size_t)slot] = run;
-        if (run > 0) {
-            total += cost(s, run);
-            ++active;
-        }
-    }
-    // A graph of an epoch would replay whatever the staging buffers hold by then.
-    if (active > 0 && capturing(b->stream)) return bfail(b);
-    // After teams that could not form come epochs without.
-    if (*const_cast<volatile int32_t*>(batch_apart(b)) != 0) {
-        *const_cast<volatile int32_t*>(batch_apart(b)) = 0;
-        b->team_pause = sca::kTeamPause;
-    }
-    const bool apart = b->team_pause > 0;
-    if (apart && active > 0) --b->team_pause;
     const int64_t chip_share = b->cu_grid > 0 ? total / (2 * b->cu_grid) : 0;
-    auto chip_parts = [&](const SlotHost& s, int64_t w, int max_parts, int32_t* rows) {
-        const int Y = (int)s.req.Y;
-        for (int32_t P = 1; P <= max_parts; P *= 2) {
-            const int N = sca::team_rows(s.W, Y, P);
-            if (N == 0) continue;
-            const bool more = b->cfg.order == 0 && w / P > chip_share && N > 2 && 2 * P <= max_parts;
-            if (more && sca::team_rows(s.W, Y, 2 * P) > 0) continue;
-            *rows = N;
-            return P;
-        }
-        return 0;
-    };
-    // Fills the descriptors and both kinds of lists, with teams of up to max_parts
-    // workgroups; whether there are any.
-    auto place = [&](int max_parts) {
+    auto place = [&](int max_parts) {  // whether there are teams
         bool teams = false;
-        rest_total = 0;
-        hi = -1;
-        work.clear();
-        for (auto& list : chip) list.clear();
-        for (int32_t slot = 0; slot < b->max_slots; ++slot) {
-            SlotHost& s = b->slots[(size_t)slot];
-            if (!s.used) continue;
-            const int64_t run = runs[(size_t)slot], w = run * s.req.X * s.req.Y;
-            sca::BatchDesc d = s.desc;
-            d.t = (uint32_t)s.t;
-            d.n_run = (uint32_t)run;
-            d.depth = 0;
-            d.bands = 0;
-            d.parts = 1;
-            d.sync_idx = 0;
-            d.save = nullptr;
-            if (run > 0) {
-                int32_t rows = 0;
-                const int32_t P =
-                    (b->cfg.lds_bytes > 0 && d.mode == 0) ? chip_parts(s, cost(s, run), max_parts, &rows) : 0;
-                if (P > 0) {
-                    d.parts = P;
-                    d.bands = rows;
-                    chip[sca::kOnChipLevels - 1 - __builtin_ctz((unsigned)P)].emplace_back(cost(s, run), slot);
-                    teams = teams || P > 1;
-                } else {
-                    work.emplace_back(w, slot);
-                    rest_total += w;
-                }
+        for (EpochItem& it : items) {
+            it.parts = 0;
+            if (b->cfg.lds_bytes == 0 || !it.mask) continue;
+            for (int32_t P = 1; P <= max_parts; P *= 2) {
+                const int N = sca::team_rows(it.W, it.Y, P);
+                if (N == 0) continue;
+                const bool more = b->cfg.order == 0 && it.cost / P > chip_share && N > 2 && 2 * P <= max_parts;
+                if (more && sca::team_rows(it.W, it.Y, 2 * P) > 0) continue;
+                it.parts = P;
+                it.rows = N;
+                teams = teams || P > 1;
+                break;
             }
-            b->h_desc[slot] = d;
-            hi = slot;
         }
         return teams;
     };
-    bool teams = place(std::min(apart || b->no_teams ? 1 : sca::kOnChipMaxParts, b->cu_grid));
+    bool teams = place(std::min(paused || b->no_teams ? 1 : sca::kOnChipMaxParts, b->cu_grid));
     if (teams && !b->d_team &&
         hipMalloc(&b->d_team, sizeof(uint64_t) * (size_t)sca::onchip_team_words(b->cu_grid)) != hipSuccess) {
         (void)hipGetLastError();
         b->d_team = nullptr;
         b->no_teams = true;
         teams = place(1);
+    }
+    // The lists, as items with a key: on chip by size of team, the persistent
+    // kernel's, and, should the teams not form, its list with everything but the
+    // single workgroups' realizations.
+    auto &work = b->epoch_work, &apart_work = b->epoch_apart;
+    work.clear();
+    apart_work.clear();
+    for (auto& list : b->epoch_chip) list.clear();
+    int64_t work_total = 0, apart_total = 0;
+    for (int32_t i = 0; i < (int32_t)items.size(); ++i) {
+        const EpochItem& it = items[(size_t)i];
+        const SlotHost& s = b->slots[(size_t)it.slot];
+        sca::BatchDesc& d = b->h_desc[it.slot];
+        d = s.desc;
+        d.t = (uint32_t)s.t;
+        d.n_run = (uint32_t)it.run;
+        d.geo = sca::BlockedGeometry{0, it.parts > 0 ? it.rows : 0, std::max(it.parts, 1), 0, nullptr};
+        if (it.parts > 0) {
+            b->epoch_chip[sca::kOnChipLevels - 1 - __builtin_ctz((unsigned)it.parts)].emplace_back(it.cost, i);
+        } else {
+            work.emplace_back(it.sites, i);
+            work_total += it.sites;
+        }
+        if (teams && it.parts != 1) {
+            apart_work.emplace_back(it.sites, i);
+            apart_total += it.sites;
+        }
     }
     const auto longer = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
         return x.first > y.first;
@@ -1654,11 +1665,9 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     if (!work.empty() || teams) prepare_launch(b);
     const int32_t grid = b->num_cus * b->cfg.blocks_per_cu;
     const int32_t max_depth = b->save_words > 0 ? b->cfg.depth : 0;
-    if (b->cfg.order == 0)
-        for (auto& list : chip) std::stable_sort(list.begin(), list.end(), longer);
-    // The persistent kernel's list of `work` (site updates in all: sum), from
-    // entry `count` of the order on, with its descriptors in `desc`; returns its
-    // length.  Realizations that run as temporally blocked passes go first (the
+    // The persistent kernel's list of `list` (site updates in all: sum) into `order`;
+    // returns its length.  geometry(slot) is where the realization's goes.
+    // Realizations that run as temporally blocked passes go first (the
     // kernel takes them in a phase of their own), and among them the split
     // ones: a blocked realization with more work than the average per
     // persistent workgroup runs on parts = the smallest power of two that
@@ -1667,85 +1676,68 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     // persistent workgroups that the device runs at once, so that every part
     // is taken by a running workgroup's first pop.
     int32_t n_split = 0;
-    auto list_work = [&](std::vector<std::pair<int64_t, int32_t>>& work, int64_t sum, int32_t room,
-                         sca::BatchDesc* desc) {
-        for (const auto& w : work) {
-            sca::BatchDesc& d = desc[w.second];
-            const SlotHost& s = b->slots[(size_t)w.second];
-            if (d.mode == 0)
-                (void)sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, 1, &d.depth, &d.bands);
-        }
-        if (b->cfg.order == 0) std::stable_sort(work.begin(), work.end(), longer);
-        std::stable_partition(work.begin(), work.end(),
-                              [desc](const std::pair<int64_t, int32_t>& w) { return desc[w.second].depth > 0; });
+    auto list_work = [&](std::vector<std::pair<int64_t, int32_t>>& list, int64_t sum, int32_t room, int32_t* order,
+                         auto&& geometry) {
+        if (b->cfg.order == 0) std::stable_sort(list.begin(), list.end(), longer);
         const int64_t avg = sum / grid;
-        int32_t parts_used = 0, split = 0;
-        std::vector<int32_t> rest;
-        const int32_t first = count;
-        for (const auto& w : work) {
-            sca::BatchDesc& d = desc[w.second];
-            const SlotHost& s = b->slots[(size_t)w.second];
-            int32_t P = 1, K = d.depth, nb = d.bands;
-            if (d.depth > 0 && b->cfg.order == 0)
+        int32_t parts_used = 0, split = 0, n = 0;
+        auto &whole = b->epoch_whole, &plain = b->epoch_plain;
+        whole.clear();
+        plain.clear();
+        for (const auto& w : list) {
+            const EpochItem& it = items[(size_t)w.second];
+            sca::BlockedGeometry g{0, 0, 1, 0, nullptr};
+            if (it.mask)
+                (void)sca::blocked_plan(it.W, it.Y, max_depth, b->cfg.block_threads, 1, &g.depth, &g.bands);
+            if (g.depth > 0 && b->cfg.order == 0)
                 for (int32_t p2 = 2; p2 <= b->cfg.max_parts && w.first / (p2 / 2) > avg; p2 *= 2) {
                     int32_t K2 = 0, nb2 = 0;
                     if (parts_used + p2 > room ||
-                        !sca::blocked_plan(s.W, (int)s.req.Y, max_depth, b->cfg.block_threads, p2, &K2, &nb2))
+                        !sca::blocked_plan(it.W, it.Y, max_depth, b->cfg.block_threads, p2, &K2, &nb2))
                         break;
-                    P = p2;
-                    K = K2;
-                    nb = nb2;
+                    g.parts = p2;
+                    g.depth = K2;
+                    g.bands = nb2;
                 }
-            if (P > 1) {
-                d.parts = P;
-                d.depth = K;
-                d.bands = nb;
-                d.sync_idx = split++;
-                d.save = b->d_save + (size_t)b->save_words * (size_t)(grid + parts_used);
-                parts_used += P;
-                for (int32_t m = 0; m < P; ++m) b->h_order[count++] = w.second | (m << sca::kItemSlotBits);
+            if (g.parts > 1) {
+                g.sync_idx = split++;
+                g.save = b->d_save + (size_t)b->save_words * (size_t)(grid + parts_used);
+                parts_used += g.parts;
+                for (int32_t m = 0; m < g.parts; ++m) order[n++] = it.slot | (m << sca::kItemSlotBits);
             } else {
-                rest.push_back(w.second);
+                (g.depth > 0 ? whole : plain).push_back(it.slot);
             }
+            geometry(it.slot) = g;
         }
-        for (const int32_t slot : rest) b->h_order[count++] = slot;
+        for (const int32_t slot : whole) order[n++] = slot;
+        for (const int32_t slot : plain) order[n++] = slot;
         n_split += split;
-        return count - first;
+        return n;
     };
-    // Should the teams not form, everything but the single workgroups' realizations
-    // goes through the persistent kernel: a second table and a second list, split
-    // over half of the workgroups at most, as something else holds others.
-    sca::BatchDesc* const apart_desc = b->h_desc + (hi + 1);
-    std::vector<std::pair<int64_t, int32_t>> apart_work;
-    int64_t apart_total = rest_total;
-    if (teams) {
-        apart_work = work;
-        std::copy(b->h_desc, apart_desc, apart_desc);
-        for (int i = 0; i < sca::kOnChipLevels - 1; ++i)
-            for (const auto& c : chip[i]) {
-                const int32_t slot = c.second;
-                const SlotHost& s = b->slots[(size_t)slot];
-                const int64_t w = runs[(size_t)slot] * s.req.X * s.req.Y;
-                apart_desc[slot].parts = 1;
-                apart_desc[slot].bands = 0;
-                apart_work.emplace_back(w, slot);
-                apart_total += w;
-            }
-    }
-    const int32_t items = list_work(work, rest_total, b->resident, b->h_desc);
+    const int32_t n_work = list_work(work, work_total, b->resident, b->h_order,
+                                     [b](int32_t slot) -> sca::BlockedGeometry& { return b->h_desc[slot].geo; });
+    int32_t count = n_work;
     std::memset(b->h_count, 0, kCounters * sizeof(int32_t));
-    b->h_count[kItems] = items;
+    b->h_count[kItems] = n_work;
     for (int i = 0; i < sca::kOnChipLevels; ++i) {
-        b->h_count[kOnChipCount + i] = (int32_t)chip[i].size();
-        for (const auto& w : chip[i]) b->h_order[count++] = w.second;
+        auto& list = b->epoch_chip[i];
+        if (b->cfg.order == 0) std::stable_sort(list.begin(), list.end(), longer);
+        b->h_count[kOnChipCount + i] = (int32_t)list.size();
+        for (const auto& w : list) b->h_order[count++] = items[(size_t)w.second].slot;
     }
-    const bool on_chip = count > items;
+    const bool on_chip = count > n_work;
+    // Should the teams not form: split over half of the workgroups at most, as
+    // something else holds others.  The geometries follow the table.
     const int32_t apart_order = count;
-    const int32_t apart_items = teams ? list_work(apart_work, apart_total, b->resident / 2, apart_desc) : 0;
-    if (active_out) *active_out = active;
-    if (count == 0) return SCA_OK;
-    if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1) * (teams ? 2 : 1),
-                       hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+    auto* const geometries = reinterpret_cast<sca::BlockedGeometry*>(b->h_desc + (hi + 1));
+    const int32_t apart_items =
+        teams ? list_work(apart_work, apart_total, b->resident / 2, b->h_order + count,
+                          [geometries](int32_t slot) -> sca::BlockedGeometry& { return geometries[slot]; })
+              : 0;
+    count += apart_items;
+    const size_t table =
+        (sizeof(sca::BatchDesc) + (teams ? sizeof(sca::BlockedGeometry) : 0)) * (size_t)(hi + 1);
+    if (hipMemcpyAsync(b->d_desc, b->h_desc, table, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
         hipMemcpyAsync(b->d_order, b->h_order, sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, b->stream) !=
             hipSuccess ||
         hipMemcpyAsync(b->d_counters, b->h_count, kCounters * sizeof(int32_t), hipMemcpyHostToDevice, b->stream) !=
@@ -1755,7 +1747,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
     b->staged_pending = true;
     if (on_chip) {
         const sca::OnChipLaunch L{b->d_desc,
-                                  b->d_order + items,
+                                  b->d_order + n_work,
                                   b->d_counters + kOnChipCount,
                                   b->d_counters + kOnChipQueue,
                                   teams ? b->d_team : nullptr,
@@ -1769,13 +1761,13 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         // list is chosen by what became of them
         sca::BatchLaunch L = b->launch;
         L.decision = sca::onchip_decision(b->d_team);
-        L.apart_order = apart_order;
-        L.apart_desc = hi + 1;
+        L.apart_order = b->d_order + apart_order;
+        L.apart_geometry = reinterpret_cast<const sca::BlockedGeometry*>(b->d_desc + (hi + 1));
         L.apart_items = apart_items;
         L.apart = batch_apart(b);
         if (sca::launch_ensemble(L, b->cfg.block_threads, b->cfg.words_per_lane, grid, b->stream) != hipSuccess)
             return bfail(b);
-    } else if (items > 0) {
+    } else if (n_work > 0) {
         if (!b->exec && capture_epoch_graph(b) != hipSuccess) return bfail(b);
         if (hipGraphLaunch(b->exec, b->stream) != hipSuccess) return bfail(b);
     }
@@ -1785,8 +1777,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
             return bfail(b);
         b->err_pending = true;
     }
-    for (int32_t slot = 0; slot < b->max_slots; ++slot)
-        if (b->slots[(size_t)slot].used) b->slots[(size_t)slot].t += runs[(size_t)slot];
+    for (const EpochItem& it : items) b->slots[(size_t)it.slot].t += it.run;
     return SCA_OK;
 }
 
@@ -1797,19 +1788,27 @@ extern "C" {
 int sca_batch_run(sca_batch* b, int64_t mcs_epoch, int32_t* active_out)
 {
     if (!b || mcs_epoch < 0) return SCA_EINVAL;
-    return batch_epoch(b, [mcs_epoch](const SlotHost&) { return mcs_epoch; }, active_out);
+    try {
+        return batch_epoch(b, [mcs_epoch](const SlotHost&) { return mcs_epoch; }, active_out);
+    } catch (const std::bad_alloc&) {  // of its lists, ahead of every launch
+        return SCA_ENOMEM;
+    }
 }
 
 int sca_batch_run_work(sca_batch* b, int64_t site_updates, int32_t* active_out)
 {
     if (!b || site_updates <= 0) return SCA_EINVAL;
-    return batch_epoch(
-        b,
-        [site_updates](const SlotHost& s) {
-            const int64_t q = site_updates / (s.req.X * s.req.Y);
-            return q > 0 ? q : (int64_t)1;
-        },
-        active_out);
+    try {
+        return batch_epoch(
+            b,
+            [site_updates](const SlotHost& s) {
+                const int64_t q = site_updates / (s.req.X * s.req.Y);
+                return q > 0 ? q : (int64_t)1;
+            },
+            active_out);
+    } catch (const std::bad_alloc&) {
+        return SCA_ENOMEM;
+    }
 }
 
 int sca_batch_slot(const sca_batch* b, int32_t slot, sca_slot_info* out)

@@ -440,15 +440,23 @@ __device__ __forceinline__ SweepArgs args_of(const BatchDesc& d)
     return a;
 }
 
+// The list in use, kept in LDS: in registers its pointers would spill others.
+struct EpochList {
+    const int32_t* order;
+    const BlockedGeometry* geometry;  // nullptr: the descriptors'
+};
+
 // The descriptor of an item, moved into scalar registers: it is the same for
 // the whole workgroup, and buffer descriptors built from it must be uniform.
 // *part receives the item's part of a split realization.
-__device__ __forceinline__ BatchDesc load_desc(const BatchDesc* table, const int32_t* order, int32_t item, int32_t* part)
+__device__ __forceinline__ BatchDesc load_desc(const BatchLaunch& L, const EpochList* list, int32_t item, int32_t* part)
 {
     static_assert(sizeof(BatchDesc) % 4 == 0, "descriptor of whole dwords");
-    const int32_t code = __builtin_amdgcn_readfirstlane(order[item]);
+    const int32_t code = __builtin_amdgcn_readfirstlane(list->order[item]);
     *part = code >> kItemSlotBits;
-    const BatchDesc d = table[code & ((1 << kItemSlotBits) - 1)];
+    const int32_t slot = code & ((1 << kItemSlotBits) - 1);
+    BatchDesc d = L.desc[slot];
+    if (list->geometry) d.geo = list->geometry[slot];
     uint32_t w[sizeof(BatchDesc) / 4];
     __builtin_memcpy(w, &d, sizeof(BatchDesc));
 #pragma unroll
@@ -477,40 +485,38 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
     constexpr int NWAVES = BLOCK / 64;
     extern __shared__ uint64_t lds[];
     __shared__ int32_t s_item;
+    __shared__ EpochList s_list;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     int32_t n_items = *L.n_items;
-    const int32_t* order = L.order;
-    const BatchDesc* desc = L.desc;
-    if (L.decision && *L.decision == kOnChipApart) {
-        n_items = L.apart_items;
-        order += L.apart_order;
-        desc += L.apart_desc;
-        if (blockIdx.x == 0 && threadIdx.x == 0)
-            __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    const bool apart = L.decision && *L.decision == kOnChipApart;
+    if (apart) n_items = L.apart_items;
+    if (threadIdx.x == 0) {
+        s_list = {apart ? L.apart_order : L.order, apart ? L.apart_geometry : nullptr};
+        if (apart && blockIdx.x == 0) __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 
     // Phase 1: realizations that run as temporally blocked passes (the host
-    // orders them first, split realizations at the head): passes of d.depth
+    // orders them first, split realizations at the head): passes of d.geo.depth
     // MCS, and one of a single MCS for an odd remainder.  The first other
     // item moves the workgroup on to phase 2, which handles any realization.
     // Keeping the two loops apart keeps their register needs apart.
     int32_t item = next_item(L.queue, &s_item);
     while (item < n_items) {
         int32_t part = 0;
-        const BatchDesc d = load_desc(desc, order, item, &part);
-        if (d.depth <= 0) break;
+        const BatchDesc d = load_desc(L, &s_list, item, &part);
+        if (d.geo.depth <= 0) break;
         if (d.n_run > 0) {
             const SweepArgs a = args_of(d);
             const bool has_q = d.has_q != 0;
-            uint64_t* save = d.parts > 1 ? d.save : L.save + (int64_t)blockIdx.x * L.save_words;
-            PartSync ps{d.parts > 1 ? L.sync + d.sync_idx : nullptr, d.parts, 0, L.err, false};
-            const int nbt = d.bands * d.parts, b0 = part * d.bands;
-            const int npass = (int)(d.n_run / (uint32_t)d.depth);
-            if (npass > 0) blocked_dispatch<MAXK>(a, d.S, save, d.t, npass, d.bands, b0, nbt, d.depth, has_q, ps);
-            const uint32_t done = (uint32_t)npass * (uint32_t)d.depth;
+            uint64_t* save = d.geo.parts > 1 ? d.geo.save : L.save + (int64_t)blockIdx.x * L.save_words;
+            PartSync ps{d.geo.parts > 1 ? L.sync + d.geo.sync_idx : nullptr, d.geo.parts, 0, L.err, false};
+            const int nbt = d.geo.bands * d.geo.parts, b0 = part * d.geo.bands;
+            const int npass = (int)(d.n_run / (uint32_t)d.geo.depth);
+            if (npass > 0) blocked_dispatch<MAXK>(a, d.S, save, d.t, npass, d.geo.bands, b0, nbt, d.geo.depth, has_q, ps);
+            const uint32_t done = (uint32_t)npass * (uint32_t)d.geo.depth;
             if (done < d.n_run)
-                blocked_dispatch<MAXK>(a, d.S, save, d.t + done, (int)(d.n_run - done), d.bands, b0, nbt, 1, has_q,
+                blocked_dispatch<MAXK>(a, d.S, save, d.t + done, (int)(d.n_run - done), d.geo.bands, b0, nbt, 1, has_q,
                                        ps);
         }
         item = next_item(L.queue, &s_item);
@@ -520,7 +526,7 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
     // the arena.
     for (; item < n_items; item = next_item(L.queue, &s_item)) {
         int32_t part = 0;
-        const BatchDesc d = load_desc(desc, order, item, &part);
+        const BatchDesc d = load_desc(L, &s_list, item, &part);
         if (d.n_run == 0) continue;
         SweepArgs a = args_of(d);
         const bool has_q = d.has_q != 0;

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads) void onchip_kernel(OnChipLaunch L)
             const int32_t item = __builtin_amdgcn_readfirstlane(s_item);
             if (item >= count) break;
             const BatchDesc d = load_desc(L.desc, __builtin_amdgcn_readfirstlane(L.order[first + item]));
-            switch (d.bands) {
+            switch (d.geo.bands) {
             case 2: run_rows<2>(d, xch, ly, parts, member, tag, patience); break;
             case 4: run_rows<4>(d, xch, ly, parts, member, tag, patience); break;
             default: run_rows<8>(d, xch, ly, parts, member, tag, patience); break;

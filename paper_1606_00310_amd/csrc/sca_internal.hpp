@@ -91,6 +91,21 @@ hipError_t launch_column(const uint64_t* S, const int64_t* h0, int64_t Y, int32_
 hipError_t launch_heights(const uint64_t* S, int64_t X, int64_t Y, int32_t W, const int64_t* col, int64_t y0,
                           int64_t ny, int32_t* out, hipStream_t stream);
 
+// The temporally blocked passes (phase 1 of the persistent kernel) of one
+// realization in an epoch, set by the host: depth > 0 runs passes of `depth` MCS on
+// bands of one group of W lanes each, `bands` bands per workgroup; a realization
+// split into parts > 1 runs on as many workgroups (part m owns bands m*bands ..
+// (m+1)*bands-1) that meet at a barrier on counter sync[sync_idx] and keep their
+// band save slots in `save` (contiguous for all parts); parts == 1 uses the
+// workgroup's own save area.  (On chip: parts workgroups, bands rows per thread.)
+struct BlockedGeometry {
+    int32_t depth;
+    int32_t bands;
+    int32_t parts;
+    int32_t sync_idx;
+    uint64_t* save;
+};
+
 // One realization of an ensemble epoch (device table, one entry per slot).
 struct BatchDesc {
     uint64_t* S;       // state S[2][2][Y][W] in the arena
@@ -106,18 +121,7 @@ struct BatchDesc {
     uint64_t all_p, all_q;
     uint32_t t;        // MCS index at the start of the epoch
     uint32_t n_run;    // MCS to advance in this epoch (0: skip)
-    // Temporally blocked passes (phase 1 of the persistent kernel), set by
-    // the host per epoch: depth > 0 runs passes of `depth` MCS on bands of
-    // one group of W lanes each, `bands` bands per workgroup; a realization
-    // split into parts > 1 runs on as many workgroups (part m owns bands
-    // m*bands .. (m+1)*bands-1) that meet at a barrier on counter
-    // sync[sync_idx] and keep their band save slots in `save` (contiguous
-    // for all parts); parts == 1 uses the workgroup's own save area.
-    int32_t depth;
-    int32_t bands;
-    int32_t parts;
-    int32_t sync_idx;
-    uint64_t* save;
+    BlockedGeometry geo;
 };
 
 // Arguments of the persistent ensemble kernel; the table, the order and the
@@ -137,9 +141,11 @@ struct BatchLaunch {
     int32_t* err;            // set if a barrier wait of a split realization ran out of patience
     // Behind an on-chip launch with teams: its decision, and the list, which has
     // the teams' realizations as well, that takes the other's place where it is
-    // kOnChipApart (entries of order and desc to start from, and their number).
+    // kOnChipApart, with a geometry per slot that goes before the descriptor's.
     const uint64_t* decision;  // nullptr: there is one list
-    int32_t apart_order, apart_desc, apart_items;
+    const int32_t* apart_order;
+    const BlockedGeometry* apart_geometry;
+    int32_t apart_items;
     int32_t* apart;            // (host memory) set in that case
 };
 constexpr uint64_t kOnChipApart = 3;

@@ -51,11 +51,11 @@ void fake_apart(int on) { g_apart = on != 0; }
 // The last launch of the persistent kernel, and what its tables hold.
 int fake_items() { return *g_batch.n_items; }
 int fake_apart_items() { return g_batch.apart_items; }
-int fake_apart_order() { return g_batch.apart_order; }
-int fake_apart_desc() { return g_batch.apart_desc; }
-int fake_order(int k) { return g_batch.order[k]; }
-int fake_parts(int k) { return g_batch.desc[k].parts; }
-int fake_depth(int k) { return g_batch.desc[k].depth; }
+int fake_apart_order(int k) { return g_batch.apart_order[k]; }
+int fake_apart_parts(int slot) { return g_batch.apart_geometry[slot].parts; }
+int fake_apart_depth(int slot) { return g_batch.apart_geometry[slot].depth; }
+int fake_parts(int slot) { return g_batch.desc[slot].geo.parts; }
+int fake_depth(int slot) { return g_batch.desc[slot].geo.depth; }
 
 void** __hipRegisterFatBinary(const void*) { return reinterpret_cast<void**>(handle()); }
 void __hipUnregisterFatBinary(void**) {}

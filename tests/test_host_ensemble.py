@@ -34,14 +34,12 @@ lines = [l for l in log() if l.startswith(("launch", "graph"))]
 assert [n for l in lines for n in ("onchip_reset", "onchip_kernel", "ensemble_kernel", "graph") if n in l] == [
     "onchip_reset", "onchip_kernel", "ensemble_kernel"]
 assert lines[-2].endswith("teams") and lines[-1].endswith("behind teams")
-items, order, desc = fake.fake_apart_items(), fake.fake_apart_order(), fake.fake_apart_desc()
-assert fake.fake_items() == 4 and order == 4 + 3 and desc == len(sizes)  # 8192 x 8192 in four parts; three on chip
-codes = [fake.fake_order(order + k) for k in range(items)]
+assert fake.fake_items() == 4  # 8192 x 8192 in four parts; the others on chip
+codes = [fake.fake_apart_order(k) for k in range(fake.fake_apart_items())]
 assert {c & 0xfffff for c in codes} == {e.slots[i] for i in (1, 2, 3)}
-for c in codes:  # every part of a split realization is there, and no descriptor of the teams' kind
+for c in codes:  # every part of a split realization is there, with a geometry of its own
     s = c & 0xfffff
-    parts = fake.fake_parts(desc + s)
-    assert sorted(x >> 20 for x in codes if x & 0xfffff == s) == list(range(parts))
-    assert fake.fake_depth(desc + s) > 0
+    assert sorted(x >> 20 for x in codes if x & 0xfffff == s) == list(range(fake.fake_apart_parts(s)))
+    assert fake.fake_apart_depth(s) > 0
 assert fake.fake_parts(e.slots[1]) > 1 and fake.fake_depth(e.slots[1]) == 0
 """)
