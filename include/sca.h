@@ -313,8 +313,11 @@ typedef struct sca_batch_config {
     int32_t blocks_per_cu; /* persistent workgroups per compute unit, 1..8 */
     int32_t lds_bytes;     /* realizations with 32*X*Y/128 <= lds_bytes bytes of
                               state (X >= 128; 4*Y*8 bytes for X < 128) run
-                              from LDS; 0 = never, and no realization stays
-                              on chip; at most 65536 */
+                              from LDS, if they are per-site or, with
+                              block_threads = 256 and blocks_per_cu >= 2, many
+                              and of at most 512 words per sublattice; 0 =
+                              never, and no realization stays on chip; at
+                              most 65536 */
     int32_t order;         /* 0: longest remaining work first, 1: slot order */
     int32_t words_per_lane;/* word tile: 64-site words per lane in a row, 1 or 2 */
     int32_t depth;         /* realizations in global memory with dyadic p, q and

@@ -1549,6 +1549,56 @@ int sca_batch_admit(sca_batch* b, const sca_req* reqs, int32_t n, int32_t* slots
 
 namespace {
 
+// Whether the smallest realizations go to the persistent kernel's LDS after all.
+// On chip each takes a workgroup of 1024 threads, one per compute unit, mostly idle
+// below 512 words per sublattice; workgroups of 256 threads run up to three such
+// states side by side on a unit.  With many of them that is faster, with few the
+// latency of one counts, which the on-chip kernel has the lower: 60 MCS of 8192
+// lattices of 128^2 at p = 15/16 take 3.2 ms on chip and 1.5 ms in LDS, of 256 of
+// them 140 and 181 us.  Larger workgroups are no faster (512 threads, 2 per unit:
+// 0.65 us per half-step of a unit at p = 1/2, on chip 0.46), nor is one per unit.
+// Times in us, fitted to 4^2 .. 256^2 and 512 x 256 at p = 1/2, 3/4, 15/16 and 1; the
+// estimate has to be 15 % worse before a case that LDS can serve stays on chip.
+struct SmallStates {
+    static constexpr int kLdsPerCu = 160 * 1024;
+    double rounds_in_lds;               // of a compute unit for one state
+    double chip = 0, chip_longest = 0;  // of all of them on chip, and of the longest
+    double lds = 0, lds_longest = 0;    // and in LDS
+
+    explicit SmallStates(const sca_batch_config& c)
+        : rounds_in_lds(c.blocks_per_cu >= 3 && 3 * c.lds_bytes <= kLdsPerCu ? 1 : 1.45)
+    {
+    }
+    static bool served(const sca_batch_config& c)
+    {
+        return c.block_threads == 256 && c.blocks_per_cu >= 2 && 2 * c.lds_bytes <= kLdsPerCu;
+    }
+    static bool fits(const sca_batch_config& c, const EpochItem& it)
+    {
+        const int64_t words = (int64_t)it.Y * it.W;
+        return it.mask && words <= 512 && 32 * words <= c.lds_bytes;
+    }
+    void add(const EpochItem& it)
+    {
+        const int64_t words = (int64_t)it.Y * it.W;
+        const double h = 2 * (double)it.run, V = (double)it.cost / ((double)it.run * (double)words);
+        const double on_chip = 9 + h * (0.12 + 0.0048 * V + (words >= 128 ? 0.1 : 0)), loops = words > 256 ? 2 : 1;
+        chip += on_chip;
+        chip_longest = std::max(chip_longest, on_chip);
+        lds += (7 + h * (0.126 + 0.002 * V) * loops) * rounds_in_lds;
+        lds_longest = std::max(lds_longest, 15 + h * (0.75 + 0.004 * V) * loops);
+    }
+    // others: the same for the rest of the on-chip realizations
+    bool in_lds(int cus, double others, double others_longest) const
+    {
+        // beyond one round the last ones do not come out even: 661 of 32^2 make three
+        const double tail = std::max(0.0, std::min(0.4 * chip_longest, chip / cus - chip_longest));
+        const double together = std::max((chip + others) / cus + tail, std::max(chip_longest, others_longest));
+        return chip > 0 &&
+               std::max(others / cus, others_longest) + std::max(lds / cus, lds_longest) < 1.15 * together;
+    }
+};
+
 // One epoch in which slot s advances mcs_of(s) MCS (clamped to its budget).
 template <typename F>
 int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
@@ -1613,7 +1663,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
             for (int32_t P = 1; P <= max_parts; P *= 2) {
                 const int N = sca::team_rows(it.W, it.Y, P);
                 if (N == 0) continue;
-                const bool more = b->cfg.order == 0 && it.cost / P > chip_share && N > 2 && 2 * P <= max_parts;
+                const bool more = b->cfg.order == 0 && it.cost >= (chip_share + 1) * P && N > 2 && 2 * P <= max_parts;
                 if (more && sca::team_rows(it.W, it.Y, 2 * P) > 0) continue;
                 it.parts = P;
                 it.rows = N;
@@ -1630,6 +1680,24 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         b->d_team = nullptr;
         b->no_teams = true;
         teams = place(1);
+    }
+    if (SmallStates::served(b->cfg)) {
+        SmallStates small(b->cfg);
+        double others = 0, others_longest = 0;
+        for (const EpochItem& it : items) {
+            if (it.parts == 0) continue;
+            if (SmallStates::fits(b->cfg, it)) {
+                small.add(it);
+            } else {
+                const double V = (double)it.cost / ((double)it.run * it.W * it.Y);
+                const double t = 9 + 2 * (double)it.run * (0.12 + 0.006 * V * it.rows);
+                others += t * it.parts;
+                others_longest = std::max(others_longest, t);
+            }
+        }
+        if (small.in_lds(b->cu_grid, others, others_longest))
+            for (EpochItem& it : items)
+                if (SmallStates::fits(b->cfg, it)) it.parts = 0;
     }
     // The lists, as items with a key: on chip by size of team, the persistent
     // kernel's, and, should the teams not form, its list with everything but the

@@ -1,6 +1,6 @@
 // batch.hip -- many independent realizations in one persistent launch: those
-// that do not stay on chip (onchip.hip), per-site ones and the largest, or all of
-// them where the configuration says so.
+// that do not stay on chip (onchip.hip), per-site ones, the largest and many small
+// ones in small workgroups, or all of them where the configuration says so.
 //
 // A fixed grid of workgroups (a few per compute unit) pulls realizations from
 // a device work counter, largest remaining work first, and runs each one's

@@ -208,11 +208,11 @@ constexpr int kTeamThreads = 1024;
 constexpr int kTeamMessage = 128;  // 64-bit words per message and word of a lane: two for each of 64 lanes
 
 // Rows per thread (2, 4 or 8; at most eight words) with which `parts` workgroups
-// hold a lattice of Y rows of W words, or 0.
+// hold a lattice of Y rows of W words, or 0 (all of them powers of two).
 inline int team_rows(int W, int64_t Y, int parts)
 {
-    if (W > 128 || Y % parts != 0) return 0;
-    const int64_t R = Y / parts;
+    if (W > 128 || Y < parts) return 0;
+    const int64_t R = Y >> __builtin_ctz((unsigned)parts);
     for (int N = 2; N <= (W > 64 ? 4 : 8); N *= 2)
         if (R % N == 0 && R / N * (W > 64 ? 64 : W) <= kTeamThreads) return N;
     return 0;

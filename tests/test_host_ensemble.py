@@ -43,3 +43,28 @@ for c in codes:  # every part of a split realization is there, with a geometry o
     assert fake.fake_apart_depth(s) > 0
 assert fake.fake_parts(e.slots[1]) > 1 and fake.fake_depth(e.slots[1]) == 0
 """)
+
+
+def test_many_small_states_share_a_compute_unit(host):
+    """Workgroups of 256 threads run many small states side by side in LDS, as
+    their configuration says; few of them, larger ones and other workgroups stay on chip."""
+    host("""
+def routes(n, X, Y, p, run=60, more=(), **config):
+    e = Ensemble([(X, Y)] * n + list(more), n_mcs=10**6, p=p, **config)
+    log()
+    assert e.run(run) == 0
+    lines = log()
+    return len(launches("onchip_kernel", lines)), len([l for l in lines if l == "graph launch" or "ensemble_kernel" in l])
+
+small = dict(block_threads=256, blocks_per_cu=8, lds_bytes=16384)
+for p in (0.5, 0.9375, 1.0, 0.75):
+    for X, Y in ((8, 8), (64, 64), (128, 128), (256, 256)):
+        assert routes(2048, X, Y, p, **small)[0] == 0, (X, Y, p)
+        assert routes(200, X, Y, p, **small) == (1, 0), (X, Y, p)
+        assert routes(2048, X, Y, p) == (1, 0) and routes(2048, X, Y, p, block_threads=1024, blocks_per_cu=1) == (1, 0)
+    assert routes(2048, 512, 512, p, **small) == (1, 0)
+assert routes(2048, 64, 64, 0.5, lds_bytes=65536, block_threads=256, blocks_per_cu=1) == (1, 0)
+# beside one that lasts longer than all of them on chip they cost nothing there
+assert routes(300, 64, 64, 0.5, more=[(1024, 1024)], **small) == (1, 1) and fake.fake_items() == 0
+assert routes(4000, 64, 64, 0.5, more=[(1024, 1024)], **small) == (1, 1) and fake.fake_items() == 4000
+""")
