@@ -57,7 +57,12 @@ enum class Draws : int { Any = 0, Even = 1, OddTail = 2 };
 // one call (g, t, n-1, 0): lanes 0|1 in the even half-step, 2|3 in the odd
 // one.  OddTail: the even half-step leaves lanes 2|3 of that call in *tail
 // and the odd one takes its draw from there instead of calling again.
-template <Draws D = Draws::Any>
+// SCALAR_TAIL: that call's first two rounds go through the scalar unit as every
+// other call's do (philox_word).  The row sweeps without removals leave it out:
+// there, 2^16 x 2^16 sites at p = 1/2, whose only call it is, take 121.2 us per MCS
+// with them and 119.4 us without (p = 7/8 193.3 and 191.8); with removals
+// 136.6 us with them and 138.0 us without (p = q = 1/2).
+template <Draws D = Draws::Any, bool SCALAR_TAIL = true>
 __device__ __forceinline__ void mask_words(const SweepArgs& a, uint32_t g, bool has_q, uint64_t& xp, uint64_t& xq,
                                            uint64_t* tail = nullptr)
 {
@@ -73,7 +78,8 @@ __device__ __forceinline__ void mask_words(const SweepArgs& a, uint32_t g, bool 
         if (a.parity == 1) {
             r = *tail;
         } else {
-            const u32x4 o = philox_word(g, a.t, 2u * (uint32_t)j, a.k0, a.k1);
+            const u32x4 o = SCALAR_TAIL ? philox_word(g, a.t, 2u * (uint32_t)j, a.k0, a.k1)
+                                        : philox4x32_10(g, a.t, 2u * (uint32_t)j, 0u, a.k0, a.k1);
             r = (uint64_t)o.v0 | ((uint64_t)o.v1 << 32);
             *tail = (uint64_t)o.v2 | ((uint64_t)o.v3 << 32);
         }
@@ -235,7 +241,7 @@ __device__ __forceinline__ void apply_xplus(uint64_t (&D)[I], const uint64_t (&M
 // D: what the caller knows of the number of draws (mask_words); with
 // Draws::OddTail, tail holds the I words that carry the shared last draw from
 // the row's even half-step to its odd one.
-template <int G, int I, XiMode MODE, bool HASQ, Draws D = Draws::Any>
+template <int G, int I, XiMode MODE, bool HASQ, Draws D = Draws::Any, bool SCALAR_TAIL = true>
 __device__ __forceinline__ void row_masks(const SweepArgs& a, int64_t y, int gl, uint64_t (&A)[I], uint64_t (&B)[I],
                                           uint64_t (&C)[I], const uint64_t (&XP)[I], uint64_t (&M)[I],
                                           uint64_t& mp0, uint64_t& mq0, uint64_t* tail = nullptr)
@@ -245,7 +251,7 @@ __device__ __forceinline__ void row_masks(const SweepArgs& a, int64_t y, int gl,
         const uint32_t g = (uint32_t)(y * a.W + i * G + gl);
         uint64_t xip, xiq;
         if constexpr (MODE == XiMode::Mask) {
-            mask_words<D>(a, g, HASQ, xip, xiq, D == Draws::OddTail ? tail + i : nullptr);
+            mask_words<D, SCALAR_TAIL>(a, g, HASQ, xip, xiq, D == Draws::OddTail ? tail + i : nullptr);
         } else if constexpr (MODE == XiMode::PerSite) {
             persite_words(a, g, HASQ, xip, xiq);
         } else if constexpr (MODE == XiMode::Fixed) {
