@@ -7,8 +7,8 @@ every configuration leaves bit-identical states, and keeps the fastest.  The
 sample should keep the ensemble's mix: with the MCS budgets scaled down
 uniformly it has the same ratio of the longest realization (which one
 workgroup runs alone) to the total work, so the ranking carries over.
-Realizations that stay on chip (dyadic p, q, up to 2^23 sites) run alike under
-all of them; the choice matters for the others.
+Realizations that stay on chip (dyadic p, q, up to 2^24 sites) run alike under
+all of these candidates; the choice matters for the others.
 The choice is cached in a JSON file keyed by the device name and the sample's
 signature.
 """

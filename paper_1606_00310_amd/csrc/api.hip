@@ -39,7 +39,9 @@ struct ProbCode {
 // number of `depth`-MCS passes, then the remainder r < 2*depth as two passes
 // of ceil(r/2) and floor(r/2) MCS, or, for r = 1, two half-step launches.
 // Lattices that one workgroup holds may run in place in one launch instead.
-// The per-site path runs unfused from X = 8192 on, where it is ALU-bound.
+// The per-site path runs unfused from X = 8192 on: with many rows it is ALU-bound
+// (2^14 squared: 52 us per half-step, 93 % of the issue rate); with few, 8192 x 64,
+// it is not, and takes two launches per MCS all the same.
 struct StepPlan {
     ProbCode P, Q;
     bool persite = false, has_q = false, draw_free = false;
@@ -325,11 +327,14 @@ constexpr int64_t kWholeMcs = 1 << 14;
 //    waves on its SIMD (0.065 k us); it moves its bytes at 4.7 TB/s, or 6.5 TB/s
 //    where the caches hold both states;
 //  - a half-step launch takes 2.95 us or its state's MB at about 5 TB/s.
-// Against the rule before (bands by width alone, and none below X = 8192) 1440
-// combinations of 60 sizes, four probabilities and 1 .. 100 MCS got faster by
-// 2.3 in the geometric mean (2^10 x 2^9 at p = 1/2: 5.2 to 0.9 us per MCS; 2^12
-// squared at p = 3/4, q = 1/4: 6.1 to 2.4 us; 2^14 squared at p = 1: 12 to 6.7
-// us), and none slower by more than a tenth.
+// Against the rule before (bands by width alone, and none below X = 8192) 4489
+// combinations of 140 sizes, five probabilities and 1 .. 60 MCS got faster by 2.5
+// in the geometric mean, teams included (2^10 x 2^9 at p = 1/2: 5.2 to 0.9 us per
+// MCS; 2^12 squared at p = 3/4, q = 1/4: 6.1 to 2.4 us; 2^14 squared at p = 1: 12 to
+// 3.5 us), and none of 2 MCS and more slower by more than 7 % (2^13 x 2^12 at p = 1,
+// 2 MCS: 13.9 to 15.0 us).  Single MCS of lattices above one workgroup's size are the
+// two launches that they were.  The choice is not always the best: 2^12 x 2^16 at
+// p = 1/2, 8 MCS, takes 86 us as a team and 77 us in tiles.
 struct CostModel {
     double V, draws, mb;  // mb: the state in MB
     int64_t Y;

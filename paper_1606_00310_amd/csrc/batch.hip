@@ -62,12 +62,21 @@ __device__ __forceinline__ void all_rows_mode(const SweepArgs& a, uint64_t* S, i
     }
 }
 
+// Whether workgroups of BLOCK threads take a state of this mode into LDS: the host
+// sends bit-mask ones there with 256 threads only, and on chip otherwise.
+template <int BLOCK>
+__device__ __forceinline__ bool lds_serves(int mode)
+{
+    return BLOCK == 256 || mode != 0;
+}
+
 // Half-step over a state in LDS (W <= 8: at most 64 KiB fits only such rows
 // of a lattice with X*Y <= 2^18).
 template <int NWAVES, int IW>
 __device__ __forceinline__ void halfstep_lds(const SweepArgs& a, uint64_t* S, int mode, bool has_q, int wave,
                                              int lane)
 {
+    if (!lds_serves<64 * NWAVES>(mode)) __builtin_unreachable();
     switch (a.W) {
     case 1: all_rows_mode<1, NWAVES, IW>(a, S, mode, has_q, wave, lane); break;
     case 2: all_rows_mode<2, NWAVES, IW>(a, S, mode, has_q, wave, lane); break;
@@ -531,7 +540,7 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
         SweepArgs a = args_of(d);
         const bool has_q = d.has_q != 0;
         const int64_t words = 4 * d.plane;
-        const bool in_lds = d.W <= 8 && words * 8 <= (int64_t)L.lds_bytes;
+        const bool in_lds = d.W <= 8 && words * 8 <= (int64_t)L.lds_bytes && lds_serves<BLOCK>(d.mode);
 
         if (in_lds) {
             for (int64_t i = threadIdx.x; i < words; i += BLOCK) lds[i] = d.S[i];

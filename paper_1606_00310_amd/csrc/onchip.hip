@@ -23,7 +23,8 @@
 // through memory and take 0.36 s; a 2048^2 lattice alone at p = 1/2 takes 2.4 us
 // per MCS on a team of sixteen, whose half-steps wait for messages (3.8 us on
 // eight; p = 15/16: 4.0 and 7.1 us).  A workgroup
-// per CU: eight rows per thread fill the 128 registers that 1024 threads leave.
+// per CU: eight rows per thread fill the 128 registers that 1024 threads leave, and
+// 67 more go to scratch in this one kernel of all twelve forms (96 bytes per lane).
 #include "sca_internal.hpp"
 #include "team.hpp"
 

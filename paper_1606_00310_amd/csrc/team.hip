@@ -6,7 +6,8 @@
 // large for the tiles: bands of 16 to 32 rows compute every row 1.25 to 1.5
 // times, and the state passes through memory every few MCS.  Here it does so
 // once per call.  Bound by vector issue with eight words per thread, by the
-// 1.25 us of a message per half-step with two.  us for 64 MCS with the sweeps or
+// 1.25 us of a message per half-step with two.  (With eight words 2 to 19 registers
+// of the 128 that 1024 threads leave go to scratch.)  us for 64 MCS with the sweeps or
 // tiles, and as a team:
 //                    p = 1/2      3/4, 1/4      15/16          p = 1
 //   2^14 x 2^14    941 -> 426   1355 -> 642   1678 -> 846   379 -> 224

@@ -28,7 +28,7 @@
 // write, barrier, LDS read, the row's masks: 0.13 us at p = 1, 0.16 us at p =
 // 1/2), with eight and more waves the vector issue.  Against two launches per
 // MCS (2.8 us each, 1.6 us of it in the kernel): 128 x 128 at p = 1/2, 1000 MCS,
-// 5.80 to 0.32 ms; 2^12 x 2^12 at p = 3/4, q = 1/4, 6.1 to 2.4 us per MCS, of
+// 5.80 to 0.30 ms; 2^12 x 2^12 at p = 3/4, q = 1/4, 6.1 to 2.4 us per MCS, of
 // which half is the recomputed halo (16-row bands, 12 MCS per pass).
 #pragma once
 

@@ -27,7 +27,8 @@ class Lattice:
         self.slopes = torch.empty((2, 2, self.Y, self.W), dtype=torch.int64, device=self.device)
         self.aux = torch.zeros(L.SCA_AUX_LEN, dtype=torch.int64, device=self.device)
         # passes of several MCS run out of place into a second buffer of the
-        # state's size
+        # state's size, so that a lattice takes twice its state; one whose steps
+        # all run in one workgroup or one by one could do without
         self.pass_buffer = torch.empty_like(self.slopes)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         ctx = ctypes.c_void_p()

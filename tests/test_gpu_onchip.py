@@ -185,3 +185,19 @@ def test_teams_of_sixteen(sca, p, q):
     reals = [R(2048, 2048, p, q, 33, 70)]
     b, slots = run_batch(reals)
     check_solo(sca, b, slots, reals)
+
+
+@pytest.mark.parametrize("config", [dict(), dict(block_threads=1024, blocks_per_cu=1, depth=2, max_parts=4),
+                                    dict(block_threads=512, blocks_per_cu=1, depth=4, max_parts=4),
+                                    dict(block_threads=512, blocks_per_cu=1, depth=3, order=1)],
+                         ids=["default", "split", "deep", "slot-order"])
+def test_beside_blocked_passes(sca, config):
+    """One epoch with realizations on chip, in teams, and ones that no team holds:
+    blocked passes of the persistent kernel, split and whole, and per-site ones."""
+    from paper_1606_00310_amd.batch import Realization as R
+
+    reals = [R(8192, 4096, 0.5, 0.0, 7, 1), R(64, 64, 0.5, 0.0, 30, 2), R(8192, 8192, 0.75, 0.25, 5, 3),
+             R(2048, 2048, 0.9375, 0.0, 9, 4), R(512, 512, 0.3, 0.1, 4, 5), R(1024, 131072, 0.5, 0.5, 4, 6),
+             R(8192, 4096, 1.0, 0.0, 6, 7), R(256, 256, 0.625, 0.125, 11, 8)]
+    b, slots = run_batch(reals, epochs=(3, 1), **config)
+    check_solo(sca, b, slots, reals)
