@@ -1221,9 +1221,10 @@ struct sca_batch {
     int32_t* d_counters = nullptr;  // kCounters words, see below
     int64_t* d_ws = nullptr;        // moments workspace for Y up to 131072
     // sca_batch_collect: kCollect result slots of 8 words (the first one is also
-    // sca_batch_roughness's), behind them as many items, and a word that an
-    // on-chip launch sets whose teams could not form; pinned
+    // sca_batch_roughness's), behind them as many items, a word that a launch sets
+    // whose teams could not form, and two lists for those in turn; pinned
     int64_t* results = nullptr;
+    int apart_at = 0;               // the list of the last epoch with teams
     // pinned staging
     sca::BatchDesc* h_desc = nullptr;
     int32_t* h_order = nullptr;
@@ -1264,6 +1265,24 @@ sca::MomentsItem* collect_items(const sca_batch* b)
 }
 
 int32_t* batch_apart(const sca_batch* b) { return reinterpret_cast<int32_t*>(collect_items(b) + kCollect); }
+
+// The list of an epoch for teams that do not form, and its geometries by slot.  An
+// epoch's launches may still read one of the two of them when the next is planned;
+// the one before has ended, as this epoch waited for the last one's copies.
+size_t apart_orders(const sca_batch* b) { return ((size_t)b->max_slots + (size_t)b->num_cus * 8 + 1) / 2 * 2; }
+
+size_t apart_bytes(const sca_batch* b)
+{
+    return sizeof(sca::BlockedGeometry) * (size_t)b->max_slots + sizeof(int32_t) * apart_orders(b);
+}
+
+sca::BlockedGeometry* apart_geometry(const sca_batch* b)
+{
+    return reinterpret_cast<sca::BlockedGeometry*>(reinterpret_cast<uint8_t*>(batch_apart(b)) + sizeof(int64_t) +
+                                                   apart_bytes(b) * (size_t)b->apart_at);
+}
+
+int32_t* apart_order(const sca_batch* b) { return reinterpret_cast<int32_t*>(apart_geometry(b) + b->max_slots); }
 
 int bfail(sca_batch* b)
 {
@@ -1397,10 +1416,9 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
     }
     // the work queue holds one item per realization, plus one more per extra
     // part of a split realization (at most one part per persistent workgroup
-    // in all, and at most 8 of those per compute unit); the table has a second
-    // geometry and the order a second list, for teams that do not form
-    const size_t nd = (sizeof(sca::BatchDesc) + sizeof(sca::BlockedGeometry)) * (size_t)max_slots,
-                 no = 2 * sizeof(int32_t) * ((size_t)max_slots + (size_t)b->num_cus * 8);
+    // in all, and at most 8 of those per compute unit)
+    const size_t nd = sizeof(sca::BatchDesc) * (size_t)max_slots,
+                 no = sizeof(int32_t) * ((size_t)max_slots + (size_t)b->num_cus * 8);
     if (hipMalloc(&b->d_desc, nd) != hipSuccess || hipMalloc(&b->d_order, no) != hipSuccess ||
         hipMalloc(&b->d_counters, kCounters * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(&b->d_ws, sizeof(int64_t) * (size_t)(4 * 131072 + 8)) != hipSuccess ||
@@ -1414,7 +1432,7 @@ int sca_batch_create(sca_batch** out, int32_t max_slots, void* arena_dev, size_t
         hipMalloc(&b->d_sync, sizeof(int32_t) * (size_t)b->num_cus * 8) != hipSuccess ||
         hipMalloc(&b->d_err, sizeof(int32_t)) != hipSuccess ||
         hipHostMalloc(&b->h_err, sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(&b->results, kCollect * (8 * sizeof(int64_t) + sizeof(sca::MomentsItem)) + sizeof(int64_t),
+        hipHostMalloc(&b->results, kCollect * (8 * sizeof(int64_t) + sizeof(sca::MomentsItem)) + sizeof(int64_t) + 2 * apart_bytes(b),
                       hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&b->err_copied, hipEventDisableTiming) != hipSuccess ||
         hipMemsetAsync(b->d_err, 0, sizeof(int32_t), b->stream) != hipSuccess) {
@@ -1731,13 +1749,14 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
             apart_total += it.sites;
         }
     }
+    b->epoch_whole.reserve(items.size());  // nothing is allocated once the first kernel is launched
+    b->epoch_plain.reserve(items.size());
     const auto longer = [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
         return x.first > y.first;
     };
     // The save areas and their depth decide which realizations can run blocked.
-    if (!work.empty() || teams) prepare_launch(b);
+    if (!work.empty()) prepare_launch(b);
     const int32_t grid = b->num_cus * b->cfg.blocks_per_cu;
-    const int32_t max_depth = b->save_words > 0 ? b->cfg.depth : 0;
     // The persistent kernel's list of `list` (site updates in all: sum) into `order`;
     // returns its length.  geometry(slot) is where the realization's goes.
     // Realizations that run as temporally blocked passes go first (the
@@ -1753,6 +1772,7 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
                          auto&& geometry) {
         if (b->cfg.order == 0) std::stable_sort(list.begin(), list.end(), longer);
         const int64_t avg = sum / grid;
+        const int32_t max_depth = b->save_words > 0 ? b->cfg.depth : 0;
         int32_t parts_used = 0, split = 0, n = 0;
         auto &whole = b->epoch_whole, &plain = b->epoch_plain;
         whole.clear();
@@ -1799,18 +1819,8 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         for (const auto& w : list) b->h_order[count++] = items[(size_t)w.second].slot;
     }
     const bool on_chip = count > n_work;
-    // Should the teams not form: split over half of the workgroups at most, as
-    // something else holds others.  The geometries follow the table.
-    const int32_t apart_order = count;
-    auto* const geometries = reinterpret_cast<sca::BlockedGeometry*>(b->h_desc + (hi + 1));
-    const int32_t apart_items =
-        teams ? list_work(apart_work, apart_total, b->resident / 2, b->h_order + count,
-                          [geometries](int32_t slot) -> sca::BlockedGeometry& { return geometries[slot]; })
-              : 0;
-    count += apart_items;
-    const size_t table =
-        (sizeof(sca::BatchDesc) + (teams ? sizeof(sca::BlockedGeometry) : 0)) * (size_t)(hi + 1);
-    if (hipMemcpyAsync(b->d_desc, b->h_desc, table, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+    if (hipMemcpyAsync(b->d_desc, b->h_desc, sizeof(sca::BatchDesc) * (size_t)(hi + 1), hipMemcpyHostToDevice,
+                       b->stream) != hipSuccess ||
         hipMemcpyAsync(b->d_order, b->h_order, sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, b->stream) !=
             hipSuccess ||
         hipMemcpyAsync(b->d_counters, b->h_count, kCounters * sizeof(int32_t), hipMemcpyHostToDevice, b->stream) !=
@@ -1830,13 +1840,21 @@ int batch_epoch(sca_batch* b, F mcs_of, int32_t* active_out)
         if (sca::launch_onchip(L, b->cu_grid, teams, b->stream) != hipSuccess) return bfail(b);
     }
     if (teams) {
-        // behind teams, in one launch of this epoch's own: nothing to reset, and the
-        // list is chosen by what became of them
+        // Behind teams the persistent kernel takes the list that became of them, in a
+        // launch of this epoch's own.  The list for teams that did not form is
+        // made here, while the others run, and read where the host wrote it, if at
+        // all: on the device it cost the epochs that need none of it some 15 us.
+        // Splits use half of the workgroups at most, as something else holds others.
+        prepare_launch(b);
+        b->apart_at ^= 1;
+        int32_t* const order = apart_order(b);
+        sca::BlockedGeometry* const geometry = apart_geometry(b);
         sca::BatchLaunch L = b->launch;
         L.decision = sca::onchip_decision(b->d_team);
-        L.apart_order = b->d_order + apart_order;
-        L.apart_geometry = reinterpret_cast<const sca::BlockedGeometry*>(b->d_desc + (hi + 1));
-        L.apart_items = apart_items;
+        L.apart_items = list_work(apart_work, apart_total, b->resident / 2, order,
+                                  [geometry](int32_t slot) -> sca::BlockedGeometry& { return geometry[slot]; });
+        L.apart_order = order;
+        L.apart_geometry = geometry;
         L.apart = batch_apart(b);
         if (sca::launch_ensemble(L, b->cfg.block_threads, b->cfg.words_per_lane, grid, b->stream) != hipSuccess)
             return bfail(b);
