@@ -10,7 +10,8 @@
 // counters (g, t, 2j+parity, 0), so its state is bit-identical to a solo run
 // whatever the launch shape or the order.
 //
-// States small enough for the workgroup's LDS budget are copied into LDS once
+// States small enough for the workgroup's LDS budget (per-site ones, and bit-mask
+// ones in workgroups of 256 threads) are copied into LDS once
 // per epoch and all their half-steps run there; larger ones are updated in
 // place in the arena, where they stay L2 / Infinity-Cache resident while one
 // workgroup works on them, and those with rows of 8..64 words run as
