@@ -501,6 +501,7 @@ __global__ __launch_bounds__(BLOCK) void ensemble_kernel(BatchLaunch L)
     int32_t n_items = *L.n_items;
     const bool apart = L.decision && *L.decision == kOnChipApart;
     if (apart) n_items = L.apart_items;
+    if (n_items == 0) return;  // behind teams that formed, mostly
     if (threadIdx.x == 0) {
         s_list = {apart ? L.apart_order : L.order, apart ? L.apart_geometry : nullptr};
         if (apart && blockIdx.x == 0) __hip_atomic_store(L.apart, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
