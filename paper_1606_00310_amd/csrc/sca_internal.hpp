@@ -260,7 +260,8 @@ void team_kernel_name(const SweepArgs& a, bool has_q, int rows, char* out, size_
 
 // After a launch whose teams did not form, this many steps of the lattice, or
 // epochs of the ensemble, go without.  An attempt in vain costs a quarter of a
-// millisecond, a hundredth of what these take at the smallest sizes.
+// millisecond, one to two hundredths of what these take where they are shortest
+// (2^25 sites or one 2048^2 realization, two MCS each).
 constexpr int32_t kTeamPause = 256;
 
 // Realizations that stay on chip for an epoch (onchip.hip): bit-mask mode, in
