@@ -125,3 +125,22 @@ def test_ensemble(sca, X, Y, config):
         if apart:
             return
     raise AssertionError("the teams formed every time")
+
+
+@pytest.mark.parametrize("X,Y", [(8192, 8192), (8192, 16384), (16384, 4096)])
+@pytest.mark.parametrize("p,q", [(0.5, 0.0), (0.75, 0.25)])
+@pytest.mark.parametrize("held", [False, True])
+def test_a_step_of_two_launches(sca, X, Y, p, q, held):
+    """513 MCS: a launch of as many as one takes, and one of a single MCS, whose
+    band passes are a copy and an MCS."""
+    lat, ref = sca.Lattice(X, Y, seed=8), sca.Lattice(X, Y, seed=8)
+    for each in (lat, ref):
+        each.step(3, 0.75, 0.25, fuse=False)
+    assert lat.plan(513, p, q)["kernel"].startswith("team_kernel")
+    holder = Holder()
+    if held:
+        holder.hold()
+    lat.step(513, p, q)
+    torch.cuda.synchronize()
+    ref.step(513, p, q, fuse=False)
+    assert torch.equal(lat.slopes, ref.slopes) and lat.meta() == ref.meta()
